@@ -108,7 +108,7 @@ def cpu_baseline(n, gates, budget_s):
                             "sample": f"first {done_one} gates on one thread, {el_one:.1f} s"}}
 
 
-TILE_SOURCES = ("k_tile.hip", "tile_ops.hpp", "juqcs_internal.hpp")
+TILE_SOURCES = ("k_block.hip", "block_ops.hpp", "block.cpp", "juqcs_internal.hpp")
 TUNING_RECORD = os.path.join(ROOT, "paper_1912_03243_amd", "tuning_mi355x.json")
 
 
@@ -288,8 +288,8 @@ def main():
         roofline = {"bound": "alu", "achieved": tflops, "peak": FP64_VECTOR_PEAK_TFLOPS,
                     "unit": "TFLOP/s", "frac": tflops / FP64_VECTOR_PEAK_TFLOPS,
                     "traffic": traffic_for(TILE_SOURCES),
-                    "kernel": ("k_tile_fixed<double,12,512>" if tune and tune["tile_bits"] == 12
-                               else "k_tile_fixed<double,13,1024>"),
+                    "kernel": ("k_block<double,12,4>" if tune and tune["tile_bits"] == 12
+                               else "k_block<double,13,4>"),
                     "flops_per_launch": flops_launch, "avg_launch_ms": pass_ms, "hbm": hbm}
     elif chosen == "fused":
         tf = mma_flops / max(passes, 1) / (pass_ms / 1e3) / 1e12
@@ -832,8 +832,8 @@ def other_workload(args, juqcs, W, dev, stream, emit=True):
                          "unit": "TFLOP/s", "frac": tf / FP32_MFMA_PEAK_TFLOPS,
                          "frac_of_fp32_valu": tf / FP64_VECTOR_PEAK_TFLOPS,
                          "flops_per_launch": fl / passes, "avg_launch_ms": kms / passes,
-                         "kernel": (("k_tile_fixed<float,12,512>" if tune and tune["tile_bits"] == 12
-                                     else "k_tile_fixed<float,13,1024>") if dtype == "c64"
+                         "kernel": (("k_block<float,12,4>" if tune and tune["tile_bits"] == 12
+                                     else "k_block<float,13,4>") if dtype == "c64"
                                     else "k_tile_enc2_fixed<13>"),
                          "hbm": {"achieved_GBps": achieved, "peak_GBps": HBM_PEAK_GBPS,
                                  "frac": achieved / HBM_PEAK_GBPS, "bytes_per_launch": kb / passes}},

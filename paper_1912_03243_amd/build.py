@@ -18,7 +18,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libjuqcs_gpu.so")
 
-SOURCES = ["api.cpp", "planner.cpp", "batch.cpp", "k_gates.hip", "k_tile.hip",
+SOURCES = ["api.cpp", "planner.cpp", "block.cpp", "batch.cpp", "k_gates.hip", "k_tile.hip", "k_block.hip",
            "k_fused.hip", "k_codec.hip", "k_batch.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

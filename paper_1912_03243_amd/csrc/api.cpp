@@ -206,6 +206,25 @@ juqcs_status run_tile_plan(juqcs_state* st, const TilePlan& plan) {
   return JUQCS_OK;
 }
 
+// Runs a register-resident plan: one upload, then every pass.
+juqcs_status run_block_plan(juqcs_state* st, const BlkPlan& plan) {
+  if (plan.passes.empty()) return JUQCS_OK;
+  std::vector<char> buf;
+  const BlkLayout lay = block_image(plan, st->dt == JUQCS_C128, &buf);
+  char* dev = nullptr;
+  if (juqcs_status rc = upload(st, buf.data(), buf.size(), &dev)) return rc;
+  for (size_t i = 0; i < plan.passes.size(); ++i) {
+    const BlkPass& p = plan.passes[i];
+    prof_begin(st);
+    hipError_t e = launch_block(st->dt, st->amps, p.g, (const BlkGeom*)(dev + lay.o_geoms) + i,
+                                block_device(lay, dev, p), st->stream);
+    prof_end(st);
+    if (e != hipSuccess) return hip_fail(e, "tile pass launch");
+    st->bytes += full_pass_bytes(st);
+  }
+  return JUQCS_OK;
+}
+
 // Defaults measured on MI355X for layered circuits (2^b-amplitude tiles,
 // chunks of 2^L contiguous amplitudes).
 void default_tile_bits(juqcs_dtype dt, int B, int* L, int* b) {
@@ -273,6 +292,7 @@ juqcs_status tile_gates(juqcs_state* st, const std::vector<Gate>& gates, int L, 
   if (st->dt == JUQCS_ENC2 && b < L + 2) b = std::min(maxb, L + 2);  // room for two gathered qubits
   if (st->n > b && b - L < 2)
     return fail(JUQCS_ERR_ARG, "a tile needs at least two gathered bits (tile_bits >= low_bits + 2)");
+  const bool block = kin <= 0;  // no fusion width asked for
   if (kin <= 0) kin = 3;
   if (kin > 4) return fail(JUQCS_ERR_ARG, "in-pass fusion width must be 1..4");
   if (pass_gates < -1) return fail(JUQCS_ERR_ARG, "pass_gates must be >= -1");
@@ -281,8 +301,18 @@ juqcs_status tile_gates(juqcs_state* st, const std::vector<Gate>& gates, int L, 
   const int mcap = tile_mma_cap(st->dt, std::min(b, st->n));
   const int l = std::min(L, st->n);
   const bool rl = relabel >= 0;
-  TilePlan plan;
   std::vector<int> moved;  // moved[p]: physical bit that the qubit at bit p ends on
+  if (block && block_sized(st->dt, std::min(b, st->n))) {
+    BlkPlan bp;
+    if (plan_block(st->n, l, b, gates, st->dt == JUQCS_C128, std::max(pass_gates, 0), rl, &bp, &moved)) {
+      if (passes) *passes = (int64_t)bp.passes.size();
+      if (juqcs_status rc = run_block_plan(st, bp)) return rc;
+      if (rl)
+        for (int q = 0; q < st->n; ++q) st->phys[q] = moved[st->phys[q]];
+      return JUQCS_OK;
+    }
+  }
+  TilePlan plan;
   if (pass_gates != 0 || st->dt == JUQCS_C128) {
     plan_tiles(st->n, l, b, st->B, gates, &plan, kin, cap, std::max(pass_gates, 0), mcap, rl, &moved);
   } else {

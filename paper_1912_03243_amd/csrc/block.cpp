@@ -1,0 +1,948 @@
+// Planning of register-resident tile programs (block_ops.hpp): the circuit's
+// gates rewritten as rotations and phases, and every tile pass turned into
+// stages of register, lane and wave bits with their ops.  Pure C++.
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+
+#include "juqcs_internal.hpp"
+
+namespace juqcs {
+
+namespace {
+
+using C = cplx<double>;
+
+C mul(C a, C b) { return C{a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
+C div(C a, C b) {
+  // scaled by the larger part of b (Smith), so that |b|^2 cannot overflow
+  if (std::fabs(b.re) >= std::fabs(b.im)) {
+    const double r = b.im / b.re, d = b.re + b.im * r;
+    return C{(a.re + a.im * r) / d, (a.im - a.re * r) / d};
+  }
+  const double r = b.re / b.im, d = b.re * r + b.im;
+  return C{(a.re * r + a.im) / d, (a.im * r - a.re) / d};
+}
+double absv(C a) { return std::hypot(a.re, a.im); }
+bool zero(C a) { return a.re == 0.0 && a.im == 0.0; }
+bool one(C a) { return a.re == 1.0 && a.im == 0.0; }
+bool finite(C a) { return std::isfinite(a.re) && std::isfinite(a.im); }
+
+// Collects the single-qubit gates of each qubit until a gate that does not
+// commute with them, then emits them as one gate.
+struct Rewriter {
+  double tol;
+  std::vector<BlkGate>* out;
+  struct Open {
+    bool any = false;
+    C m[4];
+  };
+  std::vector<Open> open;
+
+  void single(int q, const C* u) {
+    Open& w = open[q];
+    if (!w.any) {
+      w.any = true;
+      for (int i = 0; i < 4; ++i) w.m[i] = u[i];
+      return;
+    }
+    C r[4];
+    for (int i = 0; i < 2; ++i)
+      for (int j = 0; j < 2; ++j) r[2 * i + j] = cmad(u[2 * i + 1], w.m[2 + j], mul(u[2 * i], w.m[j]));
+    for (int i = 0; i < 4; ++i) w.m[i] = r[i];
+  }
+
+  void push_phase(int q, C lam, C ph) {
+    if (one(ph) && one(lam)) return;
+    BlkGate g;
+    g.kind = BlkGate::PHASE1;
+    g.q[0] = q;
+    g.ph = ph;
+    g.lam = lam;
+    out->push_back(g);
+  }
+
+  // Emits what is open on qubit q.  all = false: a diagonal may stay open
+  // (the next gate on q commutes with diagonals).
+  void flush(int q, bool all) {
+    Open& w = open[q];
+    if (!w.any) return;
+    const C a = w.m[0], b = w.m[1], c = w.m[2], d = w.m[3];
+    if (zero(b) && zero(c)) {
+      if (!all) return;
+      w.any = false;
+      const C ph = zero(a) ? C{0, 0} : div(d, a);
+      if (!zero(a) && finite(ph) && finite(div(C{1, 0}, ph))) {
+        push_phase(q, a, ph);
+        return;
+      }
+      dense(q, w.m);
+      return;
+    }
+    // diag(lam, mu) R diag(1, p) with R = [[1, -t], [t, 1]] (|a| >= |c|) or
+    // [[t, -1], [1, t]]: three entries are met by construction, the fourth
+    // tells whether the matrix has this form
+    const double na = absv(a), nc = absv(c);
+    const double scale = std::max(std::max(na, nc), std::max(absv(b), absv(d)));
+    BlkGate g;
+    g.kind = BlkGate::ROT;
+    g.q[0] = q;
+    C lam, mu, miss;
+    bool ok = false;
+    g.formb = nc > na;
+    if (!g.formb && nc > 0.0) {
+      g.t = nc / na;
+      lam = a;
+      mu = C{c.re / g.t, c.im / g.t};
+      g.ph = div(d, mu);
+      const C x = mul(lam, g.ph);
+      miss = C{b.re + g.t * x.re, b.im + g.t * x.im};
+      ok = g.t > 0.0;
+    } else if (g.formb) {
+      g.t = na / nc;
+      mu = c;
+      lam = g.t > 0.0 ? C{a.re / g.t, a.im / g.t} : mu;
+      g.ph = div(C{-b.re, -b.im}, lam);
+      const C x = mul(mu, g.ph);
+      miss = C{d.re - g.t * x.re, d.im - g.t * x.im};
+      ok = true;
+    }
+    if (ok) {
+      const C rest = div(mu, lam);
+      ok = finite(lam) && finite(g.ph) && finite(rest) && finite(div(C{1, 0}, g.ph)) && !zero(lam) &&
+           absv(miss) <= tol * scale;
+      if (ok) {
+        g.lam = lam;
+        out->push_back(g);
+        w.m[0] = C{1, 0};
+        w.m[1] = w.m[2] = C{0, 0};
+        w.m[3] = rest;
+        w.any = !one(rest);
+        if (all && w.any) {
+          w.any = false;
+          push_phase(q, C{1, 0}, rest);
+        }
+        return;
+      }
+    }
+    w.any = false;
+    dense(q, w.m);
+  }
+
+  void dense(int q, const C* m) {
+    BlkGate g;
+    g.kind = BlkGate::DENSE;
+    g.q[0] = q;
+    for (int i = 0; i < 4; ++i) g.m[i] = m[i];
+    out->push_back(g);
+  }
+};
+
+}  // namespace
+
+bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<BlkGate>* out) {
+  out->clear();
+  Rewriter rw;
+  rw.tol = tol;
+  rw.out = out;
+  rw.open.resize(n);
+  for (const Gate& g : gates) {
+    if (g.nq == 1) {
+      rw.single(g.q[0], g.m);
+      continue;
+    }
+    const C* m = g.m;  // index b_q0 + 2 b_q1
+    BlkGate b;
+    b.q[0] = g.q[0];
+    b.q[1] = g.q[1];
+    bool diag = one(m[0]) && one(m[5]) && one(m[10]), cnot = one(m[0]) && one(m[10]) && one(m[7]) && one(m[13]);
+    for (int i = 0; i < 16; ++i) {
+      if (i != 0 && i != 5 && i != 10 && i != 15 && !zero(m[i])) diag = false;
+      if (i != 0 && i != 10 && i != 7 && i != 13 && !zero(m[i])) cnot = false;
+    }
+    if (diag && finite(div(C{1, 0}, m[15]))) {
+      b.kind = BlkGate::CPHASE;
+      b.ph = m[15];
+      rw.flush(b.q[0], false);
+      rw.flush(b.q[1], false);
+    } else if (cnot) {
+      b.kind = BlkGate::CNOT;
+      rw.flush(b.q[0], false);
+      rw.flush(b.q[1], true);
+    } else {
+      return false;
+    }
+    out->push_back(b);
+  }
+  for (int q = 0; q < n; ++q) rw.flush(q, true);
+  return true;
+}
+
+namespace {
+
+// A gate of one pass on tile-local bits (q < 64) or, for controls and
+// controlled phases, bits of the tile number (q - 64).
+struct Local {
+  const BlkGate* g;
+  int q[2];
+};
+
+bool outside(int q) { return q >= 64; }
+uint32_t bit(int q) { return outside(q) ? 0u : 1u << q; }
+
+// Gates (in order) that a stage with register bits P can apply: every target
+// a register bit, at least one bit of a controlled phase, and no earlier
+// gate left behind that does not commute.  Diagonal gates and controls
+// commute with each other.
+struct Absorber {
+  uint32_t blk_n = 0, blk_d = 0;  // bits with a gate left behind: any, diagonal on this bit
+  uint32_t P;
+  explicit Absorber(uint32_t p) : P(p) {}
+  bool done() const { return !(P & ~blk_n); }
+  bool take(const Local& l) {
+    const uint32_t a = bit(l.q[0]);
+    switch (l.g->kind) {
+      case BlkGate::ROT:
+      case BlkGate::DENSE:
+        if ((a & P) && !(a & (blk_n | blk_d))) return true;
+        blk_n |= a;
+        return false;
+      case BlkGate::PHASE1:
+        if ((a & P) && !(a & blk_n)) return true;
+        blk_d |= a;
+        return false;
+      case BlkGate::CPHASE: {
+        const uint32_t m = a | bit(l.q[1]);
+        if ((m & P) && !(m & blk_n)) return true;
+        blk_d |= m;
+        return false;
+      }
+      default: {  // CNOT
+        const uint32_t t = bit(l.q[1]);
+        if ((t & P) && !(t & (blk_n | blk_d)) && !(a & blk_n)) return true;
+        blk_n |= t;
+        blk_d |= a;
+        return false;
+      }
+    }
+  }
+};
+
+bool nondiag(const Local& l) { return l.g->kind != BlkGate::PHASE1 && l.g->kind != BlkGate::CPHASE; }
+
+// Controlled phases with one register bit that no later gate of the stage
+// takes over are left for a stage where one does, if there is one: there
+// they cost a sign per thread, here a sweep over half of the registers.
+void leave_for_later(const std::vector<Local>& gs, uint32_t P, std::vector<int>* take, std::vector<int>* keep) {
+  uint32_t later = 0;  // bits with a non-diagonal gate in a later stage
+  for (int i : *keep)
+    if (nondiag(gs[i])) later |= bit(gs[i].q[gs[i].g->kind == BlkGate::CNOT ? 1 : 0]);
+  uint32_t now = 0;    // register bits with a rotation further on in this stage
+  std::vector<int> stay, left;
+  for (size_t k = take->size(); k-- > 0;) {
+    const Local& l = gs[(*take)[k]];
+    const uint32_t t = nondiag(l) ? bit(l.q[l.g->kind == BlkGate::CNOT ? 1 : 0]) : 0u;
+    now |= t;
+    const uint32_t m = bit(l.q[0]) | bit(l.q[1] < 0 ? 64 : l.q[1]);
+    const bool single = l.g->kind == BlkGate::CPHASE && (m & P & ((m & P) - 1)) == 0;
+    (single && !(m & now) && (m & later) ? left : stay).push_back((*take)[k]);
+  }
+  if (stay.empty()) return;
+  take->assign(stay.rbegin(), stay.rend());
+  keep->insert(keep->end(), left.begin(), left.end());
+  std::sort(keep->begin(), keep->end());
+}
+
+int weight(const Local& l) {
+  return l.g->kind == BlkGate::PHASE1 || l.g->kind == BlkGate::CPHASE ? 1 : 4;
+}
+
+int score(const std::vector<Local>& gs, const std::vector<int>& rem, uint32_t P) {
+  Absorber ab(P);
+  int s = 0;
+  for (int i : rem) {
+    if (ab.take(gs[i])) s += weight(gs[i]);
+    else if (ab.done()) break;
+  }
+  return s;
+}
+
+// Register bits for the next stage: greedily the bit that lets the most
+// through, among the bits of allowed (at least K of them).
+uint32_t pick_regs(const std::vector<Local>& gs, const std::vector<int>& rem, int tb, int K,
+                   uint32_t allowed, int* got) {
+  uint32_t P = 0;
+  int best_all = 0;
+  for (int k = 0; k < K; ++k) {
+    int best = -1, bs = -1;
+    for (int b = 0; b < tb; ++b) {
+      if (!((allowed >> b) & 1) || ((P >> b) & 1)) continue;
+      const int s = score(gs, rem, P | (1u << b));
+      if (s > bs) {
+        bs = s;
+        best = b;
+      }
+    }
+    P |= 1u << best;
+    best_all = bs;
+  }
+  *got = best_all;
+  return P;
+}
+
+enum EKind { E_ROT, E_DENSE, E_SWAP, E_PHASE, E_PAIR, E_NEG, E_SIGNS };
+
+struct EOp {  // an op of a stage before it is put into layers
+  EKind kind = E_ROT;
+  int J = 0;            // ROT, DENSE, SWAP, NEG: register bit
+  uint32_t cm = 0;      // SWAP, PHASE, PAIR, SIGNS: register bits
+  uint32_t tmask = 0;   // tile-local bits (thread bits of the stage)
+  uint64_t gmask = 0;
+  C ph{1, 0};
+  double t = 0.0;
+  C m[4];
+  C lam{1, 0};
+  struct Col {          // phase where an outer bit is set
+    C ph;
+    int q;
+  };
+  std::vector<Col> col;
+  bool plain() const { return !tmask && !gmask && col.empty(); }
+};
+
+struct StagePlan {
+  uint32_t regs = 0;
+  C scal{1, 0};  // scalar factors of the stage's gates that no op carries
+  std::vector<EOp> ops;
+  int reg[8], thr[kBlkThrBits];
+};
+
+// What a pass carries from stage to stage per tile bit: whether the bit is
+// stored complemented, and a phase of its (stored) set half still to apply.
+struct Frame {
+  uint32_t flip = 0;
+  C pend[32];
+  Frame() {
+    for (C& z : pend) z = C{1, 0};
+  }
+  bool flipped(int q) const { return !outside(q) && ((flip >> q) & 1); }
+};
+
+// Emits the ops of a stage for its gates in order.
+struct Emitter {
+  const std::vector<Local>& gs;
+  Frame& fr;
+  StagePlan& st;
+  int K;
+  int jof_[64];
+  // what waits for each register bit's next op, on the stored set half: a
+  // phase, sign masks, and phases that depend on an outer bit
+  struct Wait {
+    C ph{1, 0};
+    uint32_t tmask = 0;
+    uint64_t gmask = 0;
+    std::vector<EOp::Col> col;
+    bool outer() const { return tmask || gmask || !col.empty(); }
+  };
+  std::vector<Wait> wait;
+
+  Emitter(const std::vector<Local>& g, Frame& f, StagePlan& s, int k) : gs(g), fr(f), st(s), K(k), wait(k) {
+    for (int& j : jof_) j = -1;
+    for (int j = 0; j < K; ++j) {
+      jof_[s.reg[j]] = j;
+      wait[j].ph = f.pend[s.reg[j]];
+      f.pend[s.reg[j]] = C{1, 0};
+    }
+  }
+  int jof(int q) const { return outside(q) ? -1 : jof_[q]; }
+
+  void take_wait(EOp& e, int j) {
+    Wait& w = wait[j];
+    e.ph = mul(e.ph, w.ph);
+    e.tmask = w.tmask;
+    e.gmask = w.gmask;
+    e.col = std::move(w.col);
+    w = Wait();
+  }
+  void settle(int j) {  // applies what waits for j now
+    Wait& w = wait[j];
+    if (!w.outer() && one(w.ph)) return;
+    EOp e;
+    e.J = j;
+    e.kind = w.col.empty() && one(w.ph) ? E_NEG : E_ROT;  // a phase alone: t = 0
+    take_wait(e, j);
+    st.ops.push_back(std::move(e));
+  }
+  // phase of the set half of bit q (as stored)
+  void phase_on(int q, C p) {
+    const int j = jof(q);
+    if (j >= 0) wait[j].ph = mul(wait[j].ph, p);
+    else fr.pend[q] = mul(fr.pend[q], p);
+  }
+
+  void gate(const Local& l) {
+    const BlkGate& g = *l.g;
+    const int q0 = l.q[0], q1 = l.q[1], j = jof(q0);
+    const bool f0 = fr.flipped(q0);
+    const auto inv = [](C p) { return div(C{1, 0}, p); };
+    EOp e;
+    e.J = j;
+    switch (g.kind) {
+      case BlkGate::ROT:
+        // on a flipped bit diag(1, p) is p diag(1, 1 / p) and t changes sign;
+        // the second form is [[1, t], [-t, 1]] after a flip
+        e.kind = E_ROT;
+        e.lam = g.lam;
+        e.ph = f0 ? inv(g.ph) : g.ph;
+        e.t = f0 ? -g.t : g.t;
+        if (f0) e.lam = mul(e.lam, g.ph);
+        if (g.formb) {
+          e.ph = C{-e.ph.re, -e.ph.im};
+          if (f0) e.lam = C{-e.lam.re, -e.lam.im};
+          fr.flip ^= 1u << q0;
+        }
+        take_wait(e, j);
+        st.ops.push_back(std::move(e));
+        break;
+      case BlkGate::DENSE: {
+        if (wait[j].outer()) settle(j);
+        const C p = wait[j].ph;  // a plain phase joins the matrix's second column
+        wait[j] = Wait();
+        e.kind = E_DENSE;
+        e.m[0] = f0 ? g.m[3] : g.m[0];
+        e.m[1] = mul(f0 ? g.m[2] : g.m[1], p);
+        e.m[2] = f0 ? g.m[1] : g.m[2];
+        e.m[3] = mul(f0 ? g.m[0] : g.m[3], p);
+        st.ops.push_back(std::move(e));
+        break;
+      }
+      case BlkGate::PHASE1:
+        st.scal = mul(st.scal, g.lam);
+        if (f0) st.scal = mul(st.scal, g.ph);
+        phase_on(q0, f0 ? inv(g.ph) : g.ph);
+        break;
+      case BlkGate::CPHASE: {
+        // phi (f0 + s0 b0) (f1 + s1 b1) with f = 1, s = -1 on a flipped bit
+        const bool f1 = fr.flipped(q1);
+        const C p = g.ph, ip = f0 || f1 ? inv(p) : p;
+        if (f0 && f1) st.scal = mul(st.scal, p);
+        if (f0) phase_on(q1, f1 ? ip : p);
+        if (f1) phase_on(q0, f0 ? ip : p);
+        const C pp = f0 != f1 ? ip : p;
+        const bool neg = pp.re == -1.0 && pp.im == 0.0;
+        const int j1 = jof(q1);
+        if (j >= 0 && j1 >= 0) {
+          e.kind = neg ? E_PAIR : E_PHASE;
+          e.cm = (1u << j) | (1u << j1);
+          if (!neg) e.ph = pp;
+          st.ops.push_back(std::move(e));
+          break;
+        }
+        const int other = j >= 0 ? q1 : q0;
+        Wait& w = wait[j >= 0 ? j : j1];
+        if (!neg) w.col.push_back({pp, other});
+        else if (outside(other)) w.gmask ^= uint64_t(1) << (other - 64);
+        else w.tmask ^= 1u << other;
+        break;
+      }
+      default: {  // CNOT; a flipped control also flips the target
+        const int jt = jof(q1);
+        settle(jt);
+        e.kind = E_SWAP;
+        e.J = jt;
+        if (j >= 0) e.cm = 1u << j;
+        else if (outside(q0)) e.gmask = uint64_t(1) << (q0 - 64);
+        else e.tmask = 1u << q0;
+        st.ops.push_back(std::move(e));
+        if (f0) fr.flip ^= 1u << q1;
+        break;
+      }
+    }
+  }
+
+  void finish() {
+    for (int j = 0; j < K; ++j) {
+      if (!wait[j].outer()) {  // a plain phase can wait for a later stage
+        fr.pend[st.reg[j]] = wait[j].ph;
+        wait[j].ph = C{1, 0};
+      }
+      settle(j);
+    }
+  }
+};
+
+// Applies the phases that a pass's stages left pending, at its end.
+void settle_frame(Frame& fr, StagePlan& st, int tb, int K) {
+  EOp s;
+  s.kind = E_SIGNS;
+  std::vector<EOp> rest;
+  for (int b = 0; b < tb; ++b) {
+    const C p = fr.pend[b];
+    if (one(p)) continue;
+    int j = -1;
+    for (int i = 0; i < K; ++i)
+      if (st.reg[i] == b) j = i;
+    if (p.re == -1.0 && p.im == 0.0) {
+      if (j >= 0) s.cm |= 1u << j;
+      else s.tmask |= 1u << b;
+    } else {
+      EOp e;
+      e.kind = j >= 0 ? E_ROT : E_PHASE;
+      if (j >= 0) {
+        e.J = j;
+        e.ph = p;
+      } else {
+        e.col.push_back({p, b});
+      }
+      // phases of thread bits share one op
+      if (j < 0 && !rest.empty() && rest.back().kind == E_PHASE) rest.back().col.push_back({p, b});
+      else rest.push_back(std::move(e));
+    }
+  }
+  if (s.cm || s.tmask) st.ops.push_back(std::move(s));
+  for (EOp& e : rest) st.ops.push_back(std::move(e));
+}
+
+// Scalar parts of the pass's gates: their product goes into the matrix of a
+// rotation without outer signs or phases (any op can carry a scalar), as a
+// dense 2x2; on the way it is kept within 2^+-20 of what the registers hold.
+void place_scalars(std::vector<StagePlan>& st) {
+  C run{1, 0};
+  EOp* last = nullptr;
+  auto carry = [](EOp* e, C s) {
+    if (e->kind == E_ROT) {
+      e->kind = E_DENSE;
+      e->m[0] = s;
+      e->m[1] = mul(s, C{-e->t * e->ph.re, -e->t * e->ph.im});
+      e->m[2] = C{s.re * e->t, s.im * e->t};
+      e->m[3] = mul(s, e->ph);
+    } else {
+      for (C& z : e->m) z = mul(s, z);
+    }
+  };
+  for (StagePlan& s : st) {
+    run = mul(run, s.scal);
+    for (EOp& e : s.ops) {
+      run = mul(run, e.lam);
+      if ((e.kind == E_ROT && e.plain()) || e.kind == E_DENSE) {
+        last = &e;
+        const double a = absv(run);
+        if (a > 0x1p20 || a < 0x1p-20) {
+          carry(last, run);
+          run = C{1, 0};
+        }
+      }
+    }
+  }
+  if (one(run)) return;
+  if (!last) {
+    EOp e;
+    e.kind = E_DENSE;
+    e.m[0] = e.m[3] = C{1, 0};
+    e.m[1] = e.m[2] = C{0, 0};
+    st.back().ops.push_back(std::move(e));
+    last = &st.back().ops.back();
+  }
+  carry(last, run);
+}
+
+// Puts a stage's ops into layers and appends them to the plan as device
+// stages: misc ops, then an even number of layers (sign changes, then one
+// rotation per register bit at most); misc ops in between start another
+// device stage of the same layout.
+void emit_layers(const StagePlan& p, int nthr, BlkStage base, BlkPlan* plan) {
+  const auto tmask_of = [&](uint32_t m) {
+    uint32_t t = 0;
+    for (int i = 0; i < nthr; ++i)
+      if ((m >> p.thr[i]) & 1) t |= 1u << i;
+    return t;
+  };
+  struct Layer {
+    BlkLayer<double> y{};
+    BlkMore more{};
+    std::vector<const EOp*> misc;
+    std::vector<EOp::Col> col[kBlkRegs];
+    uint32_t sgn = 0;  // register bits in a sign change
+  };
+  const auto push_op = [&](int kind, uint32_t tm, uint64_t gm, const double* c, int n) {
+    BlkOp o{};
+    o.kind = kind;
+    o.tmask = tm;
+    o.gmask = gm;
+    plan->ops.push_back(o);
+    for (int i = 0; i < 8; ++i) plan->ocoef.push_back(i < n ? c[i] : 0.0);
+    return (int)plan->ops.size() - 1;
+  };
+  const auto push_cols = [&](const std::vector<EOp::Col>& col, int32_t* c0, int32_t* c1) {
+    *c0 = (int32_t)plan->ops.size();
+    for (const EOp::Col& c : col) {
+      const double v[2] = {c.ph.re, c.ph.im};
+      push_op(BLK_COLLECT, outside(c.q) ? 0u : tmask_of(1u << c.q), outside(c.q) ? uint64_t(1) << (c.q - 64) : 0, v, 2);
+    }
+    *c1 = (int32_t)plan->ops.size();
+  };
+  const auto start = [&](Layer& cur) {  // misc ops of a device stage
+    std::vector<std::pair<int32_t, int32_t>> cols;
+    for (const EOp* e : cur.misc) {
+      std::pair<int32_t, int32_t> c{0, 0};
+      if (!e->col.empty()) push_cols(e->col, &c.first, &c.second);
+      cols.push_back(c);
+    }
+    base.misc_begin = (int32_t)plan->ops.size();
+    for (size_t i = 0; i < cur.misc.size(); ++i) {
+      const EOp& e = *cur.misc[i];
+      double c[8] = {e.ph.re, e.ph.im, 0, 0, 0, 0, 0, 0};
+      int kind = 0;
+      if (e.kind == E_DENSE) {
+        kind = BLK_DENSE + e.J;
+        for (int k = 0; k < 4; ++k) c[2 * k] = e.m[k].re, c[2 * k + 1] = e.m[k].im;
+      } else if (e.kind == E_SWAP) {
+        kind = BLK_SWAP + e.J;
+      } else {
+        kind = e.kind == E_SIGNS ? BLK_SIGNS : BLK_PHASE;
+      }
+      const int o = push_op(kind | (int)(e.cm << 8), tmask_of(e.tmask), e.gmask, c, 8);
+      plan->ops[o].col_begin = cols[i].first;
+      plan->ops[o].col_end = cols[i].second;
+    }
+    base.misc_end = (int32_t)plan->ops.size();
+    base.layer_begin = (int32_t)plan->layers.size();
+  };
+  const auto push_layer = [&](Layer& cur) {
+    for (int j = 0; j < kBlkRegs; ++j)
+      if (!cur.col[j].empty()) push_cols(cur.col[j], &cur.more.col_begin[j], &cur.more.col_end[j]);
+    plan->layers.push_back(cur.y);
+    plan->more.push_back(cur.more);
+  };
+  const auto finish = [&]() {
+    if ((plan->layers.size() - base.layer_begin) % 2) {
+      plan->layers.push_back(BlkLayer<double>{});
+      plan->more.push_back(BlkMore{});
+    }
+    base.layer_end = (int32_t)plan->layers.size();
+    plan->stages.push_back(base);
+    base.exchange = BLK_STAY;
+  };
+  // every op goes to the first layer that it may: level[j] is the first one
+  // whose rotation of bit j comes after everything placed on j so far
+  std::vector<Layer> ly;
+  int level[kBlkRegs] = {};
+  const auto at = [&](int l) -> Layer& {
+    if ((int)ly.size() <= l) ly.resize(l + 1);
+    return ly[l];
+  };
+  const auto masks = [&](Layer& y, const EOp& e) {
+    y.y.tmask[e.J] = tmask_of(e.tmask);
+    y.more.gmask[e.J] = e.gmask;
+    if (e.gmask) y.y.flags |= BLK_GMASK << e.J;
+  };
+  for (const EOp& e : p.ops) {
+    const uint32_t jb = 1u << e.J;
+    const uint32_t u = e.kind == E_ROT || e.kind == E_NEG || e.kind == E_DENSE ? jb
+                       : e.kind == E_SWAP ? jb | e.cm : e.cm;
+    int l = 0;
+    for (int j = 0; j < kBlkRegs; ++j)
+      if ((u >> j) & 1) l = std::max(l, level[j]);
+    // misc ops run first in their layer: not after a sign change on their bits
+    const bool moves = e.kind == E_DENSE || e.kind == E_SWAP;
+    if (moves && (int)ly.size() > l && (ly[l].sgn & u)) ++l;
+    if (e.kind == E_NEG && (int)ly.size() > l && (ly[l].y.flags & (BLK_NEG << e.J))) ++l;
+    if (e.kind == E_ROT && (int)ly.size() > l && (ly[l].y.flags & (BLK_NEG << e.J))) ++l;
+    Layer& y = at(l);
+    switch (e.kind) {
+      case E_ROT:
+        y.y.flags |= BLK_ROT << e.J;
+        if (e.tmask || e.gmask) {
+          y.y.flags |= BLK_OUTER << e.J;
+          masks(y, e);
+        }
+        if (!e.col.empty()) {
+          y.y.flags |= (BLK_OUTER | BLK_COL) << e.J;
+          y.col[e.J] = e.col;
+        }
+        y.y.c[3 * e.J] = e.ph.re;
+        y.y.c[3 * e.J + 1] = e.ph.im;
+        y.y.c[3 * e.J + 2] = e.t;
+        break;
+      case E_PAIR:
+        {
+          int i = 0;
+          while (!((e.cm >> i) & 1)) ++i;
+          int j = i + 1;
+          while (!((e.cm >> j) & 1)) ++j;
+          y.y.pairs ^= 1 << pair_bit(i, j);
+        }
+        y.sgn |= e.cm;
+        break;
+      case E_NEG:
+        y.y.flags |= BLK_NEG << e.J;
+        masks(y, e);
+        y.sgn |= jb;
+        break;
+      default: y.misc.push_back(&e); break;
+    }
+    for (int j = 0; j < kBlkRegs; ++j)
+      if ((u >> j) & 1) level[j] = std::max(level[j], e.kind == E_ROT ? l + 1 : l);
+  }
+  if (ly.empty()) ly.resize(1);
+  for (size_t l = 0; l < ly.size(); ++l) {
+    if (l > 0 && !ly[l].misc.empty()) finish();
+    if (l == 0 || !ly[l].misc.empty()) start(ly[l]);
+    if (ly[l].y.flags || ly[l].y.pairs) push_layer(ly[l]);
+  }
+  finish();
+}
+
+// LDS slot (8 bytes) of tile element e: the higher bits folded onto the five
+// that pick the bank, so that lanes that step by large powers of two spread
+// over the banks.  Linear over XOR.
+int slot(int e) { return e ^ (((e >> 5) ^ (e >> 10)) & 31); }
+constexpr int kSlotBytes = 8;
+
+}  // namespace
+
+void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, const std::vector<int>& taken,
+                     const std::vector<Gate>& where, bool fp64, int low, BlkPlan* plan) {
+  const int tb = tg.b, K = kBlkRegs, nthr = tb - K, lanes = std::min(6, nthr), waves = nthr - lanes;
+  // tile-local bit of a physical bit, or 64 + its bit in the tile number
+  int local_of[64];
+  int tau = 0;
+  for (int p = 0; p < tg.n; ++p) {
+    local_of[p] = -1;
+    if (p < tg.L) local_of[p] = p;
+    for (int j = 0; j < tg.H; ++j)
+      if (tg.hbits[j] == p) local_of[p] = tg.L + j;
+    if (local_of[p] < 0) local_of[p] = 64 + tau++;
+  }
+  std::vector<Local> gs;
+  std::vector<int> rem;
+  for (size_t i = 0; i < taken.size(); ++i) {
+    Local l;
+    l.g = &gates[i];
+    for (int j = 0; j < 2; ++j) l.q[j] = j < where[taken[i]].nq ? local_of[where[taken[i]].q[j]] : -1;
+    gs.push_back(l);
+    rem.push_back((int)i);
+  }
+  // destination bit of each local bit (relabel swaps); the low bits of the
+  // source order must be lane bits as the tile is read, those of the
+  // destination order as it is written
+  int dest[64];
+  for (int b = 0; b < tb; ++b) dest[b] = b;
+  for (int i = 0; i < tg.nswap; ++i) std::swap(dest[tg.swap_a[i]], dest[tg.swap_b[i]]);
+  low = std::min(low, lanes);
+  const uint32_t all = (1u << tb) - 1, low_src = (1u << low) - 1;
+  uint32_t low_dst = 0;
+  for (int b = 0; b < tb; ++b)
+    if (dest[b] < low) low_dst |= 1u << b;
+  std::vector<StagePlan> st;
+  Frame fr;
+  do {
+    int got = 0;
+    const uint32_t first = st.empty() ? low_src : 0u;
+    uint32_t P = pick_regs(gs, rem, tb, K, all & ~first, &got);
+    if ((P & low_dst) && !st.empty()) {  // a last stage that needs no further exchange, if one finishes the pass
+      int g2 = 0, sum = 0;
+      const uint32_t P2 = pick_regs(gs, rem, tb, K, all & ~low_dst, &g2);
+      for (int i : rem) sum += weight(gs[i]);
+      if (g2 == sum) P = P2;
+    }
+    StagePlan s;
+    s.regs = P;
+    std::vector<int> take, keep;
+    Absorber ab(P);
+    for (int i : rem) (ab.take(gs[i]) ? take : keep).push_back(i);
+    leave_for_later(gs, P, &take, &keep);
+    int k = 0;
+    for (int b = 0; b < tb; ++b)
+      if ((P >> b) & 1) s.reg[k++] = b;
+    Emitter em(gs, fr, s, K);
+    for (int i : take) em.gate(gs[i]);
+    em.finish();
+    st.push_back(std::move(s));
+    rem.swap(keep);
+  } while (!rem.empty());
+  // stage at which a bit is next a register bit (or must be a lane)
+  auto next_use = [&](int b, size_t from) {
+    for (size_t s = from; s < st.size(); ++s)
+      if (((st[s].regs >> b) & 1) || (s + 1 == st.size() && ((low_dst >> b) & 1))) return (int)s;
+    return (int)st.size() + 1;
+  };
+  // the tile is written from lanes that hold the destination's low bits
+  if ((st.back().regs & low_dst) || (st.size() == 1 && low_src != low_dst)) {
+    StagePlan s;
+    // bits that stay where they are first, then the highest
+    int k = 0;
+    for (int pass = 0; pass < 2; ++pass)
+      for (int b = tb - 1; b >= 0 && k < K; --b) {
+        if (((low_dst | s.regs) >> b) & 1) continue;
+        if (pass == 0 && !((st.back().regs >> b) & 1)) continue;
+        s.regs |= 1u << b;
+        s.reg[k++] = b;
+      }
+    st.push_back(std::move(s));
+  }
+  settle_frame(fr, st.back(), tb, K);
+  place_scalars(st);
+  // thread bits: wave bits kept from stage to stage while they can be, else
+  // those that are needed again last; lane bits in an order whose LDS access
+  // phases (8 lanes of 16 bytes, 16 of 8) reach distinct bank slots
+  std::vector<int> wv;
+  constexpr int phase = 4;
+  for (size_t s = 0; s < st.size(); ++s) {
+    StagePlan& p = st[s];
+    const bool f = s == 0, l = s + 1 == st.size();
+    const uint32_t no = p.regs | (f ? low_src : 0u) | (l ? low_dst : 0u);
+    bool keep = !f;
+    for (int b : wv) keep = keep && !((no >> b) & 1);
+    if (!keep) {
+      std::vector<int> cand;
+      for (int b = 0; b < tb; ++b)
+        if (!((no >> b) & 1)) cand.push_back(b);
+      std::stable_sort(cand.begin(), cand.end(), [&](int x, int y) { return next_use(x, s + 1) > next_use(y, s + 1); });
+      wv.assign(cand.begin(), cand.begin() + waves);
+      std::sort(wv.begin(), wv.end());
+    }
+    std::vector<int> ln;
+    uint32_t used = p.regs;
+    for (int b : wv) used |= 1u << b;
+    if (f || l) {
+      for (int d = 0; d < low; ++d)
+        for (int b = 0; b < tb; ++b)
+          if ((f ? b : dest[b]) == d && !((used >> b) & 1)) {
+            ln.push_back(b);
+            used |= 1u << b;
+          }
+    }
+    int span = 1;
+    auto dir = [&](int b) { return slot(1 << b) & ((1 << phase) - 1); };
+    auto grow = [&](int b) {
+      int g = span;
+      for (int u = 0; u < (1 << phase); ++u)
+        if ((span >> u) & 1) g |= 1 << (u ^ dir(b));
+      span = g;
+    };
+    for (int b : ln) grow(b);
+    for (int pass = 0; pass < 2; ++pass)
+      for (int b = 0; b < tb; ++b) {
+        if ((used >> b) & 1 || (int)ln.size() >= lanes) continue;
+        if (pass == 0 && ((span >> dir(b)) & 1)) continue;
+        grow(b);
+        ln.push_back(b);
+        used |= 1u << b;
+      }
+    for (int i = 0; i < lanes; ++i) p.thr[i] = ln[i];
+    for (int i = 0; i < waves; ++i) p.thr[lanes + i] = wv[i];
+  }
+  // serialise
+  BlkPass out{};
+  BlkGeom& g = out.g;
+  g.n = tg.n;
+  g.b = tb;
+  g.L = tg.L;
+  g.H = tg.H;
+  g.block_bits = tg.block_bits;
+  for (int j = 0; j < tg.H; ++j) g.hbits[j] = tg.hbits[j];
+  auto phys = [&](int b) { return (int32_t)(b < tg.L ? b : tg.hbits[b - tg.L]); };
+  for (int i = 0; i < nthr; ++i) {
+    g.ld_thr[i] = phys(st.front().thr[i]);
+    g.st_thr[i] = phys(dest[st.back().thr[i]]);
+  }
+  for (int j = 0; j < K; ++j) {
+    g.ld_reg[j] = phys(st.front().reg[j]);
+    g.st_reg[j] = phys(dest[st.back().reg[j]]);
+  }
+  auto same_waves = [&](const StagePlan& a, const StagePlan& b) {
+    return std::equal(a.thr + lanes, a.thr + nthr, b.thr + lanes);
+  };
+  g.tile_sync = st.size() > 1 && !same_waves(st.front(), st.back());
+  for (int b = 0; b < tb; ++b)
+    if ((fr.flip >> b) & 1) g.st_flip |= uint64_t(1) << phys(dest[b]);
+  out.stage_begin = (int32_t)plan->stages.size();
+  for (size_t s = 0; s < st.size(); ++s) {
+    const StagePlan& p = st[s];
+    BlkStage x{};
+    x.exchange = s > 0 && !same_waves(st[s - 1], p) ? BLK_CROSS : BLK_WAVE;
+    for (int j = 0; j < K; ++j) x.row[j] = slot(1 << p.reg[j]) * kSlotBytes;
+    for (int i = 0; i < nthr; ++i) x.thr[i] = slot(1 << p.thr[i]) * kSlotBytes;
+    emit_layers(p, nthr, x, plan);
+  }
+  plan->passes.push_back(out);
+  plan->passes.back().g.nst = (int32_t)plan->stages.size() - out.stage_begin;
+}
+
+namespace {
+
+template <typename T>
+void put_reals(const BlkPlan& plan, const BlkLayout& l, char* h) {
+  auto* y = (BlkLayer<T>*)(h + l.o_layers);
+  for (size_t i = 0; i < plan.layers.size(); ++i) {
+    const BlkLayer<double>& x = plan.layers[i];
+    y[i].flags = x.flags;
+    y[i].pairs = x.pairs;
+    for (int j = 0; j < kBlkRegs; ++j) y[i].tmask[j] = x.tmask[j];
+    for (int j = 0; j < 3 * kBlkRegs; ++j) y[i].c[j] = (T)x.c[j];
+  }
+  T* c = (T*)(h + l.o_ocoef);
+  for (size_t i = 0; i < plan.ocoef.size(); ++i) c[i] = (T)plan.ocoef[i];
+}
+
+}  // namespace
+
+BlkLayout block_image(const BlkPlan& plan, bool fp64, std::vector<char>* buf) {
+  const auto up = [](size_t x) { return (x + 255) & ~size_t(255); };
+  BlkLayout l;
+  l.o_geoms = up(plan.stages.size() * sizeof(BlkStage));
+  l.o_layers = up(l.o_geoms + plan.passes.size() * sizeof(BlkGeom));
+  // two more layers: the kernels read up to two records ahead
+  l.o_more = up(l.o_layers + (plan.layers.size() + 2) * (fp64 ? sizeof(BlkLayer<double>) : sizeof(BlkLayer<float>)));
+  l.o_ops = up(l.o_more + plan.more.size() * sizeof(BlkMore));
+  l.o_ocoef = up(l.o_ops + plan.ops.size() * sizeof(BlkOp));
+  l.total = up(l.o_ocoef + plan.ocoef.size() * (fp64 ? sizeof(double) : sizeof(float)));
+  buf->assign(l.total, 0);
+  char* h = buf->data();
+  const auto put = [&](size_t o, const void* p, size_t n) {
+    if (n) std::memcpy(h + o, p, n);
+  };
+  put(0, plan.stages.data(), plan.stages.size() * sizeof(BlkStage));
+  for (size_t i = 0; i < plan.passes.size(); ++i) put(l.o_geoms + i * sizeof(BlkGeom), &plan.passes[i].g, sizeof(BlkGeom));
+  put(l.o_more, plan.more.data(), plan.more.size() * sizeof(BlkMore));
+  put(l.o_ops, plan.ops.data(), plan.ops.size() * sizeof(BlkOp));
+  if (fp64) put_reals<double>(plan, l, h);
+  else put_reals<float>(plan, l, h);
+  return l;
+}
+
+bool plan_block(int n, int L, int b, const std::vector<Gate>& gates, bool fp64, int max_take, bool relabel,
+                BlkPlan* plan, std::vector<int>* final_pos) {
+  *plan = BlkPlan();
+  // a matrix whose rotation form misses an entry by more than this (relative)
+  // stays a dense 2x2: a few FP64 roundings, or far below an FP32 rounding
+  const double tol = fp64 ? 2e-15 : 1e-9;
+  std::vector<BlkGate> bg;
+  if (!block_gates(n, gates, tol, &bg)) return false;
+  std::vector<Gate> shape(bg.size());  // the qubits alone, for the tile selection
+  for (size_t i = 0; i < bg.size(); ++i) {
+    shape[i].nq = bg[i].kind == BlkGate::CPHASE || bg[i].kind == BlkGate::CNOT ? 2 : 1;
+    shape[i].q[0] = bg[i].q[0];
+    shape[i].q[1] = bg[i].q[1];
+  }
+  TileSchedule sched;
+  if (relabel) {
+    select_tiles_relabel(n, L, b, 0, shape, &sched, max_take);
+  } else {
+    select_tiles(n, L, b, 0, shape, &sched, max_take);
+    sched.final_pos.resize(n);
+    for (int q = 0; q < n; ++q) sched.final_pos[q] = q;
+  }
+  if (sched.gates != (int64_t)shape.size()) return false;
+  const std::vector<Gate>& src = sched.tgates.empty() ? shape : sched.tgates;
+  for (size_t i = 0; i < sched.passes.size(); ++i) {
+    std::vector<BlkGate> mine;
+    for (int t : sched.taken[i]) mine.push_back(bg[sched.tsrc.empty() ? t : sched.tsrc[t]]);
+    plan_block_pass(sched.passes[i].g, mine, sched.taken[i], src, fp64, std::min(L, fp64 ? 5 : 6), plan);
+  }
+  *final_pos = sched.final_pos;
+  return true;
+}
+
+}  // namespace juqcs

@@ -144,6 +144,76 @@ struct TilePass {
 };
 
 // ---------------------------------------------------------------------------
+// Register-resident tile programs (block_ops.hpp, block.cpp)
+// ---------------------------------------------------------------------------
+constexpr int kBlkRegs = 4;      // register bits: 2^4 amplitudes per thread
+constexpr int kBlkThrBits = 9;   // most thread bits of a tile (2^13 amplitudes)
+// A layer: sign changes of register-bit pairs and bits, then at most one
+// rotation per register bit.
+template <typename T>
+struct alignas(16) BlkLayer {
+  int32_t flags;
+  int32_t pairs;                // pair_bit of every pair that changes sign where both are set
+  int32_t pad[2];
+  uint32_t tmask[kBlkRegs];     // thread bits whose parity signs C + i S of register bit j
+  T c[3 * kBlkRegs];            // C, S, t at 3 j
+};
+struct BlkMore {  // what few layers need
+  uint64_t gmask[kBlkRegs];     // bits of the tile number that join tmask's
+  int32_t col_begin[kBlkRegs], col_end[kBlkRegs];  // phases that join C + i S per thread
+};
+enum BlkFlags : int32_t {  // J: register bit
+  BLK_ROT = 1 << 0,      // << J: phase C + i S on the set half, then [[1, -t], [t, 1]]
+  BLK_OUTER = 1 << 4,    // << J: C, S take signs or phases of outer bits
+  BLK_NEG = 1 << 8,      // << J: no rotation, the set half changes sign by the masks
+  BLK_COL = 1 << 12,     // << J: C + i S takes the collected phases
+  BLK_GMASK = 1 << 16,   // << J: gmask counts
+  BLK_NEGS = 15 << 8,
+};
+// Bit of a pair of register bits: neighbours first (0-2), then the others.
+constexpr int pair_bit(int i, int j) { return j == i + 1 ? i : j == i + 2 ? 3 + i : 5; }
+enum BlkKind : int32_t {  // misc ops
+  BLK_DENSE = 0,    // + J: dense 2x2, 8 reals
+  BLK_SWAP = 8,     // + J: the halves trade places where all control bits are set
+  BLK_PHASE = 16,   // C + i S where all register control bits (none or two) are set
+  BLK_COLLECT = 17, // entry of a col list: C + i S where all mask bits are set
+  BLK_SIGNS = 18,   // sign by the parity of the masked thread bits and of the register control bits
+  // bits 8..15: register control bits (BLK_SWAP, BLK_PHASE, BLK_SIGNS)
+};
+struct BlkOp {     // coefficients: 8 reals per op
+  int32_t kind;
+  uint32_t tmask;  // thread bits (of the thread index)
+  uint64_t gmask;  // bits of the tile number
+  int32_t col_begin, col_end;  // BLK_PHASE: phases that join per thread
+};
+enum BlkExchange : int32_t { BLK_STAY, BLK_WAVE, BLK_CROSS };  // nothing, within waves, across waves
+struct BlkStage {
+  int32_t misc_begin, misc_end;
+  int32_t layer_begin, layer_end;  // an even number
+  int32_t exchange;           // what comes before this stage
+  int32_t row[kBlkRegs];      // LDS byte offset of each register bit
+  int32_t thr[kBlkThrBits];   // of each thread bit
+};
+struct BlkGeom {
+  int32_t n, b, L, H;            // as TileGeom
+  int32_t hbits[kMaxGather];
+  int32_t nst;                   // stages
+  int32_t tile_sync;             // the first and last stage have different wave bits
+  int32_t block_bits;            // ENC2 only
+  // physical bit of each thread and register bit as the tile is read and as
+  // it is written (through the pass's relabel swaps)
+  int32_t ld_thr[kBlkThrBits], ld_reg[kBlkRegs], st_thr[kBlkThrBits], st_reg[kBlkRegs];
+  uint64_t st_flip;              // physical bits that are written complemented
+};
+struct BlkDev {  // a plan in device memory
+  const BlkStage* stages;
+  const void* layers;  // BlkLayer<T>
+  const BlkMore* more; // one per layer
+  const BlkOp* ops;
+  const void* ocoef;   // 8 per op
+};
+
+// ---------------------------------------------------------------------------
 // Kernel launchers (defined in the .hip files).  All asynchronous on stream.
 // Return hipSuccess or the launch error.
 // ---------------------------------------------------------------------------
@@ -181,6 +251,14 @@ int expect_max_bits();
 size_t expect_partials_bytes();
 hipError_t launch_expect(juqcs_dtype dt, const void* amps, const void* scales, const TileGeom& g,
                          int jlo, double* partials, double* out3, hipStream_t s);
+
+// Register-resident tile passes (k_block.hip): tile sizes that have a kernel.
+bool block_sized(juqcs_dtype dt, int b);
+// g: the pass's geometry, d_geom the same in device memory.
+hipError_t launch_block(juqcs_dtype dt, void* amps, const BlkGeom& g, const BlkGeom* d_geom, const BlkDev& d,
+                        hipStream_t s);
+// Workgroups of a kernel that fit on the device at once (cached per kernel).
+uint64_t resident_blocks(const void* kern, int threads);
 
 // What a pass of 2^b-amplitude tiles may carry so that it runs on the
 // pipelined kernel: coefficients (staged in LDS by the two-byte kernels) and
@@ -337,6 +415,56 @@ void emit_schedule(const TileSchedule& sched, const std::vector<Gate>& gates, in
 void plan_tiles(int n, int L, int b, int block_bits, const std::vector<Gate>& gates,
                 TilePlan* plan, int kin = 2, int max_mats = 0, int max_take = 0,
                 int max_mma = 0, bool relabel = false, std::vector<int>* final_pos = nullptr);
+
+// A gate of a register-resident tile program (block.cpp).
+struct BlkGate {
+  enum Kind { ROT, DENSE, PHASE1, CPHASE, CNOT } kind = DENSE;
+  int q[2] = {0, -1};       // CNOT: control, target
+  bool formb = false;       // ROT: lam R diag(1, ph), R = [[1, -t], [t, 1]] or (formb) [[t, -1], [1, t]]
+                            // = [[1, t], [-t, 1]] [[0, -1], [1, 0]]
+  double t = 0.0;
+  cplx<double> ph{1, 0};    // phase of the set half (ROT, PHASE1) or quarter (CPHASE)
+  cplx<double> lam{1, 0};   // scalar factor (ROT, PHASE1)
+  cplx<double> m[4];        // DENSE
+};
+struct BlkPass {
+  BlkGeom g;
+  int32_t stage_begin;
+};
+struct BlkPlan {
+  std::vector<BlkPass> passes;
+  std::vector<BlkStage> stages;
+  std::vector<BlkLayer<double>> layers;
+  std::vector<BlkMore> more;
+  std::vector<BlkOp> ops;
+  std::vector<double> ocoef;
+};
+// Rewrites a circuit as rotations, phases, controlled phases and CNOTs: the
+// single-qubit gates between two others merge, and left diagonals move on
+// to the qubit's next gate.  tol: the largest relative miss of a matrix
+// entry by the rotation form (else the gate stays dense).  False when a
+// two-qubit gate is neither a controlled phase nor a CNOT.
+bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<BlkGate>* out);
+// Appends one pass: geometry tg, its gates (on the physical bits of where[taken[i]]).
+// low: low bits that the first and the last stage keep on lanes (contiguous
+// accesses of 2^low amplitudes).
+void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, const std::vector<int>& taken,
+                     const std::vector<Gate>& where, bool fp64, int low, BlkPlan* plan);
+// Plans a circuit as register-resident passes (arguments as plan_tiles);
+// false when it holds gates they do not take.
+bool plan_block(int n, int L, int b, const std::vector<Gate>& gates, bool fp64, int max_take, bool relabel,
+                BlkPlan* plan, std::vector<int>* final_pos);
+
+// Byte image of a plan for the device (reals in the state's precision) and
+// where its parts lie.
+struct BlkLayout {
+  size_t o_geoms, o_layers, o_more, o_ops, o_ocoef, total;
+};
+BlkLayout block_image(const BlkPlan& plan, bool fp64, std::vector<char>* buf);
+inline BlkDev block_device(const BlkLayout& l, const char* dev, const BlkPass& p) {
+  return BlkDev{(const BlkStage*)dev + p.stage_begin, dev + l.o_layers, (const BlkMore*)(dev + l.o_more),
+                (const BlkOp*)(dev + l.o_ops), dev + l.o_ocoef};
+}
 
 struct FusedBlock {
   std::vector<int> targets;           // physical

@@ -619,6 +619,12 @@ __global__ __launch_bounds__(64) void k_expect_final(const double* __restrict__ 
   out3[3 * k + c] = s;
 }
 
+inline unsigned tile_grid(uint64_t ntiles) {
+  return (unsigned)(ntiles < (1u << 20) ? ntiles : (1u << 20));
+}
+
+}  // namespace
+
 // Workgroups of a kernel that fit on the device at once (cached per kernel).
 uint64_t resident_blocks(const void* kern, int threads) {
   static std::mutex mu;
@@ -635,12 +641,6 @@ uint64_t resident_blocks(const void* kern, int threads) {
   cache[kern] = r;
   return r;
 }
-
-inline unsigned tile_grid(uint64_t ntiles) {
-  return (unsigned)(ntiles < (1u << 20) ? ntiles : (1u << 20));
-}
-
-}  // namespace
 
 int tile_max_bits(juqcs_dtype dt) {
   return dt == JUQCS_C128 ? TileCfg<double>::kMaxBits : TileCfg<float>::kMaxBits;
