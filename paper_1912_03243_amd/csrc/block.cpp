@@ -170,7 +170,17 @@ bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<
       rw.flush(b.q[0], false);
       rw.flush(b.q[1], true);
     } else {
-      return false;
+      bool swap = one(m[0]) && one(m[6]) && one(m[9]) && one(m[15]);
+      for (int i = 0; i < 16; ++i)
+        if (i != 0 && i != 6 && i != 9 && i != 15 && !zero(m[i])) swap = false;
+      if (!swap) return false;
+      rw.flush(b.q[0], true);
+      rw.flush(b.q[1], true);
+      b.kind = BlkGate::CNOT;
+      out->push_back(b);
+      std::swap(b.q[0], b.q[1]);
+      out->push_back(b);
+      std::swap(b.q[0], b.q[1]);
     }
     out->push_back(b);
   }
@@ -312,6 +322,7 @@ struct EOp {  // an op of a stage before it is put into layers
 
 struct StagePlan {
   uint32_t regs = 0;
+  std::vector<std::pair<int, int>> lin;  // CNOTs (control, target) done by the exchange before the stage
   C scal{1, 0};  // scalar factors of the stage's gates that no op carries
   std::vector<EOp> ops;
   int reg[8], thr[kBlkThrBits];
@@ -322,11 +333,60 @@ struct StagePlan {
 struct Frame {
   uint32_t flip = 0;
   C pend[32];
+  C outer[64];  // the same for bits of the tile number
   Frame() {
     for (C& z : pend) z = C{1, 0};
+    for (C& z : outer) z = C{1, 0};
   }
   bool flipped(int q) const { return !outside(q) && ((flip >> q) & 1); }
 };
+
+// CNOTs that no later gate of the stage waits for are left to the exchange
+// that follows: there they only change the addresses.
+void leave_cnots(const std::vector<Local>& gs, std::vector<int>* take, std::vector<int>* keep) {
+  uint32_t any = 0, full = 0;  // bits that later gates of the stage act on (full: not diagonally)
+  std::vector<int> stay, left;
+  for (size_t k = take->size(); k-- > 0;) {
+    const int i = (*take)[k];
+    const Local& l = gs[i];
+    const uint32_t a = bit(l.q[0]), b = l.q[1] < 0 ? 0u : bit(l.q[1]);
+    if (l.g->kind == BlkGate::CNOT) {
+      if (!outside(l.q[0]) && !(b & any) && !(a & full)) {
+        left.push_back(i);
+        continue;
+      }
+      full |= b;
+    } else if (nondiag(l)) {
+      full |= a;
+    }
+    any |= a | b;
+    stay.push_back(i);
+  }
+  take->assign(stay.rbegin(), stay.rend());
+  keep->insert(keep->end(), left.begin(), left.end());
+  std::sort(keep->begin(), keep->end());
+}
+
+// Takes the CNOTs between tile bits that no gate left behind comes before.
+void take_linear(const std::vector<Local>& gs, Frame& fr, std::vector<int>* rem,
+                 std::vector<std::pair<int, int>>* lin) {
+  uint32_t any = 0, full = 0;
+  std::vector<int> keep;
+  for (int i : *rem) {
+    const Local& l = gs[i];
+    const uint32_t a = bit(l.q[0]), b = l.q[1] < 0 ? 0u : bit(l.q[1]);
+    if (l.g->kind == BlkGate::CNOT && !outside(l.q[0]) && !(b & any) && !(a & full) && one(fr.pend[l.q[1]])) {
+      lin->push_back({l.q[0], l.q[1]});
+      if (fr.flipped(l.q[0])) fr.flip ^= b;  // a flipped control also flips the target
+      continue;
+    }
+    any |= a | b;
+    if (l.g->kind == BlkGate::CNOT) full |= b;
+    else if (nondiag(l)) full |= a;
+    keep.push_back(i);
+  }
+  rem->swap(keep);
+}
 
 // Emits the ops of a stage for its gates in order.
 struct Emitter {
@@ -376,7 +436,8 @@ struct Emitter {
   // phase of the set half of bit q (as stored)
   void phase_on(int q, C p) {
     const int j = jof(q);
-    if (j >= 0) wait[j].ph = mul(wait[j].ph, p);
+    if (outside(q)) fr.outer[q - 64] = mul(fr.outer[q - 64], p);
+    else if (j >= 0) wait[j].ph = mul(wait[j].ph, p);
     else fr.pend[q] = mul(fr.pend[q], p);
   }
 
@@ -499,7 +560,16 @@ void settle_frame(Frame& fr, StagePlan& st, int tb, int K) {
       else rest.push_back(std::move(e));
     }
   }
-  if (s.cm || s.tmask) st.ops.push_back(std::move(s));
+  EOp outer;
+  outer.kind = E_PHASE;
+  for (int b = 0; b < 64; ++b) {
+    const C p = fr.outer[b];
+    if (one(p)) continue;
+    if (p.re == -1.0 && p.im == 0.0) s.gmask |= uint64_t(1) << b;
+    else outer.col.push_back({p, 64 + b});
+  }
+  if (!outer.col.empty()) rest.push_back(std::move(outer));
+  if (s.cm || s.tmask || s.gmask) st.ops.push_back(std::move(s));
   for (EOp& e : rest) st.ops.push_back(std::move(e));
 }
 
@@ -736,6 +806,8 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
     if (dest[b] < low) low_dst |= 1u << b;
   std::vector<StagePlan> st;
   Frame fr;
+  std::vector<std::pair<int, int>> lin;
+  bool stuck = false;  // the last stage and exchange took nothing
   do {
     int got = 0;
     const uint32_t first = st.empty() ? low_src : 0u;
@@ -752,14 +824,20 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
     Absorber ab(P);
     for (int i : rem) (ab.take(gs[i]) ? take : keep).push_back(i);
     leave_for_later(gs, P, &take, &keep);
+    // (a CNOT onto a bit with a phase pending cannot wait for an exchange)
+    if (!stuck) leave_cnots(gs, &take, &keep);
+    stuck = take.empty();
     int k = 0;
     for (int b = 0; b < tb; ++b)
       if ((P >> b) & 1) s.reg[k++] = b;
     Emitter em(gs, fr, s, K);
     for (int i : take) em.gate(gs[i]);
     em.finish();
+    s.lin.swap(lin);
     st.push_back(std::move(s));
     rem.swap(keep);
+    take_linear(gs, fr, &rem, &lin);
+    stuck = stuck && lin.empty();
   } while (!rem.empty());
   // stage at which a bit is next a register bit (or must be a lane)
   auto next_use = [&](int b, size_t from) {
@@ -768,8 +846,9 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
     return (int)st.size() + 1;
   };
   // the tile is written from lanes that hold the destination's low bits
-  if ((st.back().regs & low_dst) || (st.size() == 1 && low_src != low_dst)) {
+  if ((st.back().regs & low_dst) || (st.size() == 1 && low_src != low_dst) || !lin.empty()) {
     StagePlan s;
+    s.lin.swap(lin);
     // bits that stay where they are first, then the highest
     int k = 0;
     for (int pass = 0; pass < 2; ++pass)
@@ -788,8 +867,22 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
   // phases (8 lanes of 16 bytes, 16 of 8) reach distinct bank slots
   std::vector<int> wv;
   constexpr int phase = 4;
+  // at[s][b]: where (in which old element's slot) the tile element 1 << b of
+  // stage s lies: the CNOTs done by the exchanges so far, linear over XOR
+  std::vector<std::vector<int>> at(st.size(), std::vector<int>(tb));
+  std::vector<char> crosses(st.size(), 0);
+  for (int b = 0; b < tb; ++b) at[0][b] = 1 << b;
   for (size_t s = 0; s < st.size(); ++s) {
     StagePlan& p = st[s];
+    if (s > 0)
+      for (int b = 0; b < tb; ++b) {
+        int x = 1 << b, y = 0;
+        for (size_t i = p.lin.size(); i-- > 0;)
+          if ((x >> p.lin[i].first) & 1) x ^= 1 << p.lin[i].second;
+        for (int c = 0; c < tb; ++c)
+          if ((x >> c) & 1) y ^= at[s - 1][c];
+        at[s][b] = y;
+      }
     const bool f = s == 0, l = s + 1 == st.size();
     const uint32_t no = p.regs | (f ? low_src : 0u) | (l ? low_dst : 0u);
     bool keep = !f;
@@ -814,7 +907,7 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
           }
     }
     int span = 1;
-    auto dir = [&](int b) { return slot(1 << b) & ((1 << phase) - 1); };
+    auto dir = [&](int b) { return slot(at[s][b]) & ((1 << phase) - 1); };
     auto grow = [&](int b) {
       int g = span;
       for (int u = 0; u < (1 << phase); ++u)
@@ -832,6 +925,10 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
       }
     for (int i = 0; i < lanes; ++i) p.thr[i] = ln[i];
     for (int i = 0; i < waves; ++i) p.thr[lanes + i] = wv[i];
+    // a CNOT onto a wave bit (of either side) moves amplitudes between waves
+    for (const auto& g : p.lin)
+      for (int i = lanes; i < nthr; ++i)
+        if (g.second == p.thr[i] || g.second == st[s - 1].thr[i]) crosses[s] = 1;
   }
   // serialise
   BlkPass out{};
@@ -854,16 +951,17 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
   auto same_waves = [&](const StagePlan& a, const StagePlan& b) {
     return std::equal(a.thr + lanes, a.thr + nthr, b.thr + lanes);
   };
-  g.tile_sync = st.size() > 1 && !same_waves(st.front(), st.back());
+  g.tile_sync = st.size() > 1 && (!same_waves(st.front(), st.back()) ||
+                                  std::find(crosses.begin(), crosses.end(), 1) != crosses.end());
   for (int b = 0; b < tb; ++b)
     if ((fr.flip >> b) & 1) g.st_flip |= uint64_t(1) << phys(dest[b]);
   out.stage_begin = (int32_t)plan->stages.size();
   for (size_t s = 0; s < st.size(); ++s) {
     const StagePlan& p = st[s];
     BlkStage x{};
-    x.exchange = s > 0 && !same_waves(st[s - 1], p) ? BLK_CROSS : BLK_WAVE;
-    for (int j = 0; j < K; ++j) x.row[j] = slot(1 << p.reg[j]) * kSlotBytes;
-    for (int i = 0; i < nthr; ++i) x.thr[i] = slot(1 << p.thr[i]) * kSlotBytes;
+    x.exchange = s > 0 && (!same_waves(st[s - 1], p) || crosses[s]) ? BLK_CROSS : BLK_WAVE;
+    for (int j = 0; j < K; ++j) x.row[j] = slot(at[s][p.reg[j]]) * kSlotBytes;
+    for (int i = 0; i < nthr; ++i) x.thr[i] = slot(at[s][p.thr[i]]) * kSlotBytes;
     emit_layers(p, nthr, x, plan);
   }
   plan->passes.push_back(out);
@@ -912,6 +1010,32 @@ BlkLayout block_image(const BlkPlan& plan, bool fp64, std::vector<char>* buf) {
   return l;
 }
 
+namespace {
+
+// Modelled duration (ms) of a plan on 2^30 amplitudes, from passes measured
+// on MI355X: HBM time of a pass, and on chip a rotation, a layer, an exchange
+// and the tile's own load and store; the two overlap to about two thirds.
+double plan_ms(const BlkPlan& p, bool fp64) {
+  const double mem = fp64 ? 6.2 : 3.1, half = fp64 ? 1.0 : 0.6;
+  double total = 0.0;
+  for (const BlkPass& ps : p.passes) {
+    double c = 0.8;
+    for (int s = 0; s < ps.g.nst; ++s) {
+      const BlkStage& st = p.stages[ps.stage_begin + s];
+      if (s > 0 && st.exchange != BLK_STAY) c += 0.45;
+      c += 0.2 * (st.misc_end - st.misc_begin) + 0.05 * (st.layer_end - st.layer_begin);
+      for (int l = st.layer_begin; l < st.layer_end; ++l)
+        for (int j = 0; j < kBlkRegs; ++j)
+          if (p.layers[l].flags & (BLK_ROT << j)) c += 0.135;
+    }
+    c *= half;
+    total += std::max(c, mem) + 0.35 * std::min(c, mem);
+  }
+  return total;
+}
+
+}  // namespace
+
 bool plan_block(int n, int L, int b, const std::vector<Gate>& gates, bool fp64, int max_take, bool relabel,
                 BlkPlan* plan, std::vector<int>* final_pos) {
   *plan = BlkPlan();
@@ -920,29 +1044,45 @@ bool plan_block(int n, int L, int b, const std::vector<Gate>& gates, bool fp64, 
   const double tol = fp64 ? 2e-15 : 1e-9;
   std::vector<BlkGate> bg;
   if (!block_gates(n, gates, tol, &bg)) return false;
-  std::vector<Gate> shape(bg.size());  // the qubits alone, for the tile selection
-  for (size_t i = 0; i < bg.size(); ++i) {
-    shape[i].nq = bg[i].kind == BlkGate::CPHASE || bg[i].kind == BlkGate::CNOT ? 2 : 1;
-    shape[i].q[0] = bg[i].q[0];
-    shape[i].q[1] = bg[i].q[1];
+  std::vector<Gate> shape(bg.size(), Gate{});  // the qubits alone, for the tile selection
+  // Two selections: gates in the tile only when all of their qubits are, or
+  // (more gates per pass, but greedier) controlled phases with one qubit and
+  // CNOTs with their target in the tile, and diagonal gates past each other.
+  // Where a run takes far longer than planning (2^24 amplitudes or more), the
+  // better by plan_ms; else the second.
+  double best = 0.0;
+  for (int strict = 0; strict < (n >= 24 ? 2 : 1); ++strict) {
+    for (size_t i = 0; i < bg.size(); ++i) {
+      const BlkGate::Kind k = bg[i].kind;
+      shape[i].nq = k == BlkGate::CPHASE || k == BlkGate::CNOT ? 2 : 1;
+      shape[i].q[0] = bg[i].q[0];
+      shape[i].q[1] = bg[i].q[1];
+      shape[i].diag_on = strict ? 0 : k == BlkGate::CPHASE ? 3 : k == BlkGate::CNOT || k == BlkGate::PHASE1 ? 1 : 0;
+    }
+    TileSchedule sched;
+    if (relabel) {
+      select_tiles_relabel(n, L, b, 0, shape, &sched, max_take);
+    } else {
+      select_tiles(n, L, b, 0, shape, &sched, max_take);
+      sched.final_pos.resize(n);
+      for (int q = 0; q < n; ++q) sched.final_pos[q] = q;
+    }
+    if (sched.gates != (int64_t)shape.size()) continue;
+    const std::vector<Gate>& src = sched.tgates.empty() ? shape : sched.tgates;
+    BlkPlan cand;
+    for (size_t i = 0; i < sched.passes.size(); ++i) {
+      std::vector<BlkGate> mine;
+      for (int t : sched.taken[i]) mine.push_back(bg[sched.tsrc.empty() ? t : sched.tsrc[t]]);
+      plan_block_pass(sched.passes[i].g, mine, sched.taken[i], src, fp64, std::min(L, fp64 ? 5 : 6), &cand);
+    }
+    const double ms = plan_ms(cand, fp64);
+    if (plan->passes.empty() || ms < best) {
+      best = ms;
+      *plan = std::move(cand);
+      *final_pos = sched.final_pos;
+    }
   }
-  TileSchedule sched;
-  if (relabel) {
-    select_tiles_relabel(n, L, b, 0, shape, &sched, max_take);
-  } else {
-    select_tiles(n, L, b, 0, shape, &sched, max_take);
-    sched.final_pos.resize(n);
-    for (int q = 0; q < n; ++q) sched.final_pos[q] = q;
-  }
-  if (sched.gates != (int64_t)shape.size()) return false;
-  const std::vector<Gate>& src = sched.tgates.empty() ? shape : sched.tgates;
-  for (size_t i = 0; i < sched.passes.size(); ++i) {
-    std::vector<BlkGate> mine;
-    for (int t : sched.taken[i]) mine.push_back(bg[sched.tsrc.empty() ? t : sched.tsrc[t]]);
-    plan_block_pass(sched.passes[i].g, mine, sched.taken[i], src, fp64, std::min(L, fp64 ? 5 : 6), plan);
-  }
-  *final_pos = sched.final_pos;
-  return true;
+  return !plan->passes.empty() || bg.empty();
 }
 
 }  // namespace juqcs

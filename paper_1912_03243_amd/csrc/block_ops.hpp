@@ -81,8 +81,8 @@ struct Regs {
     }
   }
 
-  // pairs of register bit J whose register index holds every bit of M trade
-  // places where on is set
+  // pairs of register bit J trade places: those whose register index holds
+  // the bits of M, or (M = 0) all of the thread's where on is set
   template <int J, int M>
   __device__ __forceinline__ void swap_if(bool on) {
 #pragma unroll
@@ -90,10 +90,11 @@ struct Regs {
       if (((r >> J) & 1) || (r & M) != M) continue;
       const int s = r | (1 << J);
       const v2 x = a[r], y = a[s];
-      a[r].x = on ? y.x : x.x;
-      a[r].y = on ? y.y : x.y;
-      a[s].x = on ? x.x : y.x;
-      a[s].y = on ? x.y : y.y;
+      const bool t = M != 0 || on;
+      a[r].x = t ? y.x : x.x;
+      a[r].y = t ? y.y : x.y;
+      a[s].x = t ? x.x : y.x;
+      a[s].y = t ? x.y : y.y;
     }
   }
 
@@ -200,7 +201,7 @@ __device__ __forceinline__ void run_misc(Regs<T, K>& v, Const<BlkOp> ops, Const<
       }
 #undef JUQCS_SWAP
     } else if (kind == BLK_SIGNS) {
-      v.signs(cm, parity_sign(tid & tm, 0));
+      v.signs(cm, parity_sign(tid & tm, tau & gm));
     } else {  // BLK_PHASE on two register bits, or on none (a phase per thread)
       T C = c[0], S = c[1];
       collect(ops, oc, ops[o].col_begin, ops[o].col_end, tid, tau, &C, &S);
@@ -353,7 +354,9 @@ __device__ __forceinline__ void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Redistributes the tile from the layout of stage a to that of stage b.
+// Redistributes the tile from the layout of stage a to that of stage b (and
+// does the CNOTs planned between them: they only change which slot b's
+// threads read).
 // Every thread writes the amplitudes that it holds to their own slots and
 // reads the next stage's from theirs: a slot is only ever written by the
 // thread that read it last, so one barrier per exchange is enough, and none

@@ -357,6 +357,9 @@ struct Gate {  // decoded gate: matrix on 1 or 2 qubits (physical positions)
   int q[2];
   cplx<double> m[16];  // 2x2 (first 4) or 4x4, index b_q0 + 2 b_q1
   bool diag;
+  // Bit j: the tile selection may count on the gate being diagonal on q[j]
+  // (it commutes with other gates that are, and q[j] may lie outside the tile).
+  int diag_on = 0;
 };
 
 bool decode_gate(const juqcs_gate& g, int n, Gate* out, std::string* err);

@@ -244,31 +244,46 @@ double gate_flops(const Gate& g) {
 // ---------------------------------------------------------------------------
 namespace {
 
-// Qubit masks of the gates rem lists (n <= 40 qubits fit one word).
-std::vector<uint64_t> rem_masks(const std::vector<Gate>& gates, const std::vector<int>& rem) {
-  std::vector<uint64_t> m(rem.size());
-  for (size_t i = 0; i < rem.size(); ++i) {
-    const Gate& g = gates[rem[i]];
-    uint64_t x = 0;
-    for (int j = 0; j < g.nq; ++j) x |= uint64_t(1) << g.q[j];
-    m[i] = x;
-  }
+// Qubit masks of a gate (n <= 40 qubits fit one word): those it is diagonal
+// on, and the others.
+struct GateMask {
+  uint64_t diag = 0, full = 0;
+};
+
+GateMask gate_mask(const Gate& g) {
+  GateMask m;
+  for (int j = 0; j < g.nq; ++j) ((g.diag_on >> j) & 1 ? m.diag : m.full) |= uint64_t(1) << g.q[j];
   return m;
 }
 
-// Number of gates at the front of the remaining list (as qubit masks)
-// absorbable by the tile: a gate is taken if its qubits are in the tile and
-// none of them is blocked by an earlier gate that was not taken.
-int absorb_count(const std::vector<uint64_t>& rm, uint64_t tile) {
-  uint64_t blocked = 0;
+std::vector<GateMask> rem_masks(const std::vector<Gate>& gates, const std::vector<int>& rem) {
+  std::vector<GateMask> m(rem.size());
+  for (size_t i = 0; i < rem.size(); ++i) m[i] = gate_mask(gates[rem[i]]);
+  return m;
+}
+
+// Which gates of the remaining list, in order, a tile absorbs: all qubits but
+// the diagonal ones in the tile (and at least one of any), and no earlier gate
+// left behind that it does not commute with.  Gates that are diagonal on a
+// qubit commute there.
+struct TileAbsorber {
+  uint64_t tile, full = 0, diag = 0;  // qubits of gates left behind
+  bool take(const GateMask& m) {
+    if (!(m.full & ~tile) && ((m.full | m.diag) & tile) && !(m.full & (full | diag)) && !(m.diag & full))
+      return true;
+    full |= m.full;
+    diag |= m.diag;
+    return false;
+  }
+  bool done() const { return !(tile & ~full); }
+};
+
+int absorb_count(const std::vector<GateMask>& rm, uint64_t tile) {
+  TileAbsorber ab{tile};
   int cnt = 0;
-  for (uint64_t m : rm) {
-    if (!(m & ~tile) && !(m & blocked)) {
-      ++cnt;
-    } else {
-      blocked |= m;
-      if (!(tile & ~blocked)) break;  // every tile qubit blocked
-    }
+  for (const GateMask& m : rm) {
+    if (ab.take(m)) ++cnt;
+    else if (ab.done()) break;
   }
   return cnt;
 }
@@ -362,7 +377,7 @@ void select_tiles(int n, int L, int b, int block_bits, const std::vector<Gate>& 
         if ((int)cand.size() >= kCandidates) break;
       }
       // greedy: add the candidate that lets the most gates through
-      const std::vector<uint64_t> rm = rem_masks(gates, rem);
+      const std::vector<GateMask> rm = rem_masks(gates, rem);
       for (int step = 0; step < H; ++step) {
         int best = -1, bc = -1;
         const uint64_t base = tile_mask(in_tile);
@@ -389,18 +404,10 @@ void select_tiles(int n, int L, int b, int block_bits, const std::vector<Gate>& 
     std::sort(chosen.begin(), chosen.end());
     // absorb
     std::vector<int> taken, keep;
-    std::vector<char> blocked(n, 0);
+    TileAbsorber ab{tile_mask(in_tile)};
     for (int gi : rem) {
-      const Gate& g = gates[gi];
-      bool ok = max_take <= 0 || (int)taken.size() < max_take;
-      for (int j = 0; j < g.nq; ++j)
-        if (!in_tile[g.q[j]] || blocked[g.q[j]]) ok = false;
-      if (ok) {
-        taken.push_back(gi);
-      } else {
-        keep.push_back(gi);
-        for (int j = 0; j < g.nq; ++j) blocked[g.q[j]] = 1;
-      }
+      if (max_take > 0 && (int)taken.size() >= max_take) ab.tile = 0;
+      (ab.take(gate_mask(gates[gi])) ? taken : keep).push_back(gi);
     }
     if (taken.empty()) {  // the front gate cannot fit any tile: give up
       sched->gates -= (int64_t)rem.size();
@@ -445,7 +452,7 @@ std::vector<char> pick_tile(int n, int b, const std::vector<Gate>& gates, const 
     }
     if ((int)cand.size() >= kCandidates) break;
   }
-  const std::vector<uint64_t> rm = rem_masks(gates, rem);
+  const std::vector<GateMask> rm = rem_masks(gates, rem);
   while (count < b) {
     int best = -1, bc = -1;
     const uint64_t base = tile_mask(in_tile);
@@ -530,13 +537,11 @@ void select_tiles_relabel(int n, int L, int b, int block_bits, const std::vector
   while (!rem.empty()) {
     // absorb, in order, the gates whose qubits are all in the tile
     std::vector<int> taken, keep;
-    std::vector<char> blocked(n, 0);
+    TileAbsorber ab{tile_mask(tile)};
     for (int gi : rem) {
       const Gate& g = gates[gi];
-      bool ok = max_take <= 0 || (int)taken.size() < max_take;
-      for (int j = 0; j < g.nq; ++j)
-        if (!tile[g.q[j]] || blocked[g.q[j]]) ok = false;
-      if (ok) {
+      if (max_take > 0 && (int)taken.size() >= max_take) ab.tile = 0;
+      if (ab.take(gate_mask(g))) {
         Gate t = g;
         for (int j = 0; j < t.nq; ++j) t.q[j] = pos[t.q[j]];
         taken.push_back((int)sched->tgates.size());
@@ -544,7 +549,6 @@ void select_tiles_relabel(int n, int L, int b, int block_bits, const std::vector
         sched->tsrc.push_back(gi);
       } else {
         keep.push_back(gi);
-        for (int j = 0; j < g.nq; ++j) blocked[g.q[j]] = 1;
       }
     }
     if (taken.empty()) {  // the front gate cannot fit any tile: give up
@@ -581,7 +585,7 @@ void select_tiles_relabel(int n, int L, int b, int block_bits, const std::vector
         if (moved[w] && tile[w] && !nl[w]) nl[w] = 1, ++cnt, in.push_back(w);
       for (int p = 0; p < L; ++p)
         if (!nl[at[p]]) out.push_back(at[p]);
-      const std::vector<uint64_t> rm = rem_masks(gates, rem);
+      const std::vector<GateMask> rm = rem_masks(gates, rem);
       if (cnt == L && in.size() == out.size() && (int)in.size() <= kSwapCap &&
           absorb_count(rm, tile_mask(moved)) > absorb_count(rm, tile_mask(kept))) {
         // wire in[i] (gathered in this pass) trades places with out[i] (low);
