@@ -209,15 +209,17 @@ juqcs_status run_tile_plan(juqcs_state* st, const TilePlan& plan) {
 // Runs a register-resident plan: one upload, then every pass.
 juqcs_status run_block_plan(juqcs_state* st, const BlkPlan& plan) {
   if (plan.passes.empty()) return JUQCS_OK;
-  std::vector<char> buf;
-  const BlkLayout lay = block_image(plan, st->dt == JUQCS_C128, &buf);
+  const bool fp64 = st->dt == JUQCS_C128;
+  const BlkLayout lay = block_layout(BlkSizes(plan), fp64);
+  std::vector<char> buf(lay.total, 0);
+  block_image(plan, fp64, buf.data());
   char* dev = nullptr;
   if (juqcs_status rc = upload(st, buf.data(), buf.size(), &dev)) return rc;
+  const BlkDev bd = block_device(lay, dev);
   for (size_t i = 0; i < plan.passes.size(); ++i) {
-    const BlkPass& p = plan.passes[i];
     prof_begin(st);
-    hipError_t e = launch_block(st->dt, st->amps, p.g, (const BlkGeom*)(dev + lay.o_geoms) + i,
-                                block_device(lay, dev, p), st->stream);
+    hipError_t e = launch_block(st->dt, st->amps, plan.passes[i], (const BlkPass*)(dev + lay.o_geoms) + i, bd,
+                                st->stream);
     prof_end(st);
     if (e != hipSuccess) return hip_fail(e, "tile pass launch");
     st->bytes += full_pass_bytes(st);

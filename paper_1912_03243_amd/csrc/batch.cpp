@@ -24,6 +24,9 @@ namespace {
 
 using C = cplx<double>;
 constexpr int kChunkTiles = 32;
+// Tiles per ticket of register-resident passes: nothing is built per ticket
+// there, so small chunks only balance the round's end.
+constexpr int kBlockChunkTiles = 4;
 
 juqcs_status fail(juqcs_status st, const std::string& msg) {
   set_error(msg);
@@ -33,6 +36,10 @@ juqcs_status hip_fail(hipError_t e, const char* where) {
   set_error(std::string(where) + ": " + hipGetErrorString(e));
   return JUQCS_ERR_HIP;
 }
+
+// Circuits of at least this many qubits run register-resident passes.
+bool block_batch(int n) { return n >= kBlkMinTile; }
+int block_bits_for(int n) { return std::min(n, kBlkMinTile + kBlkTileSizes - 1); }
 
 int tile_bits_for(int n) { return std::min(n, batch_max_bits()); }
 int low_bits_for(int n) { return std::min(7, tile_bits_for(n)); }
@@ -110,7 +117,7 @@ void parallel_for(int count, F f) {
 // Byte layout of a batch work list in device memory (every part 256-aligned).
 struct ListLayout {
   size_t o_groups = 0, o_passes = 0, o_ops = 0, o_mats = 0, o_tickets = 0, o_soff = 0, o_nq = 0,
-         o_pos = 0, total = 0;
+         o_pos = 0, o_bgroups = 0, o_blk = 0, total = 0;
 };
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -119,36 +126,30 @@ constexpr int kMaxBatchQubits = 32;            // layout entries per circuit
 constexpr size_t kBatchStage = size_t(4) << 20;  // read-out staging after the list
 
 // Layout of a list of count circuits with the given totals of passes (one
-// group per pass), ops and coefficients, and the most passes of one circuit.
-ListLayout list_layout(int64_t count, int64_t passes, int64_t ops, int64_t mats, int64_t nrounds) {
+// group per pass), ops and coefficients, and the most passes of one circuit;
+// and of register-resident passes: their groups, sub-rounds and distinct plans.
+ListLayout list_layout(int64_t count, int64_t passes, int64_t ops, int64_t mats, int64_t nrounds,
+                       int64_t bgroups = 0, const BlkSizes& bz = BlkSizes(), int64_t bsubs = 0) {
   ListLayout l;
   l.o_groups = 0;
   l.o_passes = align256(l.o_groups + passes * sizeof(BatchGroup));
   l.o_ops = align256(l.o_passes + passes * sizeof(BatchPass));
   l.o_mats = align256(l.o_ops + std::max<int64_t>(ops, 1) * sizeof(TileOp));
   l.o_tickets = align256(l.o_mats + std::max<int64_t>(mats, 1) * sizeof(cplx<float>));
-  l.o_soff = align256(l.o_tickets + std::max<int64_t>(nrounds, 1) * sizeof(uint64_t));
+  l.o_soff = align256(l.o_tickets + std::max<int64_t>(nrounds + bsubs, 1) * sizeof(uint64_t));
   l.o_nq = align256(l.o_soff + count * sizeof(uint64_t));
   l.o_pos = align256(l.o_nq + count * sizeof(int32_t));
-  l.total = align256(l.o_pos + (size_t)count * kMaxBatchQubits);
+  l.o_bgroups = align256(l.o_pos + (size_t)count * kMaxBatchQubits);
+  l.o_blk = align256(l.o_bgroups + bgroups * sizeof(BatchGroup));
+  l.total = align256(l.o_blk + (bgroups > 0 ? block_layout(bz, false).total : 0));
   return l;
-}
-
-ListLayout list_layout_of(const std::vector<TilePlan>& plans) {
-  int64_t passes = 0, ops = 0, mats = 0, rounds = 0;
-  for (const TilePlan& p : plans) {
-    passes += (int64_t)p.passes.size();
-    ops += (int64_t)p.ops.size();
-    mats += (int64_t)p.mats.size();
-    rounds = std::max<int64_t>(rounds, (int64_t)p.passes.size());
-  }
-  return list_layout((int64_t)plans.size(), passes, ops, mats, rounds);
 }
 
 // Host image of a work list: uploaded as is, then addressed through lay.
 struct HostList {
   std::vector<char> image;
   ListLayout lay;
+  BlkSizes bsizes;    // of the distinct register-resident plans
   BatchDevice dev{};  // round tables and counts; device pointers set by bind_list
   int64_t tasks = 0, gate_apps = 0, passes = 0;
 };
@@ -166,6 +167,13 @@ struct juqcs_batch {
   std::vector<int> kin;     // chosen on-chip fusion width per circuit
   std::vector<int8_t> pos;  // kMaxBatchQubits per circuit: physical bit of each qubit at the end
   std::vector<char> keep;   // per circuit (empty: none): start from the state in the buffer, not |0...0>
+  // register-resident circuits: their plan (null: fused passes), and per
+  // circuit (empty: none) the state that the first pass reads and the round
+  // that it runs in
+  std::vector<const BlkPlan*> bplan;
+  std::vector<uint64_t> src_off;
+  std::vector<int> delay;
+  std::vector<BlkPlan> own;  // plans of a batch's circuits
   // caller-owned workspace: the uploaded list, then the read-out staging
   char* work = nullptr;
   size_t work_bytes = 0;
@@ -209,7 +217,9 @@ juqcs_status make_list(juqcs_batch* B, const std::vector<TilePlan>& plans, HostL
   std::vector<BatchGroup> groups;
   std::vector<int> first_pass(B->count);
   L->tasks = L->gate_apps = L->passes = 0;
+  const auto block = [&](int c) { return !B->bplan.empty() && B->bplan[c]; };
   for (int c = 0; c < B->count; ++c) {
+    if (block(c)) continue;
     const TilePlan& p = plans[c];
     first_pass[c] = (int)passes.size();
     const int64_t op0 = (int64_t)ops.size(), m0 = (int64_t)mats.size();
@@ -231,7 +241,7 @@ juqcs_status make_list(juqcs_batch* B, const std::vector<TilePlan>& plans, HostL
     const int chunk = (int)std::min<int64_t>(ntiles, kChunkTiles);
     for (int i = 0; i < (int)p.passes.size(); ++i) {
       BatchGroup g{};
-      g.state_off = B->state_off[c];
+      g.state_off = g.src_off = B->state_off[c];
       g.circuit = c;
       g.pass = first_pass[c] + i;
       g.chunk_tiles = chunk;
@@ -271,16 +281,79 @@ juqcs_status make_list(juqcs_batch* B, const std::vector<TilePlan>& plans, HostL
   d.ngroups = (int)groups.size();
   d.count = B->count;
   d.nchunks = next;
+  // register-resident circuits: the distinct plans once, then a group per
+  // pass of a circuit, in rounds of passes and in each by tile size
+  BlkPlan all;
+  std::map<const BlkPlan*, int> first;
+  std::vector<BatchGroup> bgroups;
+  std::vector<int> sub;  // sub-round of each group
+  for (int c = 0; c < B->count; ++c) {
+    if (!block(c)) continue;
+    const BlkPlan& p = *B->bplan[c];
+    if (!first.count(&p)) {
+      first[&p] = (int)all.passes.size();
+      append_plan(p, &all);
+    }
+    const int delay = B->delay.empty() ? 0 : B->delay[c];
+    for (int i = 0; i < (int)p.passes.size(); ++i) {
+      const int64_t ntiles = int64_t(1) << (B->n[c] - p.passes[i].g.b);
+      BatchGroup g{};
+      g.state_off = g.src_off = B->state_off[c];
+      if (i == 0 && !B->src_off.empty()) g.src_off = B->src_off[c];
+      g.circuit = c;
+      g.pass = first[&p] + i;
+      g.chunk_tiles = (int)std::min<int64_t>(ntiles, kBlockChunkTiles);
+      g.init = (i == 0 && (B->keep.empty() || !B->keep[c])) ? 1 : 0;
+      bgroups.push_back(g);
+      sub.push_back((delay + i) * kBlkTileSizes + p.passes[i].g.b - kBlkMinTile);
+      L->tasks += ntiles;
+    }
+    L->passes += (int64_t)p.passes.size();
+    L->gate_apps += B->dec.empty() ? 0 : (int64_t)B->dec[c].size();
+  }
+  const int nsubs = sub.empty() ? 0 : *std::max_element(sub.begin(), sub.end()) + 1;
+  d.bround_group.clear();
+  d.bround_chunk.clear();
+  {
+    std::vector<int> order(bgroups.size());
+    for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return sub[a] < sub[b]; });
+    std::vector<BatchGroup> sorted;
+    long long chunk = 0;
+    size_t o = 0;
+    for (int k = 0; k < nsubs; ++k) {
+      d.bround_group.push_back((int32_t)o);
+      d.bround_chunk.push_back(chunk);
+      for (; o < order.size() && sub[order[o]] == k; ++o) {
+        BatchGroup g = bgroups[order[o]];
+        g.first_chunk = chunk;
+        const int64_t ntiles = int64_t(1) << (B->n[g.circuit] - all.passes[g.pass].g.b);
+        chunk += ntiles / g.chunk_tiles;
+        sorted.push_back(g);
+      }
+    }
+    if (nsubs) {
+      d.bround_group.push_back((int32_t)o);
+      d.bround_chunk.push_back(chunk);
+    }
+    bgroups.swap(sorted);
+  }
   L->lay = list_layout(B->count, (int64_t)passes.size(), (int64_t)ops.size(), (int64_t)mats.size(),
-                       d.nrounds);
+                       d.nrounds, (int64_t)bgroups.size(), BlkSizes(all), nsubs);
   const ListLayout& l = L->lay;
   if (B->pos.size() != (size_t)B->count * kMaxBatchQubits) set_layout(B, 0, {});
   L->image.assign(l.total, 0);
   char* h = L->image.data();
-  std::memcpy(h + l.o_groups, groups.data(), groups.size() * sizeof(BatchGroup));
-  std::memcpy(h + l.o_passes, passes.data(), passes.size() * sizeof(BatchPass));
-  std::memcpy(h + l.o_ops, ops.data(), ops.size() * sizeof(TileOp));
-  std::memcpy(h + l.o_mats, mats.data(), mats.size() * sizeof(cplx<float>));
+  const auto put = [&](size_t o, const void* p, size_t bytes) {
+    if (bytes) std::memcpy(h + o, p, bytes);
+  };
+  put(l.o_groups, groups.data(), groups.size() * sizeof(BatchGroup));
+  put(l.o_passes, passes.data(), passes.size() * sizeof(BatchPass));
+  put(l.o_ops, ops.data(), ops.size() * sizeof(TileOp));
+  put(l.o_mats, mats.data(), mats.size() * sizeof(cplx<float>));
+  put(l.o_bgroups, bgroups.data(), bgroups.size() * sizeof(BatchGroup));
+  if (!bgroups.empty()) block_image(all, false, h + l.o_blk);
+  L->bsizes = BlkSizes(all);
   std::memcpy(h + l.o_soff, B->state_off.data(), B->count * sizeof(uint64_t));
   std::memcpy(h + l.o_nq, B->n.data(), B->count * sizeof(int32_t));
   std::memcpy(h + l.o_pos, B->pos.data(), B->pos.size());
@@ -298,6 +371,13 @@ juqcs_status bind_list(const HostList& L, char* dbuf, BatchDevice* dev, hipStrea
   dev->ops = (const TileOp*)(dbuf + L.lay.o_ops);
   dev->mats = (const cplx<float>*)(dbuf + L.lay.o_mats);
   dev->tickets = (uint64_t*)(dbuf + L.lay.o_tickets);
+  if (!dev->bround_group.empty()) {
+    const BlkLayout bl = block_layout(L.bsizes, false);
+    dev->bgroups = (const BatchGroup*)(dbuf + L.lay.o_bgroups);
+    dev->bpasses = (const BlkPass*)(dbuf + L.lay.o_blk + bl.o_geoms);
+    dev->bdev = block_device(bl, dbuf + L.lay.o_blk);
+    dev->btickets = dev->tickets + dev->nrounds;
+  }
   return JUQCS_OK;
 }
 
@@ -310,11 +390,12 @@ juqcs_status run_device(char* states, const BatchDevice& d, hipStream_t s) {
 // Timed trial of one circuit's plan (used by the autotuner): runs it as a
 // one-circuit batch on the circuit's own state region, with its work list
 // at the start of the batch's workspace.  Infinite when the list does not fit.
-double time_plan(juqcs_batch* B, int c, const TilePlan& plan, hipStream_t s) {
+double time_plan(juqcs_batch* B, int c, const TilePlan& plan, const BlkPlan* bplan, hipStream_t s) {
   juqcs_batch T;
   T.count = 1;
   T.n = {B->n[c]};
   T.state_off = {B->state_off[c]};
+  T.bplan = {bplan};
   std::vector<TilePlan> plans{plan};
   HostList L;
   if (make_list(&T, plans, &L) != JUQCS_OK || L.lay.total > B->work_bytes) return 1e30;
@@ -395,7 +476,19 @@ juqcs_status juqcs_batch_create(juqcs_batch** out, int count, const int* n,
   // fusion width: fixed, or the cost model's choice per circuit (the timed
   // trials of juqcs_batch_autotune may replace it)
   std::vector<TilePlan> plans(count);
+  B->own.resize(count);
+  B->bplan.assign(count, nullptr);
   parallel_for(count, [&](int c) {
+    if (fuse == 0 && block_batch(n[c])) {
+      std::vector<int> final_pos;
+      const int b = block_bits_for(n[c]);
+      if (plan_block(n[c], std::min(7, b), b, B->dec[c], false, 0, B->relabel, &B->own[c], &final_pos)) {
+        B->bplan[c] = &B->own[c];
+        B->kin[c] = 1;  // gates one at a time
+        set_layout(B, c, final_pos);
+        return;
+      }
+    }
     TileSchedule sched;
     schedule_circuit(n[c], B->dec[c], &sched, B->relabel);
     set_layout(B, c, sched.final_pos);
@@ -462,24 +555,31 @@ juqcs_status juqcs_batch_autotune(juqcs_batch* B, void* hip_stream) {
   drop_graph(B);
   B->bound = false;  // the trials overwrite the uploaded list
   std::map<int, int> best_k;
+  std::map<int, char> fused;  // whether a fused plan beats the register-resident one
   for (int c = 0; c < B->count; ++c) {
     if (best_k.count(B->n[c])) continue;
     double best = 1e30;
     int bk = B->kin[c];
+    const double t_block = !B->bplan.empty() && B->bplan[c] ? time_plan(B, c, TilePlan(), B->bplan[c], s) : 1e30;
     for (int k = 1; k <= 4; ++k) {
       TilePlan p;
       plan_circuit(B->n[c], B->dec[c], k, B->relabel, &p);
-      const double t = time_plan(B, c, p, s);
+      const double t = time_plan(B, c, p, nullptr, s);
       if (t < best) {
         best = t;
         bk = k;
       }
     }
-    best_k[B->n[c]] = bk;
+    fused[B->n[c]] = best < t_block;
+    best_k[B->n[c]] = best < t_block ? bk : 1;
   }
   std::vector<TilePlan> plans(B->count);
   parallel_for(B->count, [&](int c) {
-    B->kin[c] = best_k[B->n[c]];
+    B->kin[c] = best_k.at(B->n[c]);
+    if (!B->bplan.empty() && B->bplan[c]) {
+      if (!fused.at(B->n[c])) return;
+      B->bplan[c] = nullptr;
+    }
     TileSchedule sched;
     plan_circuit(B->n[c], B->dec[c], B->kin[c], B->relabel, &plans[c], &sched);
     set_layout(B, c, sched.final_pos);

@@ -32,6 +32,7 @@ bool finite(C a) { return std::isfinite(a.re) && std::isfinite(a.im); }
 // commute with them, then emits them as one gate.
 struct Rewriter {
   double tol;
+  bool keep;  // phases of 1 too, so that the gates' kinds do not depend on their values
   std::vector<BlkGate>* out;
   struct Open {
     bool any = false;
@@ -53,7 +54,7 @@ struct Rewriter {
   }
 
   void push_phase(int q, C lam, C ph) {
-    if (one(ph) && one(lam)) return;
+    if (!keep && one(ph) && one(lam)) return;
     BlkGate g;
     g.kind = BlkGate::PHASE1;
     g.q[0] = q;
@@ -117,7 +118,7 @@ struct Rewriter {
         w.m[0] = C{1, 0};
         w.m[1] = w.m[2] = C{0, 0};
         w.m[3] = rest;
-        w.any = !one(rest);
+        w.any = keep || !one(rest);
         if (all && w.any) {
           w.any = false;
           push_phase(q, C{1, 0}, rest);
@@ -140,10 +141,11 @@ struct Rewriter {
 
 }  // namespace
 
-bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<BlkGate>* out) {
+bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<BlkGate>* out, bool keep) {
   out->clear();
   Rewriter rw;
   rw.tol = tol;
+  rw.keep = keep;
   rw.out = out;
   rw.open.resize(n);
   for (const Gate& g : gates) {
@@ -986,23 +988,26 @@ void put_reals(const BlkPlan& plan, const BlkLayout& l, char* h) {
 
 }  // namespace
 
-BlkLayout block_image(const BlkPlan& plan, bool fp64, std::vector<char>* buf) {
+BlkLayout block_layout(const BlkSizes& z, bool fp64) {
   const auto up = [](size_t x) { return (x + 255) & ~size_t(255); };
   BlkLayout l;
-  l.o_geoms = up(plan.stages.size() * sizeof(BlkStage));
-  l.o_layers = up(l.o_geoms + plan.passes.size() * sizeof(BlkGeom));
+  l.o_geoms = up(z.stages * sizeof(BlkStage));
+  l.o_layers = up(l.o_geoms + z.passes * sizeof(BlkPass));
   // two more layers: the kernels read up to two records ahead
-  l.o_more = up(l.o_layers + (plan.layers.size() + 2) * (fp64 ? sizeof(BlkLayer<double>) : sizeof(BlkLayer<float>)));
-  l.o_ops = up(l.o_more + plan.more.size() * sizeof(BlkMore));
-  l.o_ocoef = up(l.o_ops + plan.ops.size() * sizeof(BlkOp));
-  l.total = up(l.o_ocoef + plan.ocoef.size() * (fp64 ? sizeof(double) : sizeof(float)));
-  buf->assign(l.total, 0);
-  char* h = buf->data();
+  l.o_more = up(l.o_layers + (z.layers + 2) * (fp64 ? sizeof(BlkLayer<double>) : sizeof(BlkLayer<float>)));
+  l.o_ops = up(l.o_more + z.layers * sizeof(BlkMore));
+  l.o_ocoef = up(l.o_ops + z.ops * sizeof(BlkOp));
+  l.total = up(l.o_ocoef + 8 * z.ops * (fp64 ? sizeof(double) : sizeof(float)));
+  return l;
+}
+
+BlkLayout block_image(const BlkPlan& plan, bool fp64, char* h) {
+  const BlkLayout l = block_layout(BlkSizes(plan), fp64);
   const auto put = [&](size_t o, const void* p, size_t n) {
     if (n) std::memcpy(h + o, p, n);
   };
   put(0, plan.stages.data(), plan.stages.size() * sizeof(BlkStage));
-  for (size_t i = 0; i < plan.passes.size(); ++i) put(l.o_geoms + i * sizeof(BlkGeom), &plan.passes[i].g, sizeof(BlkGeom));
+  put(l.o_geoms, plan.passes.data(), plan.passes.size() * sizeof(BlkPass));
   put(l.o_more, plan.more.data(), plan.more.size() * sizeof(BlkMore));
   put(l.o_ops, plan.ops.data(), plan.ops.size() * sizeof(BlkOp));
   if (fp64) put_reals<double>(plan, l, h);
@@ -1036,53 +1041,104 @@ double plan_ms(const BlkPlan& p, bool fp64) {
 
 }  // namespace
 
+// The qubits of the gates alone, for the tile selection.  strict: a gate is
+// in a tile only when all of its qubits are; else (more gates per pass, but
+// greedier) controlled phases need one and CNOTs their target in the tile,
+// and gates that are diagonal on a qubit pass each other.
+void block_schedule(int n, int L, int b, const std::vector<BlkGate>& bg, int max_take, bool relabel, bool strict,
+                    BlkSchedule* out) {
+  std::vector<Gate>& shape = out->shape;
+  shape.assign(bg.size(), Gate{});
+  for (size_t i = 0; i < bg.size(); ++i) {
+    const BlkGate::Kind k = bg[i].kind;
+    shape[i].nq = k == BlkGate::CPHASE || k == BlkGate::CNOT ? 2 : 1;
+    shape[i].q[0] = bg[i].q[0];
+    shape[i].q[1] = bg[i].q[1];
+    shape[i].diag_on = strict ? 0 : k == BlkGate::CPHASE ? 3 : k == BlkGate::CNOT || k == BlkGate::PHASE1 ? 1 : 0;
+  }
+  out->kinds.clear();
+  for (const BlkGate& g : bg) out->kinds.push_back(g.kind);
+  out->low = std::min(L, n);
+  if (relabel) {
+    select_tiles_relabel(n, L, b, 0, shape, &out->sched, max_take);
+  } else {
+    select_tiles(n, L, b, 0, shape, &out->sched, max_take);
+    out->sched.final_pos.resize(n);
+    for (int q = 0; q < n; ++q) out->sched.final_pos[q] = q;
+  }
+  if (out->sched.passes.empty()) {  // no gates: one pass that writes the state as it is
+    TilePass p{};
+    p.g.n = n;
+    p.g.b = p.g.L = std::min(n, b);
+    out->sched.passes.push_back(p);
+    out->sched.taken.emplace_back();
+  }
+}
+
+bool block_build(const BlkSchedule& bs, const std::vector<BlkGate>& bg, bool fp64, BlkPlan* plan) {
+  if (bs.kinds.size() != bg.size() || bs.sched.gates != (int64_t)bg.size()) return false;
+  for (size_t i = 0; i < bg.size(); ++i)
+    if (bs.kinds[i] != bg[i].kind || bs.shape[i].q[0] != bg[i].q[0] || bs.shape[i].q[1] != bg[i].q[1]) return false;
+  const TileSchedule& sched = bs.sched;
+  const std::vector<Gate>& src = sched.tgates.empty() ? bs.shape : sched.tgates;
+  for (size_t i = 0; i < sched.passes.size(); ++i) {
+    std::vector<BlkGate> mine;
+    for (int t : sched.taken[i]) mine.push_back(bg[sched.tsrc.empty() ? t : sched.tsrc[t]]);
+    plan_block_pass(sched.passes[i].g, mine, sched.taken[i], src, fp64, std::min(bs.low, fp64 ? 5 : 6), plan);
+  }
+  return true;
+}
+
+void append_plan(const BlkPlan& p, BlkPlan* all) {
+  const int s0 = (int)all->stages.size(), l0 = (int)all->layers.size(), o0 = (int)all->ops.size();
+  for (BlkPass x : p.passes) {
+    x.stage_begin += s0;
+    all->passes.push_back(x);
+  }
+  for (BlkStage x : p.stages) {
+    x.layer_begin += l0;
+    x.layer_end += l0;
+    x.misc_begin += o0;
+    x.misc_end += o0;
+    all->stages.push_back(x);
+  }
+  all->layers.insert(all->layers.end(), p.layers.begin(), p.layers.end());
+  for (BlkMore x : p.more) {
+    for (int j = 0; j < kBlkRegs; ++j) {
+      x.col_begin[j] += o0;
+      x.col_end[j] += o0;
+    }
+    all->more.push_back(x);
+  }
+  for (BlkOp x : p.ops) {
+    x.col_begin += o0;
+    x.col_end += o0;
+    all->ops.push_back(x);
+  }
+  all->ocoef.insert(all->ocoef.end(), p.ocoef.begin(), p.ocoef.end());
+}
+
 bool plan_block(int n, int L, int b, const std::vector<Gate>& gates, bool fp64, int max_take, bool relabel,
                 BlkPlan* plan, std::vector<int>* final_pos) {
   *plan = BlkPlan();
-  // a matrix whose rotation form misses an entry by more than this (relative)
-  // stays a dense 2x2: a few FP64 roundings, or far below an FP32 rounding
-  const double tol = fp64 ? 2e-15 : 1e-9;
   std::vector<BlkGate> bg;
-  if (!block_gates(n, gates, tol, &bg)) return false;
-  std::vector<Gate> shape(bg.size(), Gate{});  // the qubits alone, for the tile selection
-  // Two selections: gates in the tile only when all of their qubits are, or
-  // (more gates per pass, but greedier) controlled phases with one qubit and
-  // CNOTs with their target in the tile, and diagonal gates past each other.
-  // Where a run takes far longer than planning (2^24 amplitudes or more), the
-  // better by plan_ms; else the second.
+  if (!block_gates(n, gates, block_tol(fp64), &bg)) return false;
+  // both selections where a run takes far longer than planning (2^24
+  // amplitudes or more), the better by plan_ms; else the second
   double best = 0.0;
   for (int strict = 0; strict < (n >= 24 ? 2 : 1); ++strict) {
-    for (size_t i = 0; i < bg.size(); ++i) {
-      const BlkGate::Kind k = bg[i].kind;
-      shape[i].nq = k == BlkGate::CPHASE || k == BlkGate::CNOT ? 2 : 1;
-      shape[i].q[0] = bg[i].q[0];
-      shape[i].q[1] = bg[i].q[1];
-      shape[i].diag_on = strict ? 0 : k == BlkGate::CPHASE ? 3 : k == BlkGate::CNOT || k == BlkGate::PHASE1 ? 1 : 0;
-    }
-    TileSchedule sched;
-    if (relabel) {
-      select_tiles_relabel(n, L, b, 0, shape, &sched, max_take);
-    } else {
-      select_tiles(n, L, b, 0, shape, &sched, max_take);
-      sched.final_pos.resize(n);
-      for (int q = 0; q < n; ++q) sched.final_pos[q] = q;
-    }
-    if (sched.gates != (int64_t)shape.size()) continue;
-    const std::vector<Gate>& src = sched.tgates.empty() ? shape : sched.tgates;
+    BlkSchedule bs;
+    block_schedule(n, L, b, bg, max_take, relabel, strict != 0, &bs);
     BlkPlan cand;
-    for (size_t i = 0; i < sched.passes.size(); ++i) {
-      std::vector<BlkGate> mine;
-      for (int t : sched.taken[i]) mine.push_back(bg[sched.tsrc.empty() ? t : sched.tsrc[t]]);
-      plan_block_pass(sched.passes[i].g, mine, sched.taken[i], src, fp64, std::min(L, fp64 ? 5 : 6), &cand);
-    }
+    if (!block_build(bs, bg, fp64, &cand)) continue;
     const double ms = plan_ms(cand, fp64);
     if (plan->passes.empty() || ms < best) {
       best = ms;
       *plan = std::move(cand);
-      *final_pos = sched.final_pos;
+      *final_pos = bs.sched.final_pos;
     }
   }
-  return !plan->passes.empty() || bg.empty();
+  return !plan->passes.empty();
 }
 
 }  // namespace juqcs

@@ -205,12 +205,27 @@ struct BlkGeom {
   int32_t ld_thr[kBlkThrBits], ld_reg[kBlkRegs], st_thr[kBlkThrBits], st_reg[kBlkRegs];
   uint64_t st_flip;              // physical bits that are written complemented
 };
+struct BlkPass {
+  BlkGeom g;
+  int32_t stage_begin;
+  int32_t pad;
+};
 struct BlkDev {  // a plan in device memory
   const BlkStage* stages;
   const void* layers;  // BlkLayer<T>
   const BlkMore* more; // one per layer
   const BlkOp* ops;
   const void* ocoef;   // 8 per op
+};
+
+struct BatchGroup {  // every tile of one pass of one circuit
+  uint64_t state_off;    // byte offset of the circuit's C64 state
+  uint64_t src_off;      // of the state that the pass reads (register-resident passes)
+  int64_t first_chunk;   // first ticket of this group
+  int32_t circuit;
+  int32_t pass;          // index into the BatchPass array
+  int32_t chunk_tiles;   // tiles claimed per ticket
+  int32_t init;          // 1: start from |0...0> instead of loading
 };
 
 // ---------------------------------------------------------------------------
@@ -254,9 +269,14 @@ hipError_t launch_expect(juqcs_dtype dt, const void* amps, const void* scales, c
 
 // Register-resident tile passes (k_block.hip): tile sizes that have a kernel.
 bool block_sized(juqcs_dtype dt, int b);
-// g: the pass's geometry, d_geom the same in device memory.
-hipError_t launch_block(juqcs_dtype dt, void* amps, const BlkGeom& g, const BlkGeom* d_geom, const BlkDev& d,
+// p: the pass, d_pass the same in device memory.
+hipError_t launch_block(juqcs_dtype dt, void* amps, const BlkPass& p, const BlkPass* d_pass, const BlkDev& d,
                         hipStream_t s);
+// Rounds of many states' passes (C64): groups [g0, g1) of tiles of 2^b
+// amplitudes, chunks [c0, c1), claimed through *ticket.
+hipError_t launch_block_round(int b, char* states, const BatchGroup* groups, int g0, int g1,
+                              const BlkPass* passes, const BlkDev& d, uint64_t* ticket, long long c0,
+                              long long c1, hipStream_t s);
 // Workgroups of a kernel that fit on the device at once (cached per kernel).
 uint64_t resident_blocks(const void* kern, int threads);
 
@@ -284,14 +304,6 @@ struct BatchPass {  // one tile pass of one circuit
   int32_t op_begin, op_count;
 };
 
-struct BatchGroup {  // every tile of one pass of one circuit
-  uint64_t state_off;    // byte offset of the circuit's C64 state
-  int64_t first_chunk;   // first ticket of this group
-  int32_t circuit;
-  int32_t pass;          // index into the BatchPass array
-  int32_t chunk_tiles;   // tiles claimed per ticket
-  int32_t init;          // 1: start from |0...0> instead of loading
-};
 
 struct BatchDevice {
   const BatchGroup* groups;
@@ -305,7 +317,16 @@ struct BatchDevice {
   std::vector<int64_t> round_chunk;    // host: first chunk of each round (+ end)
   int count;
   long long nchunks;
+  // Register-resident passes: sub-round k of round r (tiles of 2^(11 + k)
+  // amplitudes) is entry kBlkTileSizes r + k of the tables (+ end)
+  const BatchGroup* bgroups = nullptr;
+  const BlkPass* bpasses = nullptr;
+  BlkDev bdev{};
+  uint64_t* btickets = nullptr;   // one per sub-round
+  std::vector<int32_t> bround_group;
+  std::vector<int64_t> bround_chunk;
 };
+constexpr int kBlkTileSizes = 3, kBlkMinTile = 11;
 
 int batch_max_bits();
 int batch_mma_cap();  // 8x8 ops per pass whose tables the batch kernel holds in LDS
@@ -430,10 +451,6 @@ struct BlkGate {
   cplx<double> lam{1, 0};   // scalar factor (ROT, PHASE1)
   cplx<double> m[4];        // DENSE
 };
-struct BlkPass {
-  BlkGeom g;
-  int32_t stage_begin;
-};
 struct BlkPlan {
   std::vector<BlkPass> passes;
   std::vector<BlkStage> stages;
@@ -447,7 +464,9 @@ struct BlkPlan {
 // to the qubit's next gate.  tol: the largest relative miss of a matrix
 // entry by the rotation form (else the gate stays dense).  False when a
 // two-qubit gate is neither a controlled phase nor a CNOT.
-bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<BlkGate>* out);
+// keep: phases that happen to be 1 stay in the list, so that its shape (kinds
+// and qubits) is the same for circuits that differ in their diagonals' values.
+bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<BlkGate>* out, bool keep = false);
 // Appends one pass: geometry tg, its gates (on the physical bits of where[taken[i]]).
 // low: low bits that the first and the last stage keep on lanes (contiguous
 // accesses of 2^low amplitudes).
@@ -458,14 +477,39 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
 bool plan_block(int n, int L, int b, const std::vector<Gate>& gates, bool fp64, int max_take, bool relabel,
                 BlkPlan* plan, std::vector<int>* final_pos);
 
+// The relative miss of a matrix entry by the rotation form up to which a
+// gate is not kept dense: a few FP64 roundings, or far below an FP32 one.
+inline double block_tol(bool fp64) { return fp64 ? 2e-15 : 1e-9; }
+// Tile selection of a rewritten circuit; plans of circuits of the same shape
+// (kinds and qubits) can be built on it with other values.
+struct BlkSchedule {
+  TileSchedule sched;
+  std::vector<Gate> shape;
+  std::vector<BlkGate::Kind> kinds;
+  int low = 0;
+};
+void block_schedule(int n, int L, int b, const std::vector<BlkGate>& bg, int max_take, bool relabel, bool strict,
+                    BlkSchedule* out);
+// Appends the schedule's passes with bg's values; false when bg has another shape.
+bool block_build(const BlkSchedule& bs, const std::vector<BlkGate>& bg, bool fp64, BlkPlan* plan);
+
 // Byte image of a plan for the device (reals in the state's precision) and
 // where its parts lie.
-struct BlkLayout {
-  size_t o_geoms, o_layers, o_more, o_ops, o_ocoef, total;
+struct BlkSizes {
+  size_t passes = 0, stages = 0, layers = 0, ops = 0;
+  BlkSizes() = default;
+  explicit BlkSizes(const BlkPlan& p)
+      : passes(p.passes.size()), stages(p.stages.size()), layers(p.layers.size()), ops(p.ops.size()) {}
 };
-BlkLayout block_image(const BlkPlan& plan, bool fp64, std::vector<char>* buf);
-inline BlkDev block_device(const BlkLayout& l, const char* dev, const BlkPass& p) {
-  return BlkDev{(const BlkStage*)dev + p.stage_begin, dev + l.o_layers, (const BlkMore*)(dev + l.o_more),
+// Appends p to all (indices moved).
+void append_plan(const BlkPlan& p, BlkPlan* all);
+struct BlkLayout {
+  size_t o_geoms, o_layers, o_more, o_ops, o_ocoef, total;  // o_geoms: BlkPass
+};
+BlkLayout block_layout(const BlkSizes& z, bool fp64);
+BlkLayout block_image(const BlkPlan& plan, bool fp64, char* image);  // image: zeroed, layout's total bytes
+inline BlkDev block_device(const BlkLayout& l, const char* dev) {
+  return BlkDev{(const BlkStage*)dev, dev + l.o_layers, (const BlkMore*)(dev + l.o_more),
                 (const BlkOp*)(dev + l.o_ops), dev + l.o_ocoef};
 }
 

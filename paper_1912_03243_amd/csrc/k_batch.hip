@@ -443,8 +443,17 @@ int batch_mma_cap() { return kBatchTabs; }
 int batch_max_gather() { return kBatchGather; }
 
 hipError_t launch_batch(char* states, const BatchDevice& d, hipStream_t s) {
-  hipLaunchKernelGGL(k_batch_reset, dim3((d.nrounds + kThreads - 1) / kThreads), dim3(kThreads), 0, s,
-                     (unsigned long long*)d.tickets, d.nrounds);
+  // the ticket counters of both kinds of rounds lie next to each other
+  const int subs = d.bround_group.empty() ? 0 : (int)d.bround_group.size() - 1;
+  const int counters = d.nrounds + subs;
+  hipLaunchKernelGGL(k_batch_reset, dim3((counters + kThreads - 1) / kThreads), dim3(kThreads), 0, s,
+                     (unsigned long long*)d.tickets, counters);
+  for (int k = 0; k < subs; ++k) {
+    hipError_t e = launch_block_round(kBlkMinTile + k % kBlkTileSizes, states, d.bgroups, d.bround_group[k],
+                                      d.bround_group[k + 1], d.bpasses, d.bdev, d.btickets + k,
+                                      d.bround_chunk[k], d.bround_chunk[k + 1], s);
+    if (e != hipSuccess) return e;
+  }
   static uint64_t slots = 0;
   if (slots == 0) {
     int dev = 0, cus = 256, per = 1;

@@ -61,10 +61,18 @@ __device__ __forceinline__ void amp_ptrs_flip(V* base, uint64_t off, Const<int32
 // workgroup's tile is on its way from or to HBM, the others compute.  (With
 // the next tile prefetched into registers instead, FP64 had room for 8 waves:
 // brick30 175 ms per step against 165.)
+// The geometry is read again for every tile, through an opaque pointer: kept
+// over the layers it would hold the scalar registers that their coefficients
+// need.
+__device__ __forceinline__ Const<BlkGeom> geometry(const BlkPass* p) {
+  asm volatile("" : "+s"(p));
+  return as_const<BlkGeom>(&p->g);
+}
+
 template <typename T, int TB, int K>
 __global__ __launch_bounds__(1 << (TB - K), 4) void k_block(cplx<T>* __restrict__ psi,
-                                                                const BlkGeom* __restrict__ geom,
-                                                                BlkDev d, int n, int nst, int tile_sync) {
+                                                            const BlkPass* __restrict__ pass, BlkDev d, int n,
+                                                            int nst, int tile_sync) {
   constexpr int R = 1 << K, TBITS = TB - K;
   __shared__ alignas(16) char sh[8 << TB];
   typedef T v2 __attribute__((ext_vector_type(2)));
@@ -74,56 +82,123 @@ __global__ __launch_bounds__(1 << (TB - K), 4) void k_block(cplx<T>* __restrict_
   uint64_t tau = bi * per + (bi < extra ? bi : extra);
   const uint64_t tau_end = tau + per + (bi < extra ? 1 : 0);
   if (tau >= tau_end) return;
-  // The geometry is read again for every tile, through an opaque pointer:
-  // kept over the layers it would hold the scalar registers that their
-  // coefficients need.
-  const auto geometry = [&]() {
-    const BlkGeom* p = geom;
-    asm volatile("" : "+s"(p));
-    return as_const<BlkGeom>(p);
-  };
-  const uint64_t lt = place<TBITS>(threadIdx.x, geometry()->ld_thr);
-  const uint64_t wt = place<TBITS>(threadIdx.x, geometry()->st_thr) ^ geometry()->st_flip;
-  auto load = [&](uint64_t t, v2* a) {
-    const Const<BlkGeom> g = geometry();
-    v2* p[R];
-    amp_ptrs<K>(gp + block_base(t, g) + lt, g->ld_reg, p);
-#pragma unroll
-    for (int r = 0; r < R; ++r) a[r] = ld_stream(p[r]);
-  };
+  const uint64_t lt = place<TBITS>(threadIdx.x, geometry(pass)->ld_thr);
+  const uint64_t wt = place<TBITS>(threadIdx.x, geometry(pass)->st_thr) ^ geometry(pass)->st_flip;
   Regs<T, K> v;
-  load(tau, v.a);
   for (;;) {
+    {
+      const Const<BlkGeom> g = geometry(pass);
+      v2* p[R];
+      amp_ptrs<K>(gp + block_base(tau, g) + lt, g->ld_reg, p);
+#pragma unroll
+      for (int r = 0; r < R; ++r) v.a[r] = ld_stream(p[r]);
+    }
     run_stages<T, TB, K>(v, sh, d, nst, tau);
     {
-      const Const<BlkGeom> g = geometry();
+      const Const<BlkGeom> g = geometry(pass);
       v2* p[R];
       amp_ptrs_flip<K>(gp + block_base(tau, g), wt, g->st_reg, p);
 #pragma unroll
       for (int r = 0; r < R; ++r) st_stream(p[r], v.a[r]);
     }
     if (++tau >= tau_end) break;
-    load(tau, v.a);
     if (tile_sync) __syncthreads();
+  }
+}
+
+// One round of many C64 states: workgroups claim chunks of tiles through the
+// ticket counter until none are left (none ever waits for another).  States
+// are read and written through the caches: part states and small circuits
+// stay there from pass to pass.
+template <int TB, int K>
+__global__ __launch_bounds__(1 << (TB - K), 4) void k_block_round(
+    char* __restrict__ states, const BatchGroup* __restrict__ groups, int g0, int g1,
+    const BlkPass* __restrict__ passes, BlkDev d, unsigned long long* __restrict__ ticket, long long c0,
+    long long c1) {
+  constexpr int R = 1 << K, TBITS = TB - K;
+  __shared__ alignas(16) char sh[8 << TB];
+  __shared__ long long s_t;
+  __shared__ int s_g;
+  typedef float v2 __attribute__((ext_vector_type(2)));
+  const BlkStage* const stages = d.stages;
+  for (;;) {
+    __syncthreads();  // the last chunk's exchanges are done with sh
+    if (threadIdx.x == 0) {
+      const long long t = c0 + (long long)atomicAdd(ticket, 1ull);
+      int g = -1;
+      if (t < c1) {  // last group of the round whose first chunk is <= t
+        int lo = g0, hi = g1 - 1;
+        while (lo < hi) {
+          const int mid = (lo + hi + 1) >> 1;
+          if (groups[mid].first_chunk <= t) lo = mid;
+          else hi = mid - 1;
+        }
+        g = lo;
+      }
+      s_t = t;
+      s_g = g;
+    }
+    __syncthreads();
+    const int gi = __builtin_amdgcn_readfirstlane(s_g);
+    if (gi < 0) break;  // every workgroup leaves once the round's tickets run out
+    const int t_lo = __builtin_amdgcn_readfirstlane((int)s_t), t_hi = __builtin_amdgcn_readfirstlane((int)(s_t >> 32));
+    const long long t = ((long long)t_hi << 32) | (uint32_t)t_lo;
+    const Const<BatchGroup> grp = as_const<BatchGroup>(groups + gi);
+    const BlkPass* pass = passes + grp->pass;
+    v2* dst = reinterpret_cast<v2*>(states + grp->state_off);
+    const v2* src = reinterpret_cast<const v2*>(states + grp->src_off);
+    const bool init = grp->init != 0;
+    uint64_t tau = (uint64_t)(t - grp->first_chunk) * grp->chunk_tiles;
+    const uint64_t tau_end = tau + grp->chunk_tiles;
+    const int nst = geometry(pass)->nst, tile_sync = geometry(pass)->tile_sync;
+    d.stages = stages + as_const<BlkPass>(pass)->stage_begin;
+    const uint64_t lt = place<TBITS>(threadIdx.x, geometry(pass)->ld_thr);
+    const uint64_t wt = place<TBITS>(threadIdx.x, geometry(pass)->st_thr) ^ geometry(pass)->st_flip;
+    Regs<float, K> v;
+    for (;;) {
+      {
+        const Const<BlkGeom> g = geometry(pass);
+        if (init) {  // first pass: the state is |0...0>
+#pragma unroll
+          for (int r = 0; r < R; ++r) v.a[r] = v2{r == 0 && tau == 0 && lt == 0 ? 1.0f : 0.0f, 0.0f};
+        } else {
+          const v2* p[R];
+          amp_ptrs<K>(src + block_base(tau, g) + lt, g->ld_reg, p);
+#pragma unroll
+          for (int r = 0; r < R; ++r) v.a[r] = *p[r];
+        }
+      }
+      run_stages<float, TB, K>(v, sh, d, nst, tau);
+      {
+        const Const<BlkGeom> g = geometry(pass);
+        v2* p[R];
+        amp_ptrs_flip<K>(dst + block_base(tau, g), wt, g->st_reg, p);
+#pragma unroll
+        for (int r = 0; r < R; ++r) *p[r] = v.a[r];
+      }
+      if (++tau >= tau_end) break;
+      if (tile_sync) __syncthreads();
+    }
   }
 }
 
 }  // namespace
 
 bool block_sized(juqcs_dtype dt, int b) {
-  if (dt == JUQCS_C128) return b >= 11 && b <= 13;
-  if (dt == JUQCS_C64) return b >= 11 && b <= 13;
-  return false;
+  return (dt == JUQCS_C128 || dt == JUQCS_C64) && b >= kBlkMinTile && b < kBlkMinTile + kBlkTileSizes;
 }
 
-hipError_t launch_block(juqcs_dtype dt, void* amps, const BlkGeom& g,
-                        const BlkGeom* d_geom, const BlkDev& d, hipStream_t s) {
+hipError_t launch_block(juqcs_dtype dt, void* amps, const BlkPass& p, const BlkPass* d_pass, const BlkDev& d,
+                        hipStream_t s) {
+  const BlkGeom& g = p.g;
   const uint64_t ntiles = uint64_t(1) << (g.n - g.b);
+  BlkDev dev = d;
+  dev.stages += p.stage_begin;
 #define JUQCS_BLOCK(T, TB)                                                                     \
   do {                                                                                         \
     const uint64_t slots = resident_blocks((const void*)k_block<T, TB, kBlkRegs>, 1 << (TB - kBlkRegs)); \
     hipLaunchKernelGGL((k_block<T, TB, kBlkRegs>), dim3((unsigned)(ntiles < slots ? ntiles : slots)),    \
-                       dim3(1 << (TB - kBlkRegs)), 0, s, (cplx<T>*)amps, d_geom, d, g.n, g.nst, g.tile_sync); \
+                       dim3(1 << (TB - kBlkRegs)), 0, s, (cplx<T>*)amps, d_pass, dev, g.n, g.nst, g.tile_sync); \
   } while (0)
   if (dt == JUQCS_C128 && g.b == 13) JUQCS_BLOCK(double, 13);
   else if (dt == JUQCS_C128 && g.b == 12) JUQCS_BLOCK(double, 12);
@@ -133,6 +208,25 @@ hipError_t launch_block(juqcs_dtype dt, void* amps, const BlkGeom& g,
   else if (dt == JUQCS_C64 && g.b == 11) JUQCS_BLOCK(float, 11);
   else return hipErrorInvalidValue;
 #undef JUQCS_BLOCK
+  return hipGetLastError();
+}
+
+hipError_t launch_block_round(int b, char* states, const BatchGroup* groups, int g0, int g1,
+                              const BlkPass* passes, const BlkDev& d, uint64_t* ticket, long long c0,
+                              long long c1, hipStream_t s) {
+  if (c1 <= c0) return hipSuccess;
+#define JUQCS_ROUND(TB)                                                                            \
+  do {                                                                                             \
+    const uint64_t slots = resident_blocks((const void*)k_block_round<TB, kBlkRegs>, 1 << (TB - kBlkRegs)); \
+    const uint64_t grid = (uint64_t)(c1 - c0) < slots ? (uint64_t)(c1 - c0) : slots;               \
+    hipLaunchKernelGGL((k_block_round<TB, kBlkRegs>), dim3((unsigned)grid), dim3(1 << (TB - kBlkRegs)), 0, s, \
+                       states, groups, g0, g1, passes, d, (unsigned long long*)ticket, c0, c1);    \
+  } while (0)
+  if (b == 13) JUQCS_ROUND(13);
+  else if (b == 12) JUQCS_ROUND(12);
+  else if (b == 11) JUQCS_ROUND(11);
+  else return hipErrorInvalidValue;
+#undef JUQCS_ROUND
   return hipGetLastError();
 }
 
