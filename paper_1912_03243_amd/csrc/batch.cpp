@@ -8,6 +8,7 @@
 #include <cmath>
 #include <complex>
 #include <cstring>
+#include <exception>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -96,22 +97,33 @@ void plan_circuit(int n, const std::vector<Gate>& g, int kin, bool relabel, Tile
   if (sched_out) *sched_out = std::move(sched);
 }
 
-// Runs f(i) for i in [0, count) on the host's cores.
+// Runs f(i) for i in [0, count) on the host's cores; what one of them throws
+// is thrown to the caller, and with fewer threads to be had the others do
+// their share.
 template <typename F>
 void parallel_for(int count, F f) {
   const unsigned hw = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
   const int nt = (int)std::min<unsigned>(hw, (unsigned)count);
-  if (nt <= 1) {
-    for (int i = 0; i < count; ++i) f(i);
-    return;
-  }
   std::atomic<int> next(0);
-  std::vector<std::thread> th;
-  for (int t = 0; t < nt; ++t)
-    th.emplace_back([&]() {
+  std::mutex lock;
+  std::exception_ptr error;
+  const auto work = [&]() {
+    try {
       for (int i = next++; i < count; i = next++) f(i);
-    });
+    } catch (...) {
+      std::lock_guard<std::mutex> hold(lock);
+      if (!error) error = std::current_exception();
+      next = count;
+    }
+  };
+  std::vector<std::thread> th;
+  try {
+    for (int t = 1; t < nt; ++t) th.emplace_back(work);
+  } catch (const std::exception&) {
+  }
+  work();
   for (auto& x : th) x.join();
+  if (error) std::rethrow_exception(error);
 }
 
 // Byte layout of a batch work list in device memory (every part 256-aligned).
@@ -741,7 +753,19 @@ struct BranchSeg {
   std::vector<Gate> gates;  // its gates, qubits where the previous segment left them
   TilePlan tmpl;            // plan with placeholder diagonals
   TileSchedule sched;
+  // register-resident parts: one tile selection for every setting of the
+  // diagonals, the plan of each setting (bit j: crossing ks[j]), and the most
+  // that one of them takes in a work list
+  BlkSchedule bsched;
+  std::vector<BlkPlan> bplans;
+  BlkSizes bmax;
 };
+
+// Parts with a longer run of crossings keep the fused passes: the
+// register-resident plans of all 2^k settings of a run are made up front,
+// because a diagonal's value shapes its plan and a work list's share of the
+// workspace has to hold every one.
+constexpr size_t kMaxRun = 8;
 
 // One part of a decomposition: its circuit with a placeholder diagonal at
 // every crossing, and that circuit cut into segments.
@@ -753,6 +777,7 @@ struct BranchPart {
   std::vector<BranchSeg> segs;             // segs[0]: the gates before the first crossing
   std::vector<int> freek;                  // crossings with free bits, circuit order
   std::vector<int> phys;                   // physical bit of each local qubit at the leaves
+  bool block = false;                      // register-resident passes
   int free_bits(int L) const {
     int R = 0;
     for (auto& sl : slots) R += sl.second >= L ? 1 : 0;
@@ -767,12 +792,82 @@ struct BranchPart {
 // state of only 256 tiles).
 int branch_fusion_width(int nloc) { return nloc >= 24 ? 3 : 2; }
 
+void cut_part(BranchPart* bp, bool block);
+
+// The gates of a segment with its diagonals set (bit j of the setting: crossing ks[j]).
+std::vector<Gate> seg_gates(const BranchPart& bp, const BranchSeg& sg, long long setting) {
+  std::vector<Gate> hg = sg.gates;
+  for (auto& sl : bp.slots) {
+    if (sl.first < sg.g0 || sl.first >= sg.g1) continue;
+    const int j = (int)(std::find(sg.ks.begin(), sg.ks.end(), sl.second) - sg.ks.begin());
+    branch_diag((setting >> j) & 1 ? -1 : 1, hg[sl.first - sg.g0].m);
+  }
+  return hg;
+}
+
+// The register-resident plan of a segment for a setting of its diagonals.
+bool seg_plan(const BranchPart& bp, const BranchSeg& sg, long long setting, BlkPlan* out) {
+  std::vector<BlkGate> bg;
+  return block_gates(bp.nloc, seg_gates(bp, sg, setting), block_tol(false), &bg, true) &&
+         block_build(sg.bsched, bg, false, out);
+}
+
+// Selects the tiles of a part's segments for register-resident passes; pos:
+// where each qubit ends.  False when a segment's gates do not allow it.
+bool cut_block(BranchPart* bp, std::vector<int>* pos) {
+  const int b = block_bits_for(bp->nloc);
+  for (BranchSeg& sg : bp->segs) {
+    if (sg.ks.size() > kMaxRun) return false;
+    sg.gates.assign(bp->gates.begin() + sg.g0, bp->gates.begin() + sg.g1);
+    for (Gate& g : sg.gates)
+      for (int j = 0; j < g.nq; ++j) g.q[j] = (*pos)[g.q[j]];
+    std::vector<BlkGate> bg;
+    if (!block_gates(bp->nloc, seg_gates(*bp, sg, 0), block_tol(false), &bg, true)) return false;
+    block_schedule(bp->nloc, std::min(7, b), b, bg, 0, true, false, &sg.bsched);
+    for (int q = 0; q < bp->nloc; ++q) (*pos)[q] = sg.bsched.sched.final_pos[(*pos)[q]];
+  }
+  return true;
+}
+
+// The plans of every segment and setting of the register-resident parts; a
+// part that turns out not to allow one falls back to the fused passes.
+void plan_blocks(BranchPart* parts, int P) {
+  struct Todo {
+    BranchPart* bp;
+    BranchSeg* sg;
+    long long setting;
+  };
+  std::vector<Todo> todo;
+  for (int p = 0; p < P; ++p)
+    for (BranchSeg& sg : parts[p].segs) {
+      BranchPart& bp = parts[p];
+      if (!bp.block) continue;
+      sg.bplans.resize(size_t(1) << sg.ks.size());
+      for (size_t x = 0; x < sg.bplans.size(); ++x) todo.push_back({&bp, &sg, (long long)x});
+    }
+  std::vector<char> made(todo.size());
+  parallel_for((int)todo.size(), [&](int i) {
+    const Todo& t = todo[i];
+    made[i] = seg_plan(*t.bp, *t.sg, t.setting, &t.sg->bplans[t.setting]) ? 1 : 0;
+  });
+  for (size_t i = 0; i < todo.size(); ++i)
+    if (!made[i] && todo[i].bp->block) cut_part(todo[i].bp, false);
+  for (const Todo& t : todo) {
+    if (!t.bp->block) continue;
+    const BlkSizes z(t.sg->bplans[t.setting]);
+    t.sg->bmax.passes = std::max(t.sg->bmax.passes, z.passes);
+    t.sg->bmax.stages = std::max(t.sg->bmax.stages, z.stages);
+    t.sg->bmax.layers = std::max(t.sg->bmax.layers, z.layers);
+    t.sg->bmax.ops = std::max(t.sg->bmax.ops, z.ops);
+  }
+}
+
 // Cuts the part before every run of its crossings (consecutive gates of the
 // part), whatever the group size: the cut points and the segments' plans do
 // not depend on which crossings a group fixes, so a leaf goes through the
 // same plans, and holds the same bits, for any group size.  Each segment is
 // planned where the previous one left the qubits.
-void cut_part(BranchPart* bp) {
+void cut_part(BranchPart* bp, bool block) {
   const std::vector<std::pair<int, int>>& fr = bp->slots;
   const int ng = (int)bp->gates.size();
   bp->segs.clear();
@@ -790,6 +885,12 @@ void cut_part(BranchPart* bp) {
     i = j;
   }
   std::vector<int> pos(bp->nloc);
+  for (int q = 0; q < bp->nloc; ++q) pos[q] = q;
+  bp->block = block && block_batch(bp->nloc) && cut_block(bp, &pos);
+  if (bp->block) {
+    bp->phys = pos;
+    return;
+  }
   for (int q = 0; q < bp->nloc; ++q) pos[q] = q;
   for (BranchSeg& sg : bp->segs) {
     sg.gates.assign(bp->gates.begin() + sg.g0, bp->gates.begin() + sg.g1);
@@ -811,6 +912,18 @@ void set_free(BranchPart* bp, int L) {
     sg.nfree = 0;
     for (int k : sg.ks) sg.nfree += k >= L ? 1 : 0;
   }
+}
+
+// The setting of a segment's crossings (bit j: ks[j]) at a tree node (as node_plan).
+long long node_setting(const BranchSeg& sg, long long gi, int L, long long c) {
+  const int nfixed = (int)sg.ks.size() - sg.nfree;
+  long long x = 0;
+  for (int j = 0; j < (int)sg.ks.size(); ++j) {
+    const int k = sg.ks[j];
+    const long long bit = k < L ? (gi >> (L - 1 - k)) & 1 : (c >> (sg.nfree - 1 - (j - nfixed))) & 1;
+    x |= bit << j;
+  }
+  return x;
 }
 
 // The plan of one tree node: segment sg of the part with its diagonals set,
@@ -852,7 +965,7 @@ struct BranchJob {
 };
 
 juqcs_status branch_prepare(int n, const juqcs_gate* gates, size_t gate_count, const uint8_t* side,
-                            int words, size_t count, bool host_io, BranchJob* J) {
+                            int words, size_t count, bool host_io, bool block, BranchJob* J) {
   if (n < 2 || n > kBranchMaxQubits) return fail(JUQCS_ERR_ARG, "n must be in [2, 240]");
   if (words < (n + 63) / 64 || words > kBranchMaxWords)
     return fail(JUQCS_ERR_ARG, "words must be in [ceil(n / 64), 4]");
@@ -925,8 +1038,9 @@ juqcs_status branch_prepare(int n, const juqcs_gate* gates, size_t gate_count, c
   for (int p = 0; p < P; ++p) {
     parts[p].nloc = J->nloc[p];
     parts[p].sbytes = align256((size_t)8 << J->nloc[p]);
-    cut_part(&parts[p]);
   }
+  parallel_for(P, [&](int p) { cut_part(&parts[p], block); });
+  plan_blocks(parts, P);
   return JUQCS_OK;
 }
 
@@ -971,13 +1085,26 @@ BranchLayout branch_layout(const BranchJob& J, int L) {
   for (int p = 0; p < P; ++p) rounds = std::max(rounds, J.parts[p].segs.size());
   size_t list = 0;
   for (size_t r = 0; r < rounds; ++r) {
-    int64_t count = 0, passes = 0, ops = 0, mats = 0, nr = 0;
+    int64_t count = 0, passes = 0, ops = 0, mats = 0, nr = 0, bgroups = 0, bsubs = 0;
+    BlkSizes bz;
     for (int p = 0; p < P; ++p) {
       const BranchPart& bp = J.parts[p];
       if (r >= bp.segs.size()) continue;
       int done = 0;
       for (size_t i = 0; i < r; ++i) done += seg_free(bp.segs[i], L);
       const int64_t nodes = int64_t(1) << (done + seg_free(bp.segs[r], L));
+      if (bp.block) {  // one plan per setting of the free crossings, shared by the nodes
+        const BlkSizes& z = bp.segs[r].bmax;
+        const size_t plans = size_t(1) << seg_free(bp.segs[r], L);
+        count += nodes;
+        bgroups += nodes * (int64_t)z.passes;
+        bsubs = std::max<int64_t>(bsubs, kBlkTileSizes * ((int64_t)z.passes + 1));
+        bz.passes += plans * z.passes;
+        bz.stages += plans * z.stages;
+        bz.layers += plans * z.layers;
+        bz.ops += plans * z.ops;
+        continue;
+      }
       const TilePlan& t = bp.segs[r].tmpl;
       // an empty segment still runs one pass (the tree node's copy or init)
       const int64_t np = std::max<int64_t>(1, (int64_t)t.passes.size());
@@ -987,7 +1114,7 @@ BranchLayout branch_layout(const BranchJob& J, int L) {
       mats += nodes * (int64_t)t.mats.size();
       nr = std::max(nr, np);
     }
-    list = std::max(list, list_layout(count, passes, ops, mats, nr).total);
+    list = std::max(list, list_layout(count, passes, ops, mats, nr, bgroups, bz, bsubs).total);
   }
   const size_t cnt = J.count;
   size_t o = 0;
@@ -1025,10 +1152,10 @@ int group_bits(int m, int group_size) {
 // arrays.
 juqcs_status branch_amplitudes(int n, const juqcs_gate* gates, size_t gate_count, const uint8_t* side,
                                const uint64_t* z, int words, size_t count, int group_size, double* out,
-                               void* d_work, size_t work_bytes, hipStream_t s, bool dev) {
+                               void* d_work, size_t work_bytes, hipStream_t s, bool dev, bool block = true) {
   if (count > 0 && (!z || !out)) return fail(JUQCS_ERR_ARG, "null argument");
   auto J = std::make_unique<BranchJob>();
-  if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, !dev, J.get())) return rc;
+  if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, !dev, block, J.get())) return rc;
   // bits at or above n must be clear (only the words that can hold them)
   for (int w = n / 64; !dev && w < words; ++w) {
     const int lo = std::max(0, n - 64 * w);
@@ -1160,6 +1287,33 @@ juqcs_status branch_amplitudes(int n, const juqcs_gate* gates, size_t gate_count
         int done = 0;  // free bits split before this segment
         for (size_t i = 0; i < r; ++i) done += bp.segs[i].nfree;
         const int after = R - done - sg.nfree;
+        if (bp.block) {
+          // One plan per setting of the segment's crossings, shared by the
+          // nodes.  Every child but the first reads its parent's state in its
+          // first pass; the first one works in the parent's place, a round
+          // later (when the others have read it).
+          for (long long c = 0; c < (1ll << sg.nfree); ++c) {
+            const BlkPlan& plan = sg.bplans[node_setting(sg, gi, L, c)];
+            double f = 0.0;
+            for (const Gate& x : sg.gates) f += gate_flops(x);
+            const size_t np = plan.passes.size();
+            for (long long a = 0; a < (1ll << done); ++a) {
+              const long long parent = a << (R - done), leaf = parent + (c << after);
+              stats.gate_flops += f * std::ldexp(1.0, bp.nloc);
+              stats.pass_bytes += (double)np * 16.0 * std::ldexp(1.0, bp.nloc);
+              stats.tile_passes += (int64_t)np;
+              ++stats.tree_states;
+              plans.emplace_back();
+              B.bplan.push_back(&plan);
+              B.n.push_back(bp.nloc);
+              B.state_off.push_back(lay.base[p] + (size_t)leaf * bp.sbytes);
+              B.src_off.push_back(lay.base[p] + (size_t)(r > 0 ? parent : leaf) * bp.sbytes);
+              B.delay.push_back(r > 0 && c == 0 && sg.nfree > 0 ? 1 : 0);
+              B.keep.push_back(r > 0 ? 1 : 0);
+            }
+          }
+          continue;
+        }
         for (long long a = 0; a < (1ll << done); ++a)
           for (long long c = 0; c < (1ll << sg.nfree); ++c) {
             const long long parent = a << (R - done), leaf = parent + (c << after);
@@ -1173,8 +1327,11 @@ juqcs_status branch_amplitudes(int n, const juqcs_gate* gates, size_t gate_count
               stats.tile_passes += (int64_t)std::max<size_t>(1, plans.back().passes.size());
               ++stats.tree_states;
             }
+            B.bplan.push_back(nullptr);
             B.n.push_back(bp.nloc);
             B.state_off.push_back(lay.base[p] + (size_t)leaf * bp.sbytes);
+            B.src_off.push_back(B.state_off.back());
+            B.delay.push_back(0);
             B.keep.push_back(r > 0 ? 1 : 0);
             if (r > 0 && c > 0) {  // the child starts as a copy of its parent
               e = hipMemcpyAsync(states + B.state_off.back(), states + lay.base[p] + (size_t)parent * bp.sbytes,
@@ -1278,11 +1435,16 @@ extern "C" juqcs_status juqcs_branch_amplitudes_noalloc(int n, const juqcs_gate*
                                                         void* hip_stream) {
   std::lock_guard<std::mutex> lock(g_scratch_mu);
   size_t need = 0;
+  bool block = true;
   if (count > 0) {
-    auto J = std::make_unique<BranchJob>();
-    if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, false, J.get()))
-      return rc;
-    need = branch_layout(*J, group_size > 0 ? group_bits(J->m, group_size) : J->m).total;
+    // the fused passes where only their work list fits the scratch
+    for (int fused = 0; fused < 2 && (fused == 0 || need > (size_t)JUQCS_NOALLOC_SCRATCH_BYTES); ++fused) {
+      auto J = std::make_unique<BranchJob>();
+      block = fused == 0;
+      if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, false, block, J.get()))
+        return rc;
+      need = branch_layout(*J, group_size > 0 ? group_bits(J->m, group_size) : J->m).total;
+    }
     if (need > (size_t)JUQCS_NOALLOC_SCRATCH_BYTES)
       return fail(JUQCS_ERR_SIZE, "the decomposition needs " + std::to_string(need) +
                                       " bytes of workspace; the static scratch holds " +
@@ -1293,7 +1455,7 @@ extern "C" juqcs_status juqcs_branch_amplitudes_noalloc(int n, const juqcs_gate*
     if (juqcs_status rc = scratch_on_current_device(&ws)) return rc;
   return branch_amplitudes(n, gates, gate_count, side, d_z, words, count, group_size, d_out, ws,
                            count > 0 ? (size_t)JUQCS_NOALLOC_SCRATCH_BYTES : 0, (hipStream_t)hip_stream,
-                           true);
+                           true, block);
 }
 
 extern "C" juqcs_status juqcs_branch_last_stats(juqcs_branch_stats* out) {
@@ -1308,7 +1470,7 @@ extern "C" juqcs_status juqcs_branch_bytes(int n, const juqcs_gate* gates, size_
                                            size_t* bytes) {
   if (!min_bytes || !bytes) return fail(JUQCS_ERR_ARG, "null output");
   auto J = std::make_unique<BranchJob>();
-  if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, host_io != 0, J.get()))
+  if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, host_io != 0, true, J.get()))
     return rc;
   *min_bytes = branch_layout(*J, J->m).total;
   *bytes = branch_layout(*J, group_bits(J->m, group_size)).total;

@@ -14,6 +14,7 @@ gates' largest singular values; it grows at most linearly in the gates.
 import numpy as np
 import pytest
 
+from oracle import decomposition as odec
 from oracle import statevector as sv
 from paper_1912_03243_amd import workloads as W
 
@@ -125,3 +126,56 @@ def test_exact_gates_stay_exact(J, dtype):
         got = s.state_vector()
     want = sv.run_circuit(n, circ, psi=sv.init_state(n, 5))
     assert np.array_equal(got, want)
+
+
+def sized_circuits(sizes, gates, seed):
+    rng = np.random.default_rng(seed)
+    out = [(n, W.concat(*[random_gate(rng, n, False) for _ in range(gates)])) for n in sizes]
+    return out + [(n, W.empty_circuit(0)) for n in sizes[-2:]]
+
+
+@pytest.mark.parametrize("relabel", [-1, 0])
+@pytest.mark.parametrize("sizes", [[10, 11, 12, 13], [14, 11, 15, 13, 16, 12], [13, 13, 13], [17, 10]])
+def test_batch_tile_sizes(J, sizes, relabel):
+    # one tile and many, every tile size in one list, beside circuits too
+    # small for them and circuits without gates; run again over garbage
+    print("CASE batch", sizes, relabel, flush=True)
+    gates = 60
+    circuits = sized_circuits(sizes, gates, 5 + len(sizes))
+    b = J.Batch(circuits, relabel=relabel)
+    for again in range(2):
+        b.run()
+        b.wait()
+        for i, (n, circ) in enumerate(circuits):
+            want = sv.run_circuit(n, circ)
+            assert np.linalg.norm(b.state_vector(i) - want) < 8 * (len(circ) + 1) * EPS["c64"]
+            assert (b.fusion()[i] == 1) == (n >= 11)
+        b.states.fill_(7)
+    b.close()
+
+
+@pytest.mark.parametrize("group", [0, 4])
+@pytest.mark.parametrize("nloc, per_run", [(10, 2), (11, 2), (13, 3), (14, 1)])
+def test_branch_tile_sizes(J, nloc, per_run, group):
+    # two parts around the smallest and the largest tile (10 keeps the fused
+    # passes), runs of one to three crossings, every group size's tree;
+    # against the oracle's branch sum with the bound of the other branch tests
+    print("CASE branch", nloc, per_run, group, flush=True)
+    rng = np.random.default_rng(100 * nloc + per_run)
+    n, side = 2 * nloc, np.repeat([0, 1], nloc).astype(np.uint8)
+    recs = [W.gate(W.OP_U, q, u=W.haar_u2(rng)) for q in range(n)]
+    for run in range(3):
+        for h in (0, nloc):
+            for _ in range(20):
+                g = random_gate(rng, nloc, False).copy()
+                g["q0"] += h
+                g["q1"] = np.where(g["q1"] >= 0, g["q1"] + h, g["q1"])
+                recs.append(g)
+        if run < 2:
+            for _ in range(per_run):
+                recs.append(W.gate(W.OP_CZ, int(rng.integers(nloc)), nloc + int(rng.integers(nloc))))
+    circ = W.concat(*recs)
+    z = rng.integers(0, 1 << n, 64, dtype=np.uint64)
+    got = J.juqcs_branch_amplitudes(n, circ, side, z, group_size=group)
+    want = odec.branch_amplitudes(n, circ, side, z)
+    assert np.max(np.abs(got - want)) / np.abs(want).max() < 1e-5
