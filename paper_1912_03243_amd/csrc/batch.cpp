@@ -1055,7 +1055,18 @@ struct BranchLayout {
   size_t base[kBranchMaxParts] = {};        // byte offset of part p's leaves in the state region
   size_t o_z = 0, o_zp = 0, o_tab = 0, o_bad = 0, o_acc = 0, o_off = 0, o_sum = 0, o_states = 0,
          o_list = 0, total = 0;
+  // interleaved states of 2^il branches in a row (-1: none), after the rest
+  // of the workspace where it is that large: parts' logs and byte offsets
+  int il = -1;
+  int il_shift[kBranchMaxParts] = {};
+  size_t il_base[kBranchMaxParts] = {}, il_total = 0;
 };
+
+// Most bytes of interleaved states: half of the 256 MiB last-level cache, so
+// that they are read there after being written (and their sources too).
+constexpr size_t kInterleaveBytes = size_t(128) << 20;
+// Bitstrings below which sums read the states as they lie.
+constexpr size_t kManyStrings = size_t(1) << 16;
 
 // Free bits of segment sg and of the segments before it, with the first L
 // crossings fixed.
@@ -1133,6 +1144,29 @@ BranchLayout branch_layout(const BranchJob& J, int L) {
   B.o_states = take(states);
   B.o_list = take(list);
   B.total = o;
+  // Sums of many bitstrings read interleaved states: a bitstring's amplitudes
+  // of a part cost a cache line together instead of one each, for a copy of
+  // the states, which pays from one bitstring for some 16 amplitudes on (a
+  // line is 16 amplitudes, and a copy moves each twice).
+  size_t amps = 0;
+  for (int p = 0; p < P; ++p) amps += size_t(1) << J.parts[p].nloc;
+  if (cnt >= kManyStrings && cnt >= amps / 16)
+    for (int x = 1; x <= m - L; ++x) {
+      size_t end = o;
+      int shift[kBranchMaxParts] = {};
+      size_t base[kBranchMaxParts] = {};
+      for (int p = 0; p < P; ++p) {
+        for (auto& f : J.parts[p].slots) shift[p] += f.second >= m - x ? 1 : 0;
+        base[p] = end;
+        if (shift[p] > 0) end = align256(end + (size_t(8) << (J.parts[p].nloc + shift[p])));
+      }
+      if (end - o > kInterleaveBytes) break;
+      if (B.lds && x < m - L) continue;  // sums from LDS run over the whole group
+      B.il = x;
+      B.il_total = end;
+      std::copy(shift, shift + P, B.il_shift);
+      std::copy(base, base + P, B.il_base);
+    }
   return B;
 }
 
@@ -1195,20 +1229,22 @@ juqcs_status branch_amplitudes(int n, const juqcs_gate* gates, size_t gate_count
   stats.lds_sum = lay.lds ? 1 : 0;
   stats.sum_flops = (double)count * std::ldexp(1.0, m) * (6.0 * (P - 1) + 2.0);
   char* W = (char*)d_work;
-  // split table: each part's qubits and their physical bits at the leaves
+  // split table: runs of each part's qubits that stay together at the leaves
   std::vector<int32_t> tab(kBranchTabInts, 0);
   {
     int32_t* first = tab.data();
-    int32_t* qs = first + kBranchMaxParts + 1;
-    int32_t* phys = qs + kBranchMaxQubits;
+    int32_t* runs = first + kBranchMaxParts + 1;
     int o = 0;
     for (int p = 0; p < P; ++p) {
       first[p] = o;
+      int end = -1, dst = -1;  // what would prolong the last run
       for (int q = 0; q < n; ++q) {
         if (side[q] != p) continue;
-        qs[o] = q;
-        phys[o] = parts[p].phys[J->local[q]];
-        ++o;
+        const int d = parts[p].phys[J->local[q]];
+        if (q == end && d == dst && q % 64 != 0) runs[o - 1] += 1 << 16;
+        else runs[o++] = q | d << 8;
+        end = q + 1;
+        dst = d + 1;
       }
     }
     first[P] = o;
@@ -1265,13 +1301,16 @@ juqcs_status branch_amplitudes(int n, const juqcs_gate* gates, size_t gate_count
   if (e == hipSuccess) e = launch_zero(dbad, sizeof(int), s);
   if (e == hipSuccess)
     e = launch_branch_split(dev ? z : dz, words, (long long)count, P, n, dtab, zp, dbad, s);
-  if (e == hipSuccess) e = launch_zero(acc, count * 2 * sizeof(double), s);
   int bad = 0;
   if (e == hipSuccess) e = hipMemcpyAsync(&bad, dbad, sizeof(int), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   juqcs_status rc = JUQCS_OK;
   if (e != hipSuccess) rc = hip_fail(e, "branch set-up");
-  else if (bad) rc = fail(JUQCS_ERR_ARG, "bitstring >= 2^n");
+  else if (bad) {
+    e = launch_zero(acc, count * 2 * sizeof(double), s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    rc = e == hipSuccess ? fail(JUQCS_ERR_ARG, "bitstring >= 2^n") : hip_fail(e, "branch set-up");
+  }
   size_t rounds = 0;
   for (int p = 0; p < P; ++p) rounds = std::max(rounds, parts[p].segs.size());
   for (long long gi = 0; rc == JUQCS_OK && gi < ngroups; ++gi) {
@@ -1360,24 +1399,36 @@ juqcs_status branch_amplitudes(int n, const juqcs_gate* gates, size_t gate_count
     if (rc == JUQCS_OK) {
       const bool last = gi + 1 == ngroups;
       const double scale = std::ldexp(1.0, -m);
-      if (lds) {
-        BranchParts bp{};
-        for (int p = 0; p <= P; ++p) bp.first[p] = lay.first[p];
-        e = launch_branch_sum_lds(states, doff, P, bp, gsize, (const uint64_t*)dsum, zp, (long long)count,
-                                  acc, last, scale, s);
-      } else {
-        // Many coefficients read every state at random places: in chunks of
-        // branches whose states fit the 256 MiB last-level cache those reads
-        // stay on chip, at the price of one more pass over acc per chunk.
-        size_t per = 0;
-        for (int p = 0; p < P; ++p) per += parts[p].sbytes;
-        const long long chunk =
-            count >= (1u << 16) ? std::max<long long>(1, (long long)(((size_t)128 << 20) / per)) : gsize;
-        for (long long j0 = 0; e == hipSuccess && j0 < gsize; j0 += chunk) {
-          const long long c = std::min(chunk, gsize - j0);
-          e = launch_branch_gather_accum(states, doff, P, c, (const int32_t*)dsum + j0 * P, zp,
-                                         (long long)count, acc, last && j0 + c >= gsize, scale, s);
+      // Many coefficients read every state at random places: in chunks of
+      // branches whose states fit the last-level cache those reads stay on
+      // chip, at the price of one more pass over acc per chunk.
+      const bool il = lay.il > 0 && lay.il_total <= work_bytes;
+      BranchLeaves leaves{};
+      size_t per = 0;
+      for (int p = 0; p <= P; ++p) leaves.first[p] = lay.first[p];
+      for (int p = 0; p < P; ++p) {
+        leaves.shift[p] = lay.il_shift[p];
+        leaves.base[p] = lay.il_base[p] - lay.o_states;  // from the first state
+        per += parts[p].sbytes;
+      }
+      long long chunk = gsize;  // a power of two
+      if (il) chunk = 1ll << lay.il;
+      else if (!lds && count >= kManyStrings)
+        while (chunk > 1 && (size_t)chunk * per > kInterleaveBytes) chunk >>= 1;
+      for (long long j0 = 0; e == hipSuccess && j0 < gsize; j0 += chunk) {
+        for (int p = 0; il && p < P && e == hipSuccess; ++p) {
+          if (lay.il_shift[p] == 0) continue;
+          // the chunk's leaves of a part are a run of 2^shift
+          const int leaf = (lds ? (int)(t8[j0] >> (8 * p)) & 0xff : t32[(size_t)j0 * P + p]);
+          e = launch_branch_interleave(states, doff + leaf, lay.il_shift[p], parts[p].nloc,
+                                       states + leaves.base[p], s);
         }
+        if (e != hipSuccess) break;
+        const bool end = last && j0 + chunk >= gsize, begin = gi == 0 && j0 == 0;
+        e = lds ? launch_branch_sum_lds(states, doff, P, leaves, il, gsize, (const uint64_t*)dsum, zp,
+                                        (long long)count, acc, begin, end, scale, s)
+                : launch_branch_gather_accum(states, doff, P, leaves, il, chunk, (const int32_t*)dsum + j0 * P, zp,
+                                             (long long)count, acc, begin, end, scale, s);
       }
       if (e == hipSuccess) e = hipStreamSynchronize(s);
       if (e != hipSuccess) rc = hip_fail(e, "branch sum");
@@ -1473,7 +1524,8 @@ extern "C" juqcs_status juqcs_branch_bytes(int n, const juqcs_gate* gates, size_
   if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, host_io != 0, true, J.get()))
     return rc;
   *min_bytes = branch_layout(*J, J->m).total;
-  *bytes = branch_layout(*J, group_bits(J->m, group_size)).total;
+  const BranchLayout lay = branch_layout(*J, group_bits(J->m, group_size));
+  *bytes = std::max(lay.total, lay.il_total);
   return JUQCS_OK;
 }
 

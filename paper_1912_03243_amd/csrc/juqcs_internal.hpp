@@ -342,32 +342,40 @@ hipError_t launch_batch_norms(const char* states, const uint64_t* state_off, con
 constexpr int kBranchMaxParts = 8;    // parts of a decomposition
 constexpr int kBranchMaxQubits = 240; // kBranchMaxParts parts of at most 30 qubits
 constexpr int kBranchMaxWords = 4;    // 64-bit words per bitstring
-// Bitstring split table (int32 entries): [0, P] part starts into the qubit
-// lists, then kBranchMaxQubits qubit numbers (part by part, ascending), then
-// the physical bit of each in its part state.
-constexpr int kBranchTabInts = kBranchMaxParts + 1 + 2 * kBranchMaxQubits;
+// Bitstring split table (int32 entries): [0, P] part starts into the runs,
+// then the runs: qubits q, q + 1, .. q + len - 1 of one bitstring word on bits
+// d, d + 1, .. of the part's index (q | d << 8 | (len - 1) << 16).
+constexpr int kBranchTabInts = kBranchMaxParts + 1 + kBranchMaxQubits;
 // Sets *bad (device int) when a bitstring has a bit at or above n.
 hipError_t launch_branch_split(const uint64_t* z, int words, long long count, int P, int n,
                                const int32_t* tab, uint32_t* zp, int* bad, hipStream_t s);
+// The leaves of each part: first[p] .. first[p + 1], and where a sum reads
+// interleaved states, log2 of how many of them (0: the state as it lies) and
+// the byte offset of their interleaved amplitudes.
+struct BranchLeaves {
+  int32_t first[kBranchMaxParts + 1];
+  int32_t shift[kBranchMaxParts];
+  uint64_t base[kBranchMaxParts];
+};
+// Amplitude z of the 2^r states (r >= 1) at state_off[0 .. 2^r) goes to dst[z 2^r + i].
+hipError_t launch_branch_interleave(const char* states, const uint64_t* state_off, int r, int nloc, void* dst,
+                                    hipStream_t s);
 // acc[k] += sum over the group's g branches (in order) of prod_p
-// psi_{tab[j P + p]}[zp[p count + k]] (FP64); the last group multiplies by
-// scale.  States are read where they lie.
+// psi_{tab[j P + p]}[zp[p count + k]] (FP64); the first group starts from
+// zero and the last one multiplies by scale.
 hipError_t launch_branch_gather_accum(const char* states, const uint64_t* state_off, int P,
-                                      long long g, const int32_t* tab, const uint32_t* zp,
-                                      long long count, double* acc, bool last, double scale,
-                                      hipStream_t s);
+                                      const BranchLeaves& leaves, bool interleaved, long long g,
+                                      const int32_t* tab, const uint32_t* zp, long long count, double* acc,
+                                      bool first, bool last, double scale, hipStream_t s);
 // The same sum when the group has at most kBranchSumValues states, stored
 // part by part (part p: circuits first[p] .. first[p + 1]): every thread
 // gathers its coefficient's amplitude of each state into LDS once, then sums
 // the branches from there; byte p of tab8[j] is branch j's circuit of part p.
 constexpr int kBranchSumValues = 48;
 constexpr int kBranchSumThreads = 128;
-struct BranchParts {
-  int32_t first[kBranchMaxParts + 1];
-};
 hipError_t launch_branch_sum_lds(const char* states, const uint64_t* state_off, int P,
-                                 const BranchParts& parts, long long g, const uint64_t* tab8,
-                                 const uint32_t* zp, long long count, double* acc, bool last,
+                                 const BranchLeaves& leaves, bool interleaved, long long g, const uint64_t* tab8,
+                                 const uint32_t* zp, long long count, double* acc, bool first, bool last,
                                  double scale, hipStream_t s);
 
 // ---------------------------------------------------------------------------

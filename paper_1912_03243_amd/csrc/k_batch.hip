@@ -267,8 +267,8 @@ __global__ __launch_bounds__(kThreads) void k_batch_gather(const char* __restric
 // are read once, so a circuit's time is its bytes over what one CU can draw,
 // which takes many 16-byte loads in flight (sixteen waves, four per thread).
 // A grid over slices of a state would need a buffer for their sums.  301
-// circuits of 12 to 21 qubits: 0.47 ms; 3.45 ms with 256
-// threads and 8-byte loads.
+// circuits of 12 to 21 qubits: 0.47 ms; 3.45 ms with 256 threads and 8-byte
+// loads.
 constexpr int kNormThreads = 1024;
 
 __global__ __launch_bounds__(kNormThreads) void k_batch_norms(const char* __restrict__ states,
@@ -307,7 +307,10 @@ __global__ __launch_bounds__(kNormThreads) void k_batch_norms(const char* __rest
 }
 
 // Per-part bitstrings z_p of Eq. (3), each mapped through its part state's
-// layout: zp[p count + k] (one thread per bitstring).
+// layout: zp[p count + k] (one thread per bitstring).  The layout comes as
+// runs of bits that stay together (one or two a part where no qubit moved):
+// bit by bit, 128 qubits in eight parts took 0.65 ms for 2^24 bitstrings,
+// four times what reading and writing them takes.
 // A bitstring with a bit at or above n sets *bad.
 __global__ __launch_bounds__(kThreads) void k_branch_split(const uint64_t* __restrict__ z, int words,
                                                            long long count, int P, int n,
@@ -325,63 +328,184 @@ __global__ __launch_bounds__(kThreads) void k_branch_split(const uint64_t* __res
     over |= lo >= 64 ? 0 : lo <= 0 ? w[i] : w[i] >> lo;
   }
   if (over) atomicOr(bad, 1);
-  const int32_t* qs = tab + kBranchMaxParts + 1;
-  const int32_t* phys = qs + kBranchMaxQubits;
+  const int32_t* runs = tab + kBranchMaxParts + 1;
   for (int p = 0; p < P; ++p) {
     uint32_t v = 0;
     for (int i = tab[p]; i < tab[p + 1]; ++i) {
-      const int q = qs[i], wi = q >> 6;  // wave-uniform
+      const uint32_t r = (uint32_t)runs[i];  // wave-uniform
+      const uint32_t q = r & 0xff, wi = q >> 6;
       const uint64_t x = wi == 0 ? w[0] : wi == 1 ? w[1] : wi == 2 ? w[2] : w[3];
-      v |= (uint32_t)((x >> (q & 63)) & 1) << phys[i];
+      v |= ((uint32_t)(x >> (q & 63)) & ((2u << (r >> 16)) - 1)) << ((r >> 8) & 0xff);
     }
     zp[(size_t)p * count + k] = v;
   }
 }
 
-// Eq. (3) over one group of g branches, one thread per bitstring: the
-// product over parts in FP64 (p = 0..P-1), added to acc for j = 0..g-1 in
-// order, so the sum over all groups runs in one order whatever the group
-// size.  tab[j P + p] is the state holding part p of branch j (wave-uniform
-// loads).
-__global__ __launch_bounds__(kThreads) void k_branch_gather_accum(
-    const char* __restrict__ states, const uint64_t* __restrict__ state_off, int P, long long g,
-    const int32_t* __restrict__ tab, const uint32_t* __restrict__ zp, long long count,
-    double* __restrict__ acc, int last, double scale) {
-  const long long k = (long long)blockIdx.x * kThreads + threadIdx.x;
-  if (k >= count) return;
-  uint32_t zi[kBranchMaxParts];
+// One factor of Eq. (3) onto a product, with its roundings fixed: both sum
+// kernels give the same bits.
+__device__ __forceinline__ void branch_factor(double& re, double& im, const cplx<float>& b) {
+  const double br = b.re, bi = b.im;
+  const double x = __builtin_fma(re, br, -(im * bi));
+  im = __builtin_fma(re, bi, im * br);
+  re = x;
+}
+
+// Eq. (3) over one group of g branches (a multiple of B), one bitstring per
+// thread: the product over parts in FP64 (p = 0..P-1), added to (re, im) for
+// j = 0..g-1 in order, so the sum over all groups runs in one order whatever
+// the group size.  first_diff(a, b): the first part whose states differ in
+// branches a and b; at(j, p): the amplitude of branch j's part p.
+//
+// B branches in a row share what their parts share: the first of them are
+// multiplied once, the next ones (which change with the block's first
+// crossing only) for two branches, then for four, the rest for all.  The B
+// products run side by side, so that a wave has B independent loads and
+// chains in flight, in loops of straight code.  Branch by branch, with the
+// prefix products of all parts kept, a step was one load and one chain long
+// and its joins copied the prefixes: 5.6 ms for 2^24 coefficients of 128
+// branches over eight parts, now about 2.4 ms, FP64 and conversions.
+//
+// SHARE = false shares only the parts before the first change and runs all B
+// products from there: where the values come from memory, more loads in
+// flight are worth more than fewer loads (8 crossings, 2^20 coefficients,
+// 21-qubit halves: 3.3 ms against 4.1).
+template <int B, bool SHARE, typename Diff, typename At>
+__device__ __forceinline__ void branch_sum(int P, long long g, Diff first_diff, At at, double& re, double& im) {
+  for (long long j = 0; j < g; j += B) {
+    double cr[B], ci[B];
+    const auto start = [&](int i0, int step) {  // part 0 of branches j + i0, j + i0 + step, ..
 #pragma unroll
-  for (int p = 0; p < kBranchMaxParts; ++p) zi[p] = p < P ? zp[(size_t)p * count + k] : 0u;
-  double re = acc[2 * k], im = acc[2 * k + 1];
-  // prefix products over the parts, recomputed from the first part whose
-  // state differs from the previous branch's (as in k_branch_sum_lds)
-  double pr[kBranchMaxParts], pi[kBranchMaxParts];
-  for (long long j = 0; j < g; ++j) {
-    const int32_t* t = tab + j * P;
-    int p0 = 0;
-    if (j > 0)
-      while (p0 < P && t[p0] == t[p0 - P]) ++p0;  // wave-uniform
+      for (int i = i0; i < B; i += step) {
+        const cplx<float> b = at(j + i, 0);
+        cr[i] = b.re;
+        ci[i] = b.im;
+      }
+    };
+    if constexpr (!SHARE) {
+      int c0 = P;
 #pragma unroll
-    for (int p = 0; p < kBranchMaxParts; ++p) {
-      if (p < p0) continue;
-      if (p < P) {
-        const cplx<float> b = reinterpret_cast<const cplx<float>*>(states + state_off[t[p]])[zi[p]];
-        if (p == 0) {
-          pr[0] = b.re;
-          pi[0] = b.im;
-        } else {
-          const double br = b.re, bi = b.im;
-          pr[p] = pr[p - 1] * br - pi[p - 1] * bi;
-          pi[p] = pr[p - 1] * bi + pi[p - 1] * br;
+      for (int i = 1; i < B; i *= 2) c0 = min(c0, first_diff(j + i, j));
+      int p = 1;
+      if (c0 > 0) {
+        start(0, B);
+#pragma unroll 1
+        for (; p < c0; ++p) branch_factor(cr[0], ci[0], at(j, p));
+#pragma unroll
+        for (int i = 1; i < B; ++i) {
+          cr[i] = cr[0];
+          ci[i] = ci[0];
         }
       } else {
-        pr[p] = pr[p - 1];
-        pi[p] = pi[p - 1];
+        start(0, 1);
+      }
+#pragma unroll 1
+      for (; p < P; ++p) {
+        cplx<float> b[B];
+#pragma unroll
+        for (int i = 0; i < B; ++i) b[i] = at(j + i, p);
+#pragma unroll
+        for (int i = 0; i < B; ++i) branch_factor(cr[i], ci[i], b[i]);
+      }
+#pragma unroll
+      for (int i = 0; i < B; ++i) {
+        re += cr[i];
+        im += ci[i];
+      }
+      continue;
+    }
+    int p = 1;
+    start(0, B);
+    // N = 1, 2, 4, ..: N products (of branches j + i B / N) up to the first
+    // part that tells apart the branches each of them stands for
+    int same[4];  // same[l]: the first part that changes within B >> l branches
+    same[3] = P;
+#pragma unroll
+    for (int l = 2; l >= 0; --l) same[l] = B >> l > 1 ? min(same[l + 1], first_diff(j + (B >> (l + 1)), j)) : P;
+#pragma unroll
+    for (int l = 0; B >> l > 0; ++l) {
+      constexpr int kMax = B;
+      const int N = 1 << l, step = kMax >> l;
+      if (l > 0) {  // split: the odd ones start from the even ones' product
+#pragma unroll
+        for (int i = N - 1; i >= 0; --i) {
+          cr[i] = cr[i / 2];
+          ci[i] = ci[i / 2];
+        }
+        if (same[l - 1] == 0) {  // part 0 already differs
+#pragma unroll
+          for (int i = 1; i < N; i += 2) {
+            const cplx<float> b = at(j + i * step, 0);
+            cr[i] = b.re;
+            ci[i] = b.im;
+          }
+        }
+      }
+      const int end = step > 1 ? same[l] : P;
+#pragma unroll 1
+      for (; p < end; ++p) {
+        cplx<float> b[B];
+#pragma unroll
+        for (int i = 0; i < N; ++i) b[i] = at(j + i * step, p);
+#pragma unroll
+        for (int i = 0; i < N; ++i) branch_factor(cr[i], ci[i], b[i]);
       }
     }
-    re += pr[kBranchMaxParts - 1];
-    im += pi[kBranchMaxParts - 1];
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+      re += cr[i];
+      im += ci[i];
+    }
   }
+}
+
+// Interleaves the 2^r states of a part that a sum reads (state_off[0], ..):
+// amplitude z of state i at dst[z 2^r + i], one z per thread.
+__global__ __launch_bounds__(kThreads) void k_branch_interleave(const char* __restrict__ states,
+                                                                const uint64_t* __restrict__ state_off, int r,
+                                                                uint32_t count, cplx<float>* __restrict__ dst) {
+  typedef float v2 __attribute__((ext_vector_type(2)));
+  typedef float v4 __attribute__((ext_vector_type(4)));
+  const uint32_t z = blockIdx.x * kThreads + threadIdx.x;
+  if (z >= count) return;
+  v4* row = reinterpret_cast<v4*>(dst + ((size_t)z << r));
+  const auto at = [&](int i) { return reinterpret_cast<const v2*>(states + state_off[i])[z]; };
+  for (int i = 0; i < 1 << r; i += 2) {  // r >= 1
+    const v2 a = at(i), b = at(i + 1);
+    row[i >> 1] = v4{a.x, a.y, b.x, b.y};
+  }
+}
+
+// The sum with the states read where they lie, or (IL) interleaved as
+// leaves.base and .shift tell; tab[j P + p] is the state holding part p of
+// branch j (wave-uniform loads).  A bitstring's amplitudes lie in different
+// lines of different states, so every value costs a line (128 bytes for 8);
+// interleaved, the amplitudes that one bitstring reads of a part share a line.
+template <int B, bool IL>
+__global__ __launch_bounds__(kThreads) void k_branch_gather_accum(
+    const char* __restrict__ states, const uint64_t* __restrict__ state_off, int P, BranchLeaves leaves,
+    long long g, const int32_t* __restrict__ tab, const uint32_t* __restrict__ zp, long long count,
+    double* __restrict__ acc, int first, int last, double scale) {
+  const long long k = (long long)blockIdx.x * kThreads + threadIdx.x;
+  if (k >= count) return;
+  double re = first ? 0.0 : acc[2 * k], im = first ? 0.0 : acc[2 * k + 1];
+  branch_sum<B, false>(
+      P, g,
+      [&](long long a, long long b) {
+        int p = 0;
+        while (p < P && tab[a * P + p] == tab[b * P + p]) ++p;  // wave-uniform
+        return p;
+      },
+      [&](long long j, int p) {
+        const uint32_t z = zp[(size_t)p * count + k];
+        const int c = tab[j * P + p];
+        if (IL && leaves.shift[p] > 0) {
+          const int r = leaves.shift[p];
+          return reinterpret_cast<const cplx<float>*>(states + leaves.base[p])[((size_t)z << r) +
+                                                                              ((c - leaves.first[p]) & ((1 << r) - 1))];
+        }
+        return reinterpret_cast<const cplx<float>*>(states + state_off[c])[z];
+      },
+      re, im);
   if (last) {
     re *= scale;
     im *= scale;
@@ -395,58 +519,56 @@ __global__ __launch_bounds__(kThreads) void k_branch_gather_accum(
 // own LDS column (conflict-free: value c of thread t at c * threads + t),
 // then runs the branches from there.  Threads share nothing, so there is no
 // barrier.  Same arithmetic, in the same order, as k_branch_gather_accum.
+template <int B, bool IL>
 __global__ __launch_bounds__(kBranchSumThreads) void k_branch_sum_lds(
-    const char* __restrict__ states, const uint64_t* __restrict__ state_off, int P, BranchParts bp,
+    const char* __restrict__ states, const uint64_t* __restrict__ state_off, int P, BranchLeaves leaves,
     long long g, const uint64_t* __restrict__ tab8, const uint32_t* __restrict__ zp, long long count,
-    double* __restrict__ acc, int last, double scale) {
+    double* __restrict__ acc, int first, int last, double scale) {
+  typedef float v4 __attribute__((ext_vector_type(4)));
   extern __shared__ cplx<float> vals[];
   const int tid = threadIdx.x;
   const long long k = (long long)blockIdx.x * kBranchSumThreads + tid;
   if (k >= count) return;
-#pragma unroll
-  for (int p = 0; p < kBranchMaxParts; ++p) {
-    if (p < P) {
-      const uint32_t zi = zp[(size_t)p * count + k];
-      for (int c = bp.first[p]; c < bp.first[p + 1]; ++c)
-        vals[c * kBranchSumThreads + tid] = reinterpret_cast<const cplx<float>*>(states + state_off[c])[zi];
-    }
-  }
-  double re = acc[2 * k], im = acc[2 * k + 1];
-  // Prefix products over the parts, kept from branch to branch: branch j
-  // recomputes them only from the first part whose state differs from
-  // branch j-1's (a wave-uniform test on the table words), so parts whose
-  // crossings come early are multiplied once per run of branches.  The
-  // products are the same values, in the same order, as in
-  // k_branch_gather_accum.  Entries past the last part repeat the full
-  // product, so it is always pr[kBranchMaxParts - 1].
-  double pr[kBranchMaxParts], pi[kBranchMaxParts];
-  uint64_t prev = 0;
-  for (long long j = 0; j < g; ++j) {
-    const uint64_t t = tab8[j];
-    const uint64_t diff = t ^ prev;
-    const int p0 = j == 0 ? 0 : diff ? __builtin_ctzll(diff) >> 3 : kBranchMaxParts;
-    prev = t;
-#pragma unroll
-    for (int p = 0; p < kBranchMaxParts; ++p) {
-      if (p < p0) continue;
-      if (p < P) {
-        const cplx<float> b = vals[(int)((t >> (8 * p)) & 0xff) * kBranchSumThreads + tid];
-        if (p == 0) {
-          pr[0] = b.re;
-          pi[0] = b.im;
-        } else {
-          const double br = b.re, bi = b.im;
-          pr[p] = pr[p - 1] * br - pi[p - 1] * bi;
-          pi[p] = pr[p - 1] * bi + pi[p - 1] * br;
-        }
-      } else {
-        pr[p] = pr[p - 1];
-        pi[p] = pi[p - 1];
+  for (int p = 0; p < P; ++p) {
+    const uint32_t zi = zp[(size_t)p * count + k];
+    cplx<float>* col = vals + tid;
+    int c = leaves.first[p];
+    const int end = leaves.first[p + 1];
+    if (IL && leaves.shift[p] > 0) {  // the part's states: an even number of amplitudes in a row
+      const v4* row = reinterpret_cast<const v4*>(states + leaves.base[p] + ((size_t)zi << (leaves.shift[p] + 3)));
+      const auto put = [&](const v4& v) {
+        col[c * kBranchSumThreads] = {v.x, v.y};
+        col[(c + 1) * kBranchSumThreads] = {v.z, v.w};
+        c += 2;
+        ++row;
+      };
+      for (; c + 4 <= end;) {
+        const v4 a = row[0], b = row[1];
+        put(a);
+        put(b);
       }
+      for (; c < end;) put(row[0]);
+      continue;
     }
-    re += pr[kBranchMaxParts - 1];
-    im += pi[kBranchMaxParts - 1];
+    const auto at = [&](int i) { return reinterpret_cast<const cplx<float>*>(states + state_off[i])[zi]; };
+    for (; c + 4 <= end; c += 4) {  // four loads in flight
+      cplx<float> v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = at(c + i);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) col[(c + i) * kBranchSumThreads] = v[i];
+    }
+    for (; c < end; ++c) col[c * kBranchSumThreads] = at(c);
   }
+  double re = first ? 0.0 : acc[2 * k], im = first ? 0.0 : acc[2 * k + 1];
+  branch_sum<B, true>(
+      P, g,
+      [&](long long a, long long b) {
+        const uint64_t diff = tab8[a] ^ tab8[b];
+        return diff ? (int)(__builtin_ctzll(diff) >> 3) : kBranchMaxParts;
+      },
+      [&](long long j, int p) { return vals[(int)((tab8[j] >> (8 * p)) & 0xff) * kBranchSumThreads + tid]; }, re,
+      im);
   if (last) {
     re *= scale;
     im *= scale;
@@ -521,32 +643,49 @@ hipError_t launch_branch_split(const uint64_t* z, int words, long long count, in
   return hipGetLastError();
 }
 
+hipError_t launch_branch_interleave(const char* states, const uint64_t* state_off, int r, int nloc, void* dst,
+                                    hipStream_t s) {
+  if (r < 1 || nloc < 1 || nloc > 30) return hipErrorInvalidValue;
+  const uint32_t count = 1u << nloc;
+  hipLaunchKernelGGL(k_branch_interleave, dim3((count + kThreads - 1) / kThreads), dim3(kThreads), 0, s, states,
+                     state_off, r, count, (cplx<float>*)dst);
+  return hipGetLastError();
+}
+
 hipError_t launch_branch_gather_accum(const char* states, const uint64_t* state_off, int P,
-                                      long long g, const int32_t* tab, const uint32_t* zp,
-                                      long long count, double* acc, bool last, double scale,
-                                      hipStream_t s) {
+                                      const BranchLeaves& leaves, bool interleaved, long long g,
+                                      const int32_t* tab, const uint32_t* zp, long long count, double* acc,
+                                      bool first, bool last, double scale, hipStream_t s) {
   if (count == 0) return hipSuccess;
   if (P < 1 || P > kBranchMaxParts || g < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_branch_gather_accum, dim3((unsigned)((count + kThreads - 1) / kThreads)),
-                     dim3(kThreads), 0, s, states, state_off, P, g, tab, zp, count, acc, last ? 1 : 0,
-                     scale);
+  const auto kern =
+      interleaved ? (g % 8 == 0 ? k_branch_gather_accum<8, true> : g % 4 == 0 ? k_branch_gather_accum<4, true>
+                                                                              : k_branch_gather_accum<1, true>)
+                  : (g % 8 == 0 ? k_branch_gather_accum<8, false> : g % 4 == 0 ? k_branch_gather_accum<4, false>
+                                                                               : k_branch_gather_accum<1, false>);
+  hipLaunchKernelGGL(kern, dim3((unsigned)((count + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, states,
+                     state_off, P, leaves, g, tab, zp, count, acc, first ? 1 : 0, last ? 1 : 0, scale);
   return hipGetLastError();
 }
 
 hipError_t launch_branch_sum_lds(const char* states, const uint64_t* state_off, int P,
-                                 const BranchParts& parts, long long g, const uint64_t* tab8,
-                                 const uint32_t* zp, long long count, double* acc, bool last,
+                                 const BranchLeaves& leaves, bool interleaved, long long g, const uint64_t* tab8,
+                                 const uint32_t* zp, long long count, double* acc, bool first, bool last,
                                  double scale, hipStream_t s) {
   if (count == 0) return hipSuccess;
   if (P < 1 || P > kBranchMaxParts || g < 1) return hipErrorInvalidValue;
-  const int values = parts.first[P];
-  if (values < 1 || values > kBranchSumValues || parts.first[0] != 0) return hipErrorInvalidValue;
+  const int values = leaves.first[P];
+  if (values < 1 || values > kBranchSumValues || leaves.first[0] != 0) return hipErrorInvalidValue;
   for (int p = 0; p < P; ++p)
-    if (parts.first[p + 1] < parts.first[p]) return hipErrorInvalidValue;
+    if (leaves.first[p + 1] < leaves.first[p]) return hipErrorInvalidValue;
   const size_t lds = (size_t)values * kBranchSumThreads * sizeof(cplx<float>);
-  hipLaunchKernelGGL(k_branch_sum_lds, dim3((unsigned)((count + kBranchSumThreads - 1) / kBranchSumThreads)),
-                     dim3(kBranchSumThreads), lds, s, states, state_off, P, parts, g, tab8, zp, count, acc,
-                     last ? 1 : 0, scale);
+  const auto kern = interleaved ? (g % 8 == 0 ? k_branch_sum_lds<8, true> : g % 4 == 0 ? k_branch_sum_lds<4, true>
+                                                                                       : k_branch_sum_lds<1, true>)
+                                : (g % 8 == 0 ? k_branch_sum_lds<8, false> : g % 4 == 0 ? k_branch_sum_lds<4, false>
+                                                                                        : k_branch_sum_lds<1, false>);
+  hipLaunchKernelGGL(kern, dim3((unsigned)((count + kBranchSumThreads - 1) / kBranchSumThreads)),
+                     dim3(kBranchSumThreads), lds, s, states, state_off, P, leaves, g, tab8, zp, count, acc,
+                     first ? 1 : 0, last ? 1 : 0, scale);
   return hipGetLastError();
 }
 
