@@ -1149,8 +1149,7 @@ juqcs_status juqcs_expectations(juqcs_state* st, double* out) {
   double* res = (double*)(st->work + kResultOff);  // 3 sums per physical bit
   // first pass: the low b bits; then L contiguous bits plus up to b - L
   // gathered bits not covered yet per pass
-  const int b = std::min(n, expect_max_bits());
-  const int L = st->dt == JUQCS_C128 ? 5 : st->dt == JUQCS_C64 ? 6 : st->B;
+  const int b = std::min(n, expect_max_bits(st->dt, n, st->B)), L = expect_low_bits(st->dt, n, st->B);
   TileGeom g{};
   g.n = n;
   g.block_bits = st->B;

@@ -260,9 +260,11 @@ hipError_t launch_tile(juqcs_dtype dt, void* amps, void* scales,
 bool tile_pipelined(juqcs_dtype dt, const TileGeom& g, int nops);
 int tile_max_bits(juqcs_dtype dt);
 // Expectation values of sigma^x,y,z for the tile bits jlo..b-1 of geometry
-// g (b <= expect_max_bits(), at most 16 bits per launch):
+// g (b <= expect_max_bits, at most 16 bits per launch):
 // out3[3 (j - jlo) + c].  partials: expect_partials_bytes() of device memory.
-int expect_max_bits();
+int expect_max_bits(juqcs_dtype dt, int n, int block_bits);
+// least contiguous bits of its passes after the first
+int expect_low_bits(juqcs_dtype dt, int n, int block_bits);
 size_t expect_partials_bytes();
 hipError_t launch_expect(juqcs_dtype dt, const void* amps, const void* scales, const TileGeom& g,
                          int jlo, double* partials, double* out3, hipStream_t s);

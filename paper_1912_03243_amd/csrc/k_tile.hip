@@ -605,18 +605,265 @@ __global__ __launch_bounds__(kExpectThreads) void k_expect(const void* __restric
   }
 }
 
-// out3[3 k + c]: bit jlo + k, summed over the waves of its group (in wave
-// order) and over blocks, in that order.
-__global__ __launch_bounds__(64) void k_expect_final(const double* __restrict__ partials, int nblk,
-                                                     int nbits, double* __restrict__ out3) {
-  const int k = threadIdx.x / 3, c = threadIdx.x % 3;
-  if (k >= nbits) return;
-  const int ng = expect_groups(nbits), shares = expect_shares(ng);
-  const int grp = k / kExpectGroup, jj = k % kExpectGroup;
+// Two-byte amplitudes of one scale are integers times that scale, so their
+// pair sums are exact in integers: four products of codes a dot instruction
+// (two amplitudes), one FP64 multiplication with the two scales per sum of a
+// scale pair.  A tile is 2^15 amplitudes of raw codes (64 KiB of LDS, two
+// workgroups a CU), so that 2^33 amplitudes take three passes instead of the
+// five of decoded 2^13-amplitude tiles.  2^33 amplitudes: 26 ms for all 33
+// bits, 7.9 to 9.7 ms a pass (dot instructions and LDS reads; reading alone is
+// 3.3 ms); decoded 93 ms, 18.6 ms a pass, FP64 and conversions.
+// Bits 0-2 lie inside a 16-byte vector of 8 amplitudes: every thread reduces
+// them on the vectors it has loaded.  The others form groups of three as in
+// k_expect, taken by the waves in turn: a lane reduces four items of 2^gk
+// vectors at a time, whose scales are those of the first one unless all bits
+// of the group lie within a scale block or chunk (then an item has one scale).
+// Needs scale blocks and chunks of at least 2^6 amplitudes.
+constexpr int kExpect2Bits = 15;
+constexpr int kExpect2Low = 6;  // least log2 of scale blocks and chunks
+constexpr int kExpect2Gather = kExpect2Bits - kExpect2Low;
+constexpr int kExpect2Threads = 512;
+constexpr int kExpect2Waves = kExpect2Threads / 64;
+
+__device__ __forceinline__ int dot4(int a, int b, int c) { return __builtin_amdgcn_sdot4(a, b, c, false); }
+// (im, ~re) of both amplitudes of a dword: ~re = -re - 1, so dot4(a, turned(b))
+// is Im(conj(a) b) less the sum of a's imaginary codes, dot4(a, kImag)
+__device__ __forceinline__ int turned(int x) {
+  return (int)(__builtin_amdgcn_perm((uint32_t)x, (uint32_t)x, 0x02030001u) ^ 0xff00ff00u);
+}
+constexpr int kImag = 0x01000100;
+__device__ __forceinline__ int expect2_slot(int v) { return v ^ (((v >> 3) ^ (v >> 6) ^ (v >> 9)) & 7); }
+
+struct Expect2Sums {
+  double x[3] = {0.0, 0.0, 0.0}, y[3] = {0.0, 0.0, 0.0}, z[3] = {0.0, 0.0, 0.0};
+};
+
+// Bits 0..2 of a vector whose scale squared is f2.
+__device__ __forceinline__ void expect2_vector(const v4i& w, double f2, Expect2Sums* s) {
+  int x[3] = {0, 0, 0}, y[3] = {0, 0, 0}, z[3] = {0, 0, 0};
+  const auto pair = [&](int j, int a, int b) {
+    x[j] = dot4(a, b, x[j]);
+    y[j] = dot4(a, turned(b), y[j]);
+    y[j] = dot4(a, kImag, y[j]);
+    z[j] = dot4(a, a, z[j]) - dot4(b, b, 0);
+  };
+  const int d[4] = {w.x, w.y, w.z, w.w};
+  pair(2, d[0], d[2]);
+  pair(2, d[1], d[3]);
+  pair(1, d[0], d[1]);
+  pair(1, d[2], d[3]);
+#pragma unroll
+  for (int k = 0; k < 4; k += 2)  // the low and the high halves of two dwords
+    pair(0, (int)__builtin_amdgcn_perm((uint32_t)d[k + 1], (uint32_t)d[k], 0x05040100u),
+         (int)__builtin_amdgcn_perm((uint32_t)d[k + 1], (uint32_t)d[k], 0x07060302u));
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    s->x[j] = fma(f2, (double)x[j], s->x[j]);
+    s->y[j] = fma(f2, (double)y[j], s->y[j]);
+    s->z[j] = fma(f2, (double)z[j], s->z[j]);
+  }
+}
+
+// Four items of 2^GK vectors each (base[i] their first slots, row[r] the
+// slots of the group's settings); f[r]: scales, all the same if ONE.
+template <int GK, bool ONE, typename Base, typename Scale>
+__device__ __forceinline__ void expect2_items(const v4i* sh, Base base, const int* row, Scale scale,
+                                              Expect2Sums* s) {
+  constexpr int R = 1 << GK, Q = ONE ? GK : GK * R / 2;  // sums: a bit's pairs together if ONE
+  int x[Q], y[Q], nrm[R];
+#pragma unroll 1
+  for (int i = 0; i < 4; ++i) {
+    if (ONE || i == 0) {
+#pragma unroll
+      for (int q = 0; q < Q; ++q) x[q] = y[q] = 0;
+#pragma unroll
+      for (int r = 0; r < R; ++r) nrm[r] = 0;
+    }
+    const int u = base(i);
+    v4i v[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[r] = sh[u ^ row[r]];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      int t[R], im[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        t[r] = turned(v[r][k]);
+        im[r] = dot4(v[r][k], kImag, 0);
+        nrm[r] = dot4(v[r][k], v[r][k], nrm[r]);
+      }
+      int q = 0;
+#pragma unroll
+      for (int j = 0; j < GK; ++j)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          if ((r >> j) & 1) continue;
+          const int at = ONE ? j : q++;
+          x[at] = dot4(v[r][k], v[r | 1 << j][k], x[at]);
+          y[at] = dot4(v[r][k], t[r | 1 << j], y[at]) + im[r];
+        }
+      __builtin_amdgcn_sched_barrier(0);  // a dword's turned codes at a time (or they spill)
+    }
+    if (ONE) {
+      const double f = scale(i, 0), f2 = f * f;
+#pragma unroll
+      for (int j = 0; j < GK; ++j) {
+        int z = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) z += (r >> j) & 1 ? -nrm[r] : nrm[r];
+        s->x[j] = fma(f2, (double)x[j], s->x[j]);
+        s->y[j] = fma(f2, (double)y[j], s->y[j]);
+        s->z[j] = fma(f2, (double)z, s->z[j]);
+      }
+    }
+  }
+  if (!ONE) {
+    double f[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) f[r] = scale(0, r);
+    int q = 0;
+#pragma unroll
+    for (int j = 0; j < GK; ++j)
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if ((r >> j) & 1) continue;
+        const double ff = f[r] * f[r | 1 << j];
+        s->x[j] = fma(ff, (double)x[q], s->x[j]);
+        s->y[j] = fma(ff, (double)y[q], s->y[j]);
+        s->z[j] = fma(f[r] * f[r], (double)nrm[r], s->z[j]);
+        s->z[j] = fma(-(f[r | 1 << j] * f[r | 1 << j]), (double)nrm[r | 1 << j], s->z[j]);
+        ++q;
+      }
+  }
+}
+
+// FIRST: the pass over contiguous tiles, which covers bits 0 .. 14.
+template <bool FIRST>
+__global__ __launch_bounds__(kExpect2Threads, 4) void k_expect_enc2(const int8_t* __restrict__ codes,
+                                                                    const float* __restrict__ scales, TileGeom g,
+                                                                    int jlo, double* __restrict__ partials) {
+  constexpr int NV = 1 << (kExpect2Bits - 3), PER = NV / kExpect2Threads;
+  __shared__ v4i sh[NV];
+  __shared__ float sc[1 << (kExpect2Bits - kExpect2Low)];
+  __shared__ GeomLdsT<kExpect2Gather> gs;
+  load_geom<kExpect2Threads>(g, gs);
+  const int L = g.L, lmask = (1 << L) - 1, B = g.block_bits, sg = L < B ? L : B;
+  const uint64_t ntiles = uint64_t(1) << (g.n - kExpect2Bits);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int glo = FIRST ? 3 : jlo;  // first bit of the groups
+  const int ng = expect_groups(kExpect2Bits - glo), shares = kExpect2Waves / ng;
+  const int grp = wave % ng, share = wave / ng;
+  const int j0 = glo + kExpectGroup * grp, vb = j0 - 3;
+  const int gk = j0 + kExpectGroup <= kExpect2Bits ? kExpectGroup : kExpect2Bits - j0;
+  int row[1 << kExpectGroup];
+#pragma unroll
+  for (int r = 0; r < (1 << kExpectGroup); ++r) row[r] = expect2_slot((r & ((1 << gk) - 1)) << vb);
+  Expect2Sums low, up;
+  uint64_t tau, tau_end;
+  tile_run(ntiles, &tau, &tau_end);
+  for (; tau < tau_end; ++tau) {
+    int tid = (int)threadIdx.x;  // opaque: addresses kept over the tiles would spill
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63;
+    const uint64_t tb = tile_base(tau, L, g.H, gs.hb);
+    const auto at = [&](int e) { return tb + gs.choff[e >> L] + (e & lmask); };
+    v4i v[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      v[k] = ld_stream(reinterpret_cast<const v4i*>(codes + 2 * at((k * kExpect2Threads + tid) << 3)));
+    for (int i = tid; i < 1 << (kExpect2Bits - sg); i += kExpect2Threads)
+      sc[i] = ld_stream(&scales[at(i << sg) >> B]) / 127.0f;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) sh[expect2_slot(k * kExpect2Threads + tid)] = v[k];
+    __syncthreads();
+    if (FIRST) {
+#pragma unroll 1
+      for (int k = 0; k < PER; ++k) {
+        const int q = k * kExpect2Threads + tid;
+        const double f = sc[(q << 3) >> sg];
+        expect2_vector(sh[expect2_slot(q)], f * f, &low);
+      }
+    }
+    if (share < shares) {
+      for (int qd = share * 64 + lane; qd < NV >> (gk + 2); qd += 64 * shares) {
+        // vector index of item i of the quad, with the group's bits clear
+        const auto first = [&](int i) {
+          const int x = qd << 2 | i;
+          return ((x >> vb) << (vb + gk)) | (x & ((1 << vb) - 1));
+        };
+        const auto base = [&](int i) { return expect2_slot(first(i)); };
+        const auto scale = [&](int i, int r) { return (double)sc[((first(i) | r << vb) << 3) >> sg]; };
+        if constexpr (FIRST) {
+          if (j0 + gk <= sg) expect2_items<3, true>(sh, base, row, scale, &up);
+          else expect2_items<3, false>(sh, base, row, scale, &up);
+        } else {
+          if (gk == 3) expect2_items<3, false>(sh, base, row, scale, &up);
+          else if (gk == 2) expect2_items<2, false>(sh, base, row, scale, &up);
+          else expect2_items<1, false>(sh, base, row, scale, &up);
+        }
+      }
+    }
+    __syncthreads();
+  }
+  // per wave, then over the waves of a bit in order: sums of (bit, component)
+  double* red = reinterpret_cast<double*>(sh);
+  const auto put = [&](const Expect2Sums& s, int slot) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      double x = s.x[j], y = s.y[j], z = s.z[j];
+      for (int off = 32; off > 0; off >>= 1) {
+        x += __shfl_xor(x, off, 64);
+        y += __shfl_xor(y, off, 64);
+        z += __shfl_xor(z, off, 64);
+      }
+      if (lane == 0) {
+        red[(slot * 3 + j) * 3] = 2.0 * x;
+        red[(slot * 3 + j) * 3 + 1] = 2.0 * y;
+        red[(slot * 3 + j) * 3 + 2] = z;
+      }
+    }
+  };
+  if (FIRST) put(low, wave);
+  put(up, kExpect2Waves + wave);
+  __syncthreads();
+  const int k = tid / 3, c = tid % 3;
+  if (k < kExpect2Bits - jlo) {
+    double r = 0.0;
+    if (FIRST && k < 3) {
+      for (int w = 0; w < kExpect2Waves; ++w) r += red[(w * 3 + k) * 3 + c];
+    } else {
+      const int j = jlo + k - glo;
+      for (int w = j / 3; w < shares * ng; w += ng) r += red[((kExpect2Waves + w) * 3 + j % 3) * 3 + c];
+    }
+    partials[(size_t)tid * gridDim.x + blockIdx.x] = r;
+  }
+}
+
+// out3[3 k + c]: bit jlo + k, one workgroup each: runs of the partial sums in
+// order, then the runs' sums pairwise.  layout of waves: see k_expect
+// (waves > 0); 0: one run of partial sums for each value.
+constexpr int kFinalThreads = 256;
+__global__ __launch_bounds__(kFinalThreads) void k_expect_final(const double* __restrict__ partials, int nblk,
+                                                                int nbits, int waves, double* __restrict__ out3) {
+  __shared__ double sh[kFinalThreads];
+  const int k = blockIdx.x / 3, c = blockIdx.x % 3, tid = threadIdx.x;
   double s = 0.0;
-  for (int w = grp; w < shares * ng; w += ng)
-    for (int i = 0; i < nblk; ++i) s += partials[3 * (((size_t)w * kExpectGroup + jj) * nblk + i) + c];
-  out3[3 * k + c] = s;
+  if (waves) {
+    const int ng = expect_groups(nbits), shares = waves / ng;
+    const int grp = k / kExpectGroup, jj = k % kExpectGroup;
+    for (int w = grp; w < shares * ng; w += ng)
+      for (int i = tid; i < nblk; i += kFinalThreads)
+        s += partials[3 * (((size_t)w * kExpectGroup + jj) * nblk + i) + c];
+  } else {
+    for (int i = tid; i < nblk; i += kFinalThreads) s += partials[(size_t)blockIdx.x * nblk + i];
+  }
+  sh[tid] = s;
+  __syncthreads();
+  for (int off = kFinalThreads / 2; off > 0; off >>= 1) {
+    if (tid < off) sh[tid] += sh[tid + off];
+    __syncthreads();
+  }
+  if (tid == 0) out3[blockIdx.x] = sh[0];
 }
 
 inline unsigned tile_grid(uint64_t ntiles) {
@@ -724,7 +971,20 @@ hipError_t launch_tile(juqcs_dtype dt, void* amps, void* scales, const TileGeom&
   return hipGetLastError();
 }
 
-int expect_max_bits() { return kExpectBits; }
+// Two-byte states of some tiles and more, with scale blocks that an integer
+// sum can run over, read raw codes (smaller ones would leave CUs idle).
+bool expect_codes(juqcs_dtype dt, int n, int block_bits) {
+  return dt == JUQCS_ENC2 && block_bits >= kExpect2Low && n >= kExpect2Bits + 9;
+}
+int expect_max_bits(juqcs_dtype dt, int n, int block_bits) {
+  return expect_codes(dt, n, block_bits) ? kExpect2Bits : kExpectBits;
+}
+// Contiguous bits of a pass with gathered ones: 512 bytes of codes or
+// amplitudes; 128 bytes of raw codes, for one gathered bit more (33 qubits:
+// three passes, 137.3 ms with the circuit; 256 bytes, four passes, 139.0 ms).
+int expect_low_bits(juqcs_dtype dt, int n, int block_bits) {
+  return expect_codes(dt, n, block_bits) ? kExpect2Low : dt == JUQCS_C128 ? 5 : dt == JUQCS_C64 ? 6 : block_bits;
+}
 
 size_t expect_partials_bytes() {
   return sizeof(double) * 3 * kExpectWaves * kExpectGroup *
@@ -734,7 +994,21 @@ size_t expect_partials_bytes() {
 hipError_t launch_expect(juqcs_dtype dt, const void* amps, const void* scales, const TileGeom& g,
                          int jlo, double* partials, double* out3, hipStream_t s) {
   const int nbits = g.b - jlo;
-  if (g.b > kExpectBits || nbits < 1 || nbits > kExpectWaves) return hipErrorInvalidValue;
+  if (nbits < 1 || nbits > kExpectWaves) return hipErrorInvalidValue;
+  if (expect_codes(dt, g.n, g.block_bits)) {
+    if (g.b != kExpect2Bits || g.L < kExpect2Low || (jlo == 0 ? g.H != 0 : jlo < g.L))
+      return hipErrorInvalidValue;
+    const auto kern = jlo == 0 ? k_expect_enc2<true> : k_expect_enc2<false>;
+    const uint64_t tiles = uint64_t(1) << (g.n - g.b);
+    uint64_t blocks = std::min(tiles, resident_blocks((const void*)kern, kExpect2Threads));
+    blocks = std::min<uint64_t>(blocks, expect_partials_bytes() / (sizeof(double) * 3 * nbits));
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kExpect2Threads), 0, s, (const int8_t*)amps,
+                       (const float*)scales, g, jlo, partials);
+    hipLaunchKernelGGL(k_expect_final, dim3(3 * nbits), dim3(kFinalThreads), 0, s, partials, (int)blocks, nbits, 0,
+                       out3);
+    return hipGetLastError();
+  }
+  if (g.b > kExpectBits) return hipErrorInvalidValue;
   const uint64_t ntiles = uint64_t(1) << (g.n - g.b);
   const uint64_t slots = resident_blocks((const void*)k_expect<double>, kExpectThreads);
   const unsigned grid = (unsigned)(ntiles < slots ? ntiles : slots);
@@ -745,7 +1019,8 @@ hipError_t launch_expect(juqcs_dtype dt, const void* amps, const void* scales, c
     hipLaunchKernelGGL(k_expect<float>, dim3(grid), block, 0, s, amps, (const float*)scales, g, jlo, partials);
   else
     hipLaunchKernelGGL(k_expect<int8_t>, dim3(grid), block, 0, s, amps, (const float*)scales, g, jlo, partials);
-  hipLaunchKernelGGL(k_expect_final, dim3(1), dim3(64), 0, s, partials, (int)grid, nbits, out3);
+  hipLaunchKernelGGL(k_expect_final, dim3(3 * nbits), dim3(kFinalThreads), 0, s, partials, (int)grid, nbits,
+                     kExpectWaves, out3);
   return hipGetLastError();
 }
 
