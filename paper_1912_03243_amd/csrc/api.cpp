@@ -218,7 +218,7 @@ juqcs_status run_block_plan(juqcs_state* st, const BlkPlan& plan) {
   const BlkDev bd = block_device(lay, dev);
   for (size_t i = 0; i < plan.passes.size(); ++i) {
     prof_begin(st);
-    hipError_t e = launch_block(st->dt, st->amps, plan.passes[i], (const BlkPass*)(dev + lay.o_geoms) + i, bd,
+    hipError_t e = launch_block(st->dt, st->amps, st->scales, plan.passes[i], (const BlkPass*)(dev + lay.o_geoms) + i, bd,
                                 st->stream);
     prof_end(st);
     if (e != hipSuccess) return hip_fail(e, "tile pass launch");
@@ -335,7 +335,10 @@ juqcs_status tile_gates(juqcs_state* st, const std::vector<Gate>& gates, int L, 
   if (plan.gates != (int64_t)gates.size())
     return fail(JUQCS_ERR_UNSUPPORTED, "a gate does not fit any tile of this geometry");
   if (passes) *passes = (int64_t)plan.passes.size();
-  if (juqcs_status rc = run_tile_plan(st, plan)) return rc;
+  BlkPlan bp;
+  const bool codes = block && st->dt == JUQCS_ENC2 && block_codes_sized(st->B, std::min(b, st->n)) &&
+                     block_tile_plan(plan, st->B, &bp);
+  if (juqcs_status rc = codes ? run_block_plan(st, bp) : run_tile_plan(st, plan)) return rc;
   if (rl)
     for (int q = 0; q < st->n; ++q) st->phys[q] = moved[st->phys[q]];
   return JUQCS_OK;

@@ -280,12 +280,13 @@ int score(const std::vector<Local>& gs, const std::vector<int>& rem, uint32_t P)
 }
 
 // Register bits for the next stage: greedily the bit that lets the most
-// through, among the bits of allowed (at least K of them).
+// through, among the bits of allowed (at least K of them), besides those of
+// fixed.
 uint32_t pick_regs(const std::vector<Local>& gs, const std::vector<int>& rem, int tb, int K,
-                   uint32_t allowed, int* got) {
-  uint32_t P = 0;
+                   uint32_t allowed, int* got, uint32_t fixed = 0) {
+  uint32_t P = fixed;
   int best_all = 0;
-  for (int k = 0; k < K; ++k) {
+  for (int k = __builtin_popcount(fixed); k < K; ++k) {
     int best = -1, bs = -1;
     for (int b = 0; b < tb; ++b) {
       if (!((allowed >> b) & 1) || ((P >> b) & 1)) continue;
@@ -774,7 +775,7 @@ constexpr int kSlotBytes = 8;
 }  // namespace
 
 void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, const std::vector<int>& taken,
-                     const std::vector<Gate>& where, bool fp64, int low, BlkPlan* plan) {
+                     const std::vector<Gate>& where, bool fp64, int low, BlkPlan* plan, int codes) {
   const int tb = tg.b, K = kBlkRegs, nthr = tb - K, lanes = std::min(6, nthr), waves = nthr - lanes;
   // tile-local bit of a physical bit, or 64 + its bit in the tile number
   int local_of[64];
@@ -801,11 +802,31 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
   int dest[64];
   for (int b = 0; b < tb; ++b) dest[b] = b;
   for (int i = 0; i < tg.nswap; ++i) std::swap(dest[tg.swap_a[i]], dest[tg.swap_b[i]]);
-  low = std::min(low, lanes);
-  const uint32_t all = (1u << tb) - 1, low_src = (1u << low) - 1;
-  uint32_t low_dst = 0;
-  for (int b = 0; b < tb; ++b)
-    if (dest[b] < low) low_dst |= 1u << b;
+  // (two-byte amplitudes: those above the three of a 16-byte group of codes,
+  // which are register bits then, up to the scale block's last)
+  const int vec = codes > 0 ? 3 : 0;
+  low = codes > 0 ? std::max(codes, 6) : std::min(low, lanes);
+  const uint32_t all = (1u << tb) - 1, vec_src = (1u << vec) - 1, low_src = ((1u << low) - 1) & ~vec_src;
+  uint32_t low_dst = 0, vec_dst = 0;
+  for (int b = 0; b < tb; ++b) {
+    if (dest[b] < vec) vec_dst |= 1u << b;
+    else if (dest[b] < low) low_dst |= 1u << b;
+  }
+  const auto writes = [&](uint32_t regs) { return !(regs & low_dst) && (regs & vec_dst) == vec_dst; };
+  // register bits in ascending order, those of a group of codes first as they
+  // are read (first stage) and written
+  const auto order_regs = [&](uint32_t regs, bool first, StagePlan* s) {
+    int k = 0;
+    s->regs = regs;
+    if (!first && writes(regs))
+      for (int d = 0; d < vec; ++d)
+        for (int b = 0; b < tb; ++b)
+          if (dest[b] == d) s->reg[k++] = b;
+    for (int b = 0; b < tb; ++b)
+      if ((regs >> b) & 1 && std::find(s->reg, s->reg + k, b) == s->reg + k) s->reg[k++] = b;
+  };
+  bool vec_same = true;
+  for (int b = 0; b < vec; ++b) vec_same = vec_same && dest[b] == b;
   std::vector<StagePlan> st;
   Frame fr;
   std::vector<std::pair<int, int>> lin;
@@ -813,10 +834,10 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
   do {
     int got = 0;
     const uint32_t first = st.empty() ? low_src : 0u;
-    uint32_t P = pick_regs(gs, rem, tb, K, all & ~first, &got);
-    if ((P & low_dst) && !st.empty()) {  // a last stage that needs no further exchange, if one finishes the pass
+    uint32_t P = pick_regs(gs, rem, tb, K, all & ~first, &got, st.empty() ? vec_src : 0u);
+    if (!writes(P) && !st.empty()) {  // a last stage that needs no further exchange, if one finishes the pass
       int g2 = 0, sum = 0;
-      const uint32_t P2 = pick_regs(gs, rem, tb, K, all & ~low_dst, &g2);
+      const uint32_t P2 = pick_regs(gs, rem, tb, K, all & ~low_dst, &g2, vec_dst);
       for (int i : rem) sum += weight(gs[i]);
       if (g2 == sum) P = P2;
     }
@@ -829,9 +850,7 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
     // (a CNOT onto a bit with a phase pending cannot wait for an exchange)
     if (!stuck) leave_cnots(gs, &take, &keep);
     stuck = take.empty();
-    int k = 0;
-    for (int b = 0; b < tb; ++b)
-      if ((P >> b) & 1) s.reg[k++] = b;
+    order_regs(P, st.empty(), &s);
     Emitter em(gs, fr, s, K);
     for (int i : take) em.gate(gs[i]);
     em.finish();
@@ -848,18 +867,28 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
     return (int)st.size() + 1;
   };
   // the tile is written from lanes that hold the destination's low bits
-  if ((st.back().regs & low_dst) || (st.size() == 1 && low_src != low_dst) || !lin.empty()) {
+  if (!writes(st.back().regs) || (st.size() == 1 && (low_src != low_dst || !vec_same)) || !lin.empty()) {
     StagePlan s;
     s.lin.swap(lin);
     // bits that stay where they are first, then the highest
-    int k = 0;
+    uint32_t regs = vec_dst;
+    int k = vec;
     for (int pass = 0; pass < 2; ++pass)
       for (int b = tb - 1; b >= 0 && k < K; --b) {
-        if (((low_dst | s.regs) >> b) & 1) continue;
+        if (((low_dst | regs) >> b) & 1) continue;
         if (pass == 0 && !((st.back().regs >> b) & 1)) continue;
-        s.regs |= 1u << b;
-        s.reg[k++] = b;
+        regs |= 1u << b;
+        ++k;
       }
+    if (vec > 0) {
+      order_regs(regs, false, &s);
+    } else {
+      s.regs = regs;
+      k = 0;
+      for (int pass = 0; pass < 2; ++pass)
+        for (int b = tb - 1; b >= 0; --b)
+          if ((regs >> b) & 1 && (int)((st.back().regs >> b) & 1) == 1 - pass) s.reg[k++] = b;
+    }
     st.push_back(std::move(s));
   }
   settle_frame(fr, st.back(), tb, K);
@@ -900,30 +929,28 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
     std::vector<int> ln;
     uint32_t used = p.regs;
     for (int b : wv) used |= 1u << b;
-    if (f || l) {
-      for (int d = 0; d < low; ++d)
-        for (int b = 0; b < tb; ++b)
-          if ((f ? b : dest[b]) == d && !((used >> b) & 1)) {
-            ln.push_back(b);
-            used |= 1u << b;
-          }
-    }
     int span = 1;
     auto dir = [&](int b) { return slot(at[s][b]) & ((1 << phase) - 1); };
-    auto grow = [&](int b) {
+    auto put = [&](int b) {
       int g = span;
       for (int u = 0; u < (1 << phase); ++u)
         if ((span >> u) & 1) g |= 1 << (u ^ dir(b));
       span = g;
+      ln.push_back(b);
+      used |= 1u << b;
     };
-    for (int b : ln) grow(b);
+    if (f || l) {
+      // (the bits of a scale block are the lowest lane bits, in any order)
+      for (int pass = vec > 0 ? 0 : 1; pass < 2; ++pass)
+        for (int d = 0; d < (pass == 0 ? codes : low); ++d)
+          for (int b = 0; b < tb; ++b)
+            if ((f ? b : dest[b]) == d && !((used >> b) & 1) && (pass == 1 || !((span >> dir(b)) & 1))) put(b);
+    }
     for (int pass = 0; pass < 2; ++pass)
       for (int b = 0; b < tb; ++b) {
         if ((used >> b) & 1 || (int)ln.size() >= lanes) continue;
         if (pass == 0 && ((span >> dir(b)) & 1)) continue;
-        grow(b);
-        ln.push_back(b);
-        used |= 1u << b;
+        put(b);
       }
     for (int i = 0; i < lanes; ++i) p.thr[i] = ln[i];
     for (int i = 0; i < waves; ++i) p.thr[lanes + i] = wv[i];
@@ -1085,6 +1112,26 @@ bool block_build(const BlkSchedule& bs, const std::vector<BlkGate>& bg, bool fp6
     std::vector<BlkGate> mine;
     for (int t : sched.taken[i]) mine.push_back(bg[sched.tsrc.empty() ? t : sched.tsrc[t]]);
     plan_block_pass(sched.passes[i].g, mine, sched.taken[i], src, fp64, std::min(bs.low, fp64 ? 5 : 6), plan);
+  }
+  return true;
+}
+
+bool block_tile_plan(const TilePlan& tp, int block_bits, BlkPlan* plan) {
+  for (const TilePass& ps : tp.passes) {
+    // a pass's gates in the order that its ops apply them
+    std::vector<Gate> gates;
+    for (int o = ps.op_begin; o < ps.op_begin + ps.op_count; ++o)
+      for (int gi : tp.op_gates[o]) gates.push_back(tp.src[gi]);
+    std::vector<BlkGate> bg;
+    if (!block_gates(ps.g.n, gates, block_tol(false), &bg)) return false;
+    std::vector<Gate> where(bg.size());
+    std::vector<int> taken(bg.size());
+    for (size_t i = 0; i < bg.size(); ++i) {
+      taken[i] = (int)i;
+      where[i].nq = bg[i].kind == BlkGate::CPHASE || bg[i].kind == BlkGate::CNOT ? 2 : 1;
+      for (int j = 0; j < 2; ++j) where[i].q[j] = bg[i].q[j];
+    }
+    plan_block_pass(ps.g, bg, taken, where, false, 0, plan, block_bits);
   }
   return true;
 }

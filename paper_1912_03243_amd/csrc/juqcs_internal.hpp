@@ -272,7 +272,8 @@ hipError_t launch_expect(juqcs_dtype dt, const void* amps, const void* scales, c
 // Register-resident tile passes (k_block.hip): tile sizes that have a kernel.
 bool block_sized(juqcs_dtype dt, int b);
 // p: the pass, d_pass the same in device memory.
-hipError_t launch_block(juqcs_dtype dt, void* amps, const BlkPass& p, const BlkPass* d_pass, const BlkDev& d,
+bool block_codes_sized(int block_bits, int b);
+hipError_t launch_block(juqcs_dtype dt, void* amps, void* scales, const BlkPass& p, const BlkPass* d_pass, const BlkDev& d,
                         hipStream_t s);
 // Rounds of many states' passes (C64): groups [g0, g1) of tiles of 2^b
 // amplitudes, chunks [c0, c1), claimed through *ticket.
@@ -404,6 +405,7 @@ struct TilePlan {
   // for every op: the gates folded into it, in merge order, so the matrices
   // can be rebuilt for gates with other values but the same structure
   std::vector<std::vector<int>> op_gates;
+  std::vector<Gate> src;  // those gates, on the physical bits of their passes
   int64_t gates = 0;
 };
 
@@ -481,7 +483,7 @@ bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<
 // low: low bits that the first and the last stage keep on lanes (contiguous
 // accesses of 2^low amplitudes).
 void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, const std::vector<int>& taken,
-                     const std::vector<Gate>& where, bool fp64, int low, BlkPlan* plan);
+                     const std::vector<Gate>& where, bool fp64, int low, BlkPlan* plan, int codes = 0);
 // Plans a circuit as register-resident passes (arguments as plan_tiles);
 // false when it holds gates they do not take.
 bool plan_block(int n, int L, int b, const std::vector<Gate>& gates, bool fp64, int max_take, bool relabel,
@@ -502,6 +504,11 @@ void block_schedule(int n, int L, int b, const std::vector<BlkGate>& bg, int max
                     BlkSchedule* out);
 // Appends the schedule's passes with bg's values; false when bg has another shape.
 bool block_build(const BlkSchedule& bs, const std::vector<BlkGate>& bg, bool fp64, BlkPlan* plan);
+
+// The passes of a tile plan of two-byte amplitudes (scale blocks of 2^block_bits)
+// as register-resident programs: the same gates between the same encodings.
+// False if a pass has gates that they do not do.
+bool block_tile_plan(const TilePlan& tp, int block_bits, BlkPlan* plan);
 
 // Byte image of a plan for the device (reals in the state's precision) and
 // where its parts lie.

@@ -542,12 +542,12 @@ __global__ __launch_bounds__(kBranchSumThreads) void k_branch_sum_lds(
         c += 2;
         ++row;
       };
-      for (; c + 4 <= end;) {
+      while (c + 4 <= end) {
         const v4 a = row[0], b = row[1];
         put(a);
         put(b);
       }
-      for (; c < end;) put(row[0]);
+      while (c < end) put(row[0]);
       continue;
     }
     const auto at = [&](int i) { return reinterpret_cast<const cplx<float>*>(states + state_off[i])[zi]; };

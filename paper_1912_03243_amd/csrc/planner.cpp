@@ -659,6 +659,7 @@ void emit_schedule(const TileSchedule& sched, const std::vector<Gate>& gates, in
   plan->gates = sched.gates;
   kin = std::max(1, std::min(kin, 4));  // on-chip fusion width
   const std::vector<Gate>& src = sched.tgates.empty() ? gates : sched.tgates;
+  plan->src = src;
   for (size_t i = 0; i < sched.passes.size(); ++i) {
     std::vector<Cluster> cl;
     fuse(src, sched.taken[i], kin, &cl);
