@@ -4,7 +4,11 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <exception>
+#include <system_error>
+#include <thread>
 
+#include "absorb.hpp"
 #include "juqcs_internal.hpp"
 
 namespace juqcs {
@@ -202,45 +206,34 @@ struct Local {
 bool outside(int q) { return q >= 64; }
 uint32_t bit(int q) { return outside(q) ? 0u : 1u << q; }
 
+bool nondiag(const Local& l) { return l.g->kind != BlkGate::PHASE1 && l.g->kind != BlkGate::CPHASE; }
+
 // Gates (in order) that a stage with register bits P can apply: every target
 // a register bit, at least one bit of a controlled phase, and no earlier
 // gate left behind that does not commute.  Diagonal gates and controls
 // commute with each other.
-struct Absorber {
-  uint32_t blk_n = 0, blk_d = 0;  // bits with a gate left behind: any, diagonal on this bit
-  uint32_t P;
-  explicit Absorber(uint32_t p) : P(p) {}
-  bool done() const { return !(P & ~blk_n); }
-  bool take(const Local& l) {
-    const uint32_t a = bit(l.q[0]);
-    switch (l.g->kind) {
-      case BlkGate::ROT:
-      case BlkGate::DENSE:
-        if ((a & P) && !(a & (blk_n | blk_d))) return true;
-        blk_n |= a;
-        return false;
-      case BlkGate::PHASE1:
-        if ((a & P) && !(a & blk_n)) return true;
-        blk_d |= a;
-        return false;
-      case BlkGate::CPHASE: {
-        const uint32_t m = a | bit(l.q[1]);
-        if ((m & P) && !(m & blk_n)) return true;
-        blk_d |= m;
-        return false;
-      }
-      default: {  // CNOT
-        const uint32_t t = bit(l.q[1]);
-        if ((t & P) && !(t & (blk_n | blk_d)) && !(a & blk_n)) return true;
-        blk_n |= t;
-        blk_d |= a;
-        return false;
-      }
-    }
+AbsorbMask stage_mask(const Local& l) {
+  AbsorbMask m;
+  const uint32_t a = bit(l.q[0]);
+  switch (l.g->kind) {
+    case BlkGate::ROT:
+    case BlkGate::DENSE:
+      m.full = a;
+      break;
+    case BlkGate::PHASE1:
+      m.diag = a;
+      break;
+    case BlkGate::CPHASE:
+      m.diag = a | bit(l.q[1]);
+      break;
+    default:  // CNOT
+      m.full = bit(l.q[1]);
+      m.diag = a;
   }
-};
+  m.weight = nondiag(l) ? 4 : 1;
+  return m;
+}
 
-bool nondiag(const Local& l) { return l.g->kind != BlkGate::PHASE1 && l.g->kind != BlkGate::CPHASE; }
 
 // Controlled phases with one register bit that no later gate of the stage
 // takes over are left for a stage where one does, if there is one: there
@@ -265,41 +258,26 @@ void leave_for_later(const std::vector<Local>& gs, uint32_t P, std::vector<int>*
   std::sort(keep->begin(), keep->end());
 }
 
-int weight(const Local& l) {
-  return l.g->kind == BlkGate::PHASE1 || l.g->kind == BlkGate::CPHASE ? 1 : 4;
-}
-
-int score(const std::vector<Local>& gs, const std::vector<int>& rem, uint32_t P) {
-  Absorber ab(P);
-  int s = 0;
-  for (int i : rem) {
-    if (ab.take(gs[i])) s += weight(gs[i]);
-    else if (ab.done()) break;
-  }
-  return s;
-}
-
 // Register bits for the next stage: greedily the bit that lets the most
 // through, among the bits of allowed (at least K of them), besides those of
-// fixed.
-uint32_t pick_regs(const std::vector<Local>& gs, const std::vector<int>& rem, int tb, int K,
-                   uint32_t allowed, int* got, uint32_t fixed = 0) {
+// fixed.  got: what they let through.
+uint32_t pick_regs(const std::vector<AbsorbMask>& rem, int tb, int K, uint32_t allowed, uint64_t* got,
+                   uint32_t fixed = 0) {
   uint32_t P = fixed;
-  int best_all = 0;
+  AbsorbSearch search(rem, P);
   for (int k = __builtin_popcount(fixed); k < K; ++k) {
-    int best = -1, bs = -1;
-    for (int b = 0; b < tb; ++b) {
-      if (!((allowed >> b) & 1) || ((P >> b) & 1)) continue;
-      const int s = score(gs, rem, P | (1u << b));
-      if (s > bs) {
-        bs = s;
-        best = b;
+    uint64_t sets[32], w[32];
+    int which[32], count = 0;
+    for (int b = 0; b < tb; ++b)
+      if (((allowed & ~P) >> b) & 1) {
+        which[count] = b;
+        sets[count++] = P | 1u << b;
       }
-    }
-    P |= 1u << best;
-    best_all = bs;
+    search.weights(sets, count, w);
+    P |= 1u << which[std::max_element(w, w + count) - w];
+    search.grow(P);
   }
-  *got = best_all;
+  *got = search.taken();
   return P;
 }
 
@@ -832,20 +810,23 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
   std::vector<std::pair<int, int>> lin;
   bool stuck = false;  // the last stage and exchange took nothing
   do {
-    int got = 0;
+    std::vector<AbsorbMask> rm;
+    uint64_t got = 0, sum = 0;
+    for (int i : rem) {
+      rm.push_back(stage_mask(gs[i]));
+      sum += rm.back().weight;
+    }
     const uint32_t first = st.empty() ? low_src : 0u;
-    uint32_t P = pick_regs(gs, rem, tb, K, all & ~first, &got, st.empty() ? vec_src : 0u);
+    uint32_t P = pick_regs(rm, tb, K, all & ~first, &got, st.empty() ? vec_src : 0u);
     if (!writes(P) && !st.empty()) {  // a last stage that needs no further exchange, if one finishes the pass
-      int g2 = 0, sum = 0;
-      const uint32_t P2 = pick_regs(gs, rem, tb, K, all & ~low_dst, &g2, vec_dst);
-      for (int i : rem) sum += weight(gs[i]);
-      if (g2 == sum) P = P2;
+      const uint32_t P2 = pick_regs(rm, tb, K, all & ~low_dst, &got, vec_dst);
+      if (got == sum) P = P2;
     }
     StagePlan s;
     s.regs = P;
     std::vector<int> take, keep;
-    Absorber ab(P);
-    for (int i : rem) (ab.take(gs[i]) ? take : keep).push_back(i);
+    Absorb ab(P);
+    for (size_t k = 0; k < rem.size(); ++k) (ab.take(rm[k]) ? take : keep).push_back(rem[k]);
     leave_for_later(gs, P, &take, &keep);
     // (a CNOT onto a bit with a phase pending cannot wait for an exchange)
     if (!stuck) leave_cnots(gs, &take, &keep);
@@ -1170,19 +1151,40 @@ bool plan_block(int n, int L, int b, const std::vector<Gate>& gates, bool fp64, 
   *plan = BlkPlan();
   std::vector<BlkGate> bg;
   if (!block_gates(n, gates, block_tol(fp64), &bg)) return false;
-  // both selections where a run takes far longer than planning (2^24
-  // amplitudes or more), the better by plan_ms; else the second
+  // Both selections where a run takes far longer than planning (2^24
+  // amplitudes or more), side by side, and the better by plan_ms; else the
+  // second alone.
+  const int ways = n >= 24 ? 2 : 1;
+  BlkPlan cand[2];
+  BlkSchedule bs[2];
+  std::exception_ptr error[2];
+  const auto way = [&](int strict) {
+    try {
+      block_schedule(n, L, b, bg, max_take, relabel, strict != 0, &bs[strict]);
+      if (!block_build(bs[strict], bg, fp64, &cand[strict])) cand[strict] = BlkPlan();
+    } catch (...) {
+      error[strict] = std::current_exception();
+    }
+  };
+  std::thread other;
+  if (ways > 1) {
+    try {
+      other = std::thread(way, 1);
+    } catch (const std::system_error&) {  // no thread to be had
+      way(1);
+    }
+  }
+  way(0);
+  if (other.joinable()) other.join();
   double best = 0.0;
-  for (int strict = 0; strict < (n >= 24 ? 2 : 1); ++strict) {
-    BlkSchedule bs;
-    block_schedule(n, L, b, bg, max_take, relabel, strict != 0, &bs);
-    BlkPlan cand;
-    if (!block_build(bs, bg, fp64, &cand)) continue;
-    const double ms = plan_ms(cand, fp64);
+  for (int strict = 0; strict < ways; ++strict) {
+    if (error[strict]) std::rethrow_exception(error[strict]);
+    if (cand[strict].passes.empty()) continue;
+    const double ms = plan_ms(cand[strict], fp64);
     if (plan->passes.empty() || ms < best) {
       best = ms;
-      *plan = std::move(cand);
-      *final_pos = bs.sched.final_pos;
+      *plan = std::move(cand[strict]);
+      *final_pos = bs[strict].sched.final_pos;
     }
   }
   return !plan->passes.empty();

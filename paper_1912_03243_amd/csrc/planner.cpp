@@ -8,6 +8,7 @@
 #include <cmath>
 #include <cstring>
 
+#include "absorb.hpp"
 #include "juqcs_internal.hpp"
 
 namespace juqcs {
@@ -240,52 +241,102 @@ double gate_flops(const Gate& g) {
 }
 
 // ---------------------------------------------------------------------------
+// Absorption
+// ---------------------------------------------------------------------------
+namespace {
+
+// Eight sets at a time, as two vectors of four words; all ones where a set
+// leaves the gate behind.  Sets that are wholly blocked take nothing more.
+#define JUQCS_ABSORB_EIGHT(NAME, ATTR)                                                              \
+  ATTR void NAME(const AbsorbMask* m, size_t n, const uint64_t* set, uint64_t* out) {               \
+    typedef uint64_t v4 __attribute__((vector_size(32)));                                           \
+    v4 t[2], f[2] = {}, d[2] = {}, c[2] = {};                                                       \
+    for (int h = 0; h < 2; ++h) t[h] = v4{set[4 * h], set[4 * h + 1], set[4 * h + 2], set[4 * h + 3]}; \
+    for (size_t i = 0; i < n; ++i) {                                                                \
+      const uint64_t w = m[i].weight;                                                               \
+      const v4 F = v4{} + m[i].full, D = v4{} + m[i].diag, W = v4{} + w;                            \
+      for (int h = 0; h < 2; ++h) {                                                                 \
+        const v4 bad = (v4)(((F & (~t[h] | f[h] | d[h])) | (D & f[h])) != 0) | (v4)(((F | D) & t[h]) == 0); \
+        c[h] += W & ~bad;                                                                           \
+        f[h] |= F & bad;                                                                            \
+        d[h] |= D & bad;                                                                            \
+      }                                                                                             \
+      if ((i & 7) == 7) {                                                                           \
+        const v4 open = (t[0] & ~f[0]) | (t[1] & ~f[1]);                                            \
+        if (!(open[0] | open[1] | open[2] | open[3])) break;                                        \
+      }                                                                                             \
+    }                                                                                               \
+    for (int h = 0; h < 2; ++h)                                                                     \
+      for (int k = 0; k < 4; ++k) out[4 * h + k] = c[h][k];                                         \
+  }
+JUQCS_ABSORB_EIGHT(absorb_eight, )
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+JUQCS_ABSORB_EIGHT(absorb_eight_avx2, __attribute__((target("avx2"))))
+#define JUQCS_ABSORB_AVX2 1
+#endif
+#undef JUQCS_ABSORB_EIGHT
+
+}  // namespace
+
+void AbsorbSearch::weights(const uint64_t* set, int count, uint64_t* out) const {
+#ifdef JUQCS_ABSORB_AVX2
+  static const bool avx2 = __builtin_cpu_supports("avx2");
+#endif
+  for (int i = 0; i < count; i += 8) {
+    uint64_t s[8] = {}, w[8];
+    for (int k = 0; k < 8 && i + k < count; ++k) s[k] = set[i + k];
+#ifdef JUQCS_ABSORB_AVX2
+    if (avx2) absorb_eight_avx2(left_.data(), left_.size(), s, w);
+    else
+#endif
+      absorb_eight(left_.data(), left_.size(), s, w);
+    for (int k = 0; k < 8 && i + k < count; ++k) out[i + k] = taken_ + w[k];
+  }
+}
+
+// ---------------------------------------------------------------------------
 // Tile planning
 // ---------------------------------------------------------------------------
 namespace {
 
-// Qubit masks of a gate (n <= 40 qubits fit one word): those it is diagonal
-// on, and the others.
-struct GateMask {
-  uint64_t diag = 0, full = 0;
-};
-
-GateMask gate_mask(const Gate& g) {
-  GateMask m;
+// Qubit masks of a gate (n <= 40 qubits fit one word).
+AbsorbMask gate_mask(const Gate& g) {
+  AbsorbMask m;
   for (int j = 0; j < g.nq; ++j) ((g.diag_on >> j) & 1 ? m.diag : m.full) |= uint64_t(1) << g.q[j];
   return m;
 }
 
-std::vector<GateMask> rem_masks(const std::vector<Gate>& gates, const std::vector<int>& rem) {
-  std::vector<GateMask> m(rem.size());
+std::vector<AbsorbMask> rem_masks(const std::vector<Gate>& gates, const std::vector<int>& rem) {
+  std::vector<AbsorbMask> m(rem.size());
   for (size_t i = 0; i < rem.size(); ++i) m[i] = gate_mask(gates[rem[i]]);
   return m;
 }
 
-// Which gates of the remaining list, in order, a tile absorbs: all qubits but
-// the diagonal ones in the tile (and at least one of any), and no earlier gate
-// left behind that it does not commute with.  Gates that are diagonal on a
-// qubit commute there.
-struct TileAbsorber {
-  uint64_t tile, full = 0, diag = 0;  // qubits of gates left behind
-  bool take(const GateMask& m) {
-    if (!(m.full & ~tile) && ((m.full | m.diag) & tile) && !(m.full & (full | diag)) && !(m.diag & full))
-      return true;
-    full |= m.full;
-    diag |= m.diag;
-    return false;
-  }
-  bool done() const { return !(tile & ~full); }
-};
-
-int absorb_count(const std::vector<GateMask>& rm, uint64_t tile) {
-  TileAbsorber ab{tile};
+int absorb_count(const std::vector<AbsorbMask>& rm, uint64_t tile) {
+  Absorb ab(tile);
   int cnt = 0;
-  for (const GateMask& m : rm) {
+  for (const AbsorbMask& m : rm) {
     if (ab.take(m)) ++cnt;
     else if (ab.done()) break;
   }
   return cnt;
+}
+
+// The candidate (qubit not in the tile, and allowed) that lets the most gates
+// through, the first of them on a tie; -1: none.
+template <typename Allowed>
+int best_candidate(const AbsorbSearch& search, uint64_t tile, const std::vector<int>& cand, Allowed allowed) {
+  constexpr int kMost = 64;
+  uint64_t sets[kMost], got[kMost];
+  int which[kMost], k = 0;
+  for (int c : cand)
+    if (!((tile >> c) & 1) && allowed(c) && k < kMost) {
+      which[k] = c;
+      sets[k++] = tile | uint64_t(1) << c;
+    }
+  if (k == 0) return -1;
+  search.weights(sets, k, got);
+  return which[std::max_element(got, got + k) - got];
 }
 
 uint64_t tile_mask(const std::vector<char>& in_tile) {
@@ -377,18 +428,9 @@ void select_tiles(int n, int L, int b, int block_bits, const std::vector<Gate>& 
         if ((int)cand.size() >= kCandidates) break;
       }
       // greedy: add the candidate that lets the most gates through
-      const std::vector<GateMask> rm = rem_masks(gates, rem);
+      AbsorbSearch search(rem_masks(gates, rem), tile_mask(in_tile));
       for (int step = 0; step < H; ++step) {
-        int best = -1, bc = -1;
-        const uint64_t base = tile_mask(in_tile);
-        for (int c : cand) {
-          if (in_tile[c]) continue;
-          const int v = absorb_count(rm, base | (uint64_t(1) << c));
-          if (v > bc) {
-            bc = v;
-            best = c;
-          }
-        }
+        int best = best_candidate(search, tile_mask(in_tile), cand, [](int) { return true; });
         if (best < 0) {
           // fewer candidates than slots: fill with unused high bits
           for (int q = n - 1; q >= L; --q)
@@ -398,15 +440,16 @@ void select_tiles(int n, int L, int b, int block_bits, const std::vector<Gate>& 
             }
         }
         in_tile[best] = 1;
+        search.grow(tile_mask(in_tile));
         chosen.push_back(best);
       }
     }
     std::sort(chosen.begin(), chosen.end());
     // absorb
     std::vector<int> taken, keep;
-    TileAbsorber ab{tile_mask(in_tile)};
+    Absorb ab(tile_mask(in_tile));
     for (int gi : rem) {
-      if (max_take > 0 && (int)taken.size() >= max_take) ab.tile = 0;
+      if (max_take > 0 && (int)taken.size() >= max_take) ab.set = 0;
       (ab.take(gate_mask(gates[gi])) ? taken : keep).push_back(gi);
     }
     if (taken.empty()) {  // the front gate cannot fit any tile: give up
@@ -452,18 +495,10 @@ std::vector<char> pick_tile(int n, int b, const std::vector<Gate>& gates, const 
     }
     if ((int)cand.size() >= kCandidates) break;
   }
-  const std::vector<GateMask> rm = rem_masks(gates, rem);
+  AbsorbSearch search(rem_masks(gates, rem), tile_mask(in_tile));
   while (count < b) {
-    int best = -1, bc = -1;
-    const uint64_t base = tile_mask(in_tile);
-    for (int c : cand) {
-      if (in_tile[c] || (!near[c] && far >= far_cap)) continue;
-      const int v = absorb_count(rm, base | (uint64_t(1) << c));
-      if (v > bc) {
-        bc = v;
-        best = c;
-      }
-    }
+    int best = best_candidate(search, tile_mask(in_tile), cand,
+                              [&](int c) { return near[c] || far < far_cap; });
     if (best < 0)  // candidates used up: any admissible qubit, nearby ones first
       for (int round = 0; round < 2 && best < 0; ++round)
         for (int q = n - 1; q >= 0; --q)
@@ -472,6 +507,7 @@ std::vector<char> pick_tile(int n, int b, const std::vector<Gate>& gates, const 
             break;
           }
     in_tile[best] = 1;
+    search.grow(tile_mask(in_tile));
     ++count;
     if (!near[best]) ++far;
   }
@@ -486,18 +522,22 @@ namespace {
 // relabeling pass reach (local element swap(e) is read for destination e;
 // the kernels' LDS slot map folds bits s.. and 2s.. onto the low s bits:
 // s = 4 for 16-byte and 5 for 8-byte amplitudes; an access phase covers
-// 2^w lanes, w = 3 and 4).  Full rank: no bank conflicts.
-int writeback_slot_rank(const TileGeom& g, int s, int w) {
-  int span = 1, rank = 0;
+// 2^w lanes, w = 3 and 4).  Full rank: no bank conflicts.  src[j]: the local
+// bit that lands on bit j.
+int writeback_slot_rank(const int* src, int s, int w) {
+  int basis[4] = {}, rank = 0;  // by leading bit
   for (int j = 0; j < w; ++j) {
-    const int e = swap_local(1 << j, g);
-    const int v = (e ^ (((e >> s) ^ (e >> (2 * s))) & ((1 << s) - 1))) & ((1 << w) - 1);
-    if ((span >> v) & 1) continue;
-    ++rank;
-    int grown = span;
-    for (int u = 0; u < (1 << w); ++u)
-      if ((span >> u) & 1) grown |= 1 << (u ^ v);
-    span = grown;
+    const int e = 1 << src[j];
+    int v = (e ^ (((e >> s) ^ (e >> (2 * s))) & ((1 << s) - 1))) & ((1 << w) - 1);
+    for (int k = w - 1; k >= 0 && v; --k) {
+      if (!((v >> k) & 1)) continue;
+      if (!basis[k]) {
+        basis[k] = v;
+        ++rank;
+        break;
+      }
+      v ^= basis[k];
+    }
   }
   return rank;
 }
@@ -510,6 +550,8 @@ void select_tiles_relabel(int n, int L, int b, int block_bits, const std::vector
   for (int q = 0; q < n; ++q) sched->final_pos[q] = q;
   sched->tgates.clear();
   sched->tsrc.clear();
+  sched->tgates.reserve(gates.size());
+  sched->tsrc.reserve(gates.size());
   if (n <= b) {
     select_tiles(n, L, b, block_bits, gates, sched, max_take);
     sched->tgates = gates;  // a single tile: nothing moves
@@ -537,10 +579,10 @@ void select_tiles_relabel(int n, int L, int b, int block_bits, const std::vector
   while (!rem.empty()) {
     // absorb, in order, the gates whose qubits are all in the tile
     std::vector<int> taken, keep;
-    TileAbsorber ab{tile_mask(tile)};
+    Absorb ab(tile_mask(tile));
     for (int gi : rem) {
       const Gate& g = gates[gi];
-      if (max_take > 0 && (int)taken.size() >= max_take) ab.tile = 0;
+      if (max_take > 0 && (int)taken.size() >= max_take) ab.set = 0;
       if (ab.take(gate_mask(g))) {
         Gate t = g;
         for (int j = 0; j < t.nq; ++j) t.q[j] = pos[t.q[j]];
@@ -585,7 +627,7 @@ void select_tiles_relabel(int n, int L, int b, int block_bits, const std::vector
         if (moved[w] && tile[w] && !nl[w]) nl[w] = 1, ++cnt, in.push_back(w);
       for (int p = 0; p < L; ++p)
         if (!nl[at[p]]) out.push_back(at[p]);
-      const std::vector<GateMask> rm = rem_masks(gates, rem);
+      const std::vector<AbsorbMask> rm = rem_masks(gates, rem);
       if (cnt == L && in.size() == out.size() && (int)in.size() <= kSwapCap &&
           absorb_count(rm, tile_mask(moved)) > absorb_count(rm, tile_mask(kept))) {
         // wire in[i] (gathered in this pass) trades places with out[i] (low);
@@ -598,18 +640,18 @@ void select_tiles_relabel(int n, int L, int b, int block_bits, const std::vector
         for (size_t i = 0; i < out.size(); ++i) perm[i] = (int)i;
         int best_score = -1;
         do {
-          TileGeom t{};
-          t.nswap = (int)in.size();
-          for (size_t i = 0; i < in.size(); ++i) {
-            t.swap_a[i] = (int8_t)pos[out[perm[i]]];
-            t.swap_b[i] = (int8_t)lin[i];
-          }
-          const int score = 8 * writeback_slot_rank(t, 4, 3) + writeback_slot_rank(t, 5, 4);
+          int src[4] = {0, 1, 2, 3};
+          for (size_t i = 0; i < in.size(); ++i)
+            for (int side = 0; side < 2; ++side) {
+              const int from = side ? lin[i] : pos[out[perm[i]]], to = side ? pos[out[perm[i]]] : lin[i];
+              if (from < 4) src[from] = to;
+            }
+          const int score = 8 * writeback_slot_rank(src, 4, 3) + writeback_slot_rank(src, 5, 4);
           if (score > best_score) {
             best_score = score;
             best_perm = perm;
           }
-        } while (std::next_permutation(perm.begin(), perm.end()));
+        } while (best_score < 8 * 3 + 4 && std::next_permutation(perm.begin(), perm.end()));
         std::vector<int> out2(out.size());
         for (size_t i = 0; i < out.size(); ++i) out2[i] = out[best_perm[i]];
         out.swap(out2);
