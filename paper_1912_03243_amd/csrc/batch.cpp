@@ -97,13 +97,13 @@ void plan_circuit(int n, const std::vector<Gate>& g, int kin, bool relabel, Tile
   if (sched_out) *sched_out = std::move(sched);
 }
 
-// Runs f(i) for i in [0, count) on the host's cores; what one of them throws
-// is thrown to the caller, and with fewer threads to be had the others do
-// their share.
+// Runs f(i) for i in [0, count) on the host's cores, at most `most` of them;
+// what one of them throws is thrown to the caller, and with fewer threads to
+// be had the others do their share.
 template <typename F>
-void parallel_for(int count, F f) {
+void parallel_for(int count, F f, size_t most = 16) {
   const unsigned hw = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
-  const int nt = (int)std::min<unsigned>(hw, (unsigned)count);
+  const int nt = (int)std::min<size_t>(std::min<size_t>(hw, most), (size_t)count);
   std::atomic<int> next(0);
   std::mutex lock;
   std::exception_ptr error;
@@ -829,6 +829,9 @@ bool cut_block(BranchPart* bp, std::vector<int>* pos) {
   return true;
 }
 
+// Gates that are planned in about the time that it takes to start a thread.
+constexpr size_t kThreadGates = 256;
+
 // The plans of every segment and setting of the register-resident parts; a
 // part that turns out not to allow one falls back to the fused passes.
 void plan_blocks(BranchPart* parts, int P) {
@@ -846,10 +849,15 @@ void plan_blocks(BranchPart* parts, int P) {
       for (size_t x = 0; x < sg.bplans.size(); ++x) todo.push_back({&bp, &sg, (long long)x});
     }
   std::vector<char> made(todo.size());
-  parallel_for((int)todo.size(), [&](int i) {
-    const Todo& t = todo[i];
-    made[i] = seg_plan(*t.bp, *t.sg, t.setting, &t.sg->bplans[t.setting]) ? 1 : 0;
-  });
+  size_t gates = 0;
+  for (const Todo& t : todo) gates += t.sg->gates.size() + 4;
+  parallel_for(
+      (int)todo.size(),
+      [&](int i) {
+        const Todo& t = todo[i];
+        made[i] = seg_plan(*t.bp, *t.sg, t.setting, &t.sg->bplans[t.setting]) ? 1 : 0;
+      },
+      1 + gates / kThreadGates);
   for (size_t i = 0; i < todo.size(); ++i)
     if (!made[i] && todo[i].bp->block) cut_part(todo[i].bp, false);
   for (const Todo& t : todo) {
@@ -1039,7 +1047,7 @@ juqcs_status branch_prepare(int n, const juqcs_gate* gates, size_t gate_count, c
     parts[p].nloc = J->nloc[p];
     parts[p].sbytes = align256((size_t)8 << J->nloc[p]);
   }
-  parallel_for(P, [&](int p) { cut_part(&parts[p], block); });
+  parallel_for(P, [&](int p) { cut_part(&parts[p], block); }, 1 + gate_count / kThreadGates);
   plan_blocks(parts, P);
   return JUQCS_OK;
 }
