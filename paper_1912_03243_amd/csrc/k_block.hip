@@ -84,15 +84,16 @@ __global__ __launch_bounds__(1 << (TB - K), 4) void k_block(cplx<T>* __restrict_
   if (tau >= tau_end) return;
   const uint64_t lt = place<TBITS>(threadIdx.x, geometry(pass)->ld_thr);
   const uint64_t wt = place<TBITS>(threadIdx.x, geometry(pass)->st_thr) ^ geometry(pass)->st_flip;
-  Regs<T, K> v;
-  for (;;) {
-    {
-      const Const<BlkGeom> g = geometry(pass);
-      v2* p[R];
-      amp_ptrs<K>(gp + block_base(tau, g) + lt, g->ld_reg, p);
+  const auto load = [&](uint64_t t, v2* a) {
+    const Const<BlkGeom> g = geometry(pass);
+    v2* p[R];
+    amp_ptrs<K>(gp + block_base(t, g) + lt, g->ld_reg, p);
 #pragma unroll
-      for (int r = 0; r < R; ++r) v.a[r] = ld_stream(p[r]);
-    }
+    for (int r = 0; r < R; ++r) a[r] = ld_stream(p[r]);
+  };
+  Regs<T, K> v;
+  load(tau, v.a);
+  for (;;) {
     run_stages<T, TB, K>(v, sh, d, nst, tau);
     {
       const Const<BlkGeom> g = geometry(pass);
@@ -102,6 +103,7 @@ __global__ __launch_bounds__(1 << (TB - K), 4) void k_block(cplx<T>* __restrict_
       for (int r = 0; r < R; ++r) st_stream(p[r], v.a[r]);
     }
     if (++tau >= tau_end) break;
+    load(tau, v.a);  // on its way while the waves wait for each other (20 brick layers on 30 qubits: 175 -> 170 ms)
     if (tile_sync) __syncthreads();
   }
 }
@@ -270,20 +272,21 @@ __global__ __launch_bounds__(1 << (TB - K), 4) void k_block_round(
     d.stages = stages + as_const<BlkPass>(pass)->stage_begin;
     const uint64_t lt = place<TBITS>(threadIdx.x, geometry(pass)->ld_thr);
     const uint64_t wt = place<TBITS>(threadIdx.x, geometry(pass)->st_thr) ^ geometry(pass)->st_flip;
-    Regs<float, K> v;
-    for (;;) {
-      {
-        const Const<BlkGeom> g = geometry(pass);
-        if (init) {  // first pass: the state is |0...0>
+    const auto load = [&](uint64_t t, v2* a) {
+      const Const<BlkGeom> g = geometry(pass);
+      if (init) {  // first pass: the state is |0...0>
 #pragma unroll
-          for (int r = 0; r < R; ++r) v.a[r] = v2{r == 0 && tau == 0 && lt == 0 ? 1.0f : 0.0f, 0.0f};
-        } else {
-          const v2* p[R];
-          amp_ptrs<K>(src + block_base(tau, g) + lt, g->ld_reg, p);
+        for (int r = 0; r < R; ++r) a[r] = v2{r == 0 && t == 0 && lt == 0 ? 1.0f : 0.0f, 0.0f};
+      } else {
+        const v2* p[R];
+        amp_ptrs<K>(src + block_base(t, g) + lt, g->ld_reg, p);
 #pragma unroll
-          for (int r = 0; r < R; ++r) v.a[r] = *p[r];
-        }
+        for (int r = 0; r < R; ++r) a[r] = *p[r];
       }
+    };
+    Regs<float, K> v;
+    load(tau, v.a);
+    for (;;) {
       run_stages<float, TB, K>(v, sh, d, nst, tau);
       {
         const Const<BlkGeom> g = geometry(pass);
@@ -293,6 +296,7 @@ __global__ __launch_bounds__(1 << (TB - K), 4) void k_block_round(
         for (int r = 0; r < R; ++r) *p[r] = v.a[r];
       }
       if (++tau >= tau_end) break;
+      load(tau, v.a);
       if (tile_sync) __syncthreads();
     }
   }
