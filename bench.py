@@ -459,7 +459,7 @@ def tree_roofline(bst, ms):
     against the FP32 matrix-core peak, with their HBM bytes beside."""
     tf = bst["gate_flops"] / (ms / 1e3) / 1e12
     return {"bound": "alu", "achieved": tf, "peak": FP32_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
-            "frac": tf / FP32_MFMA_PEAK_TFLOPS, "kernel": "k_batch", "flops_per_step": bst["gate_flops"],
+            "frac": tf / FP32_MFMA_PEAK_TFLOPS, "kernel": "k_block_round<13,4>", "flops_per_step": bst["gate_flops"],
             "hbm": {"achieved_GBps": bst["pass_bytes"] / (ms / 1e3) / 1e9,
                     "bytes_per_step": bst["pass_bytes"],
                     "note": "24-qubit part states (128 MiB) are cache-resident: effective"},
@@ -573,7 +573,7 @@ def other_workload(args, juqcs, W, dev, stream, emit=True):
             # time is the step; in-tile ops run on FP32 matrix cores and VALU
             "roofline": {"bound": "alu", "achieved": tf, "peak": FP32_MFMA_PEAK_TFLOPS,
                          "unit": "TFLOP/s", "frac": tf / FP32_MFMA_PEAK_TFLOPS,
-                         "kernel": "k_batch", "flops_per_step": flops,
+                         "kernel": "k_block_round<13,4>", "flops_per_step": flops,
                          "hbm": {"achieved_GBps": 16.0 * st["tasks"] * 8192 / (ms / 1e3) / 1e9,
                                  "note": "tile tasks x 2^13 amplitudes x 16 B; states of n <= 24 "
                                          "are cache-resident, so effective"}},
@@ -834,7 +834,7 @@ def other_workload(args, juqcs, W, dev, stream, emit=True):
                          "flops_per_launch": fl / passes, "avg_launch_ms": kms / passes,
                          "kernel": (("k_block<float,12,4>" if tune and tune["tile_bits"] == 12
                                      else "k_block<float,13,4>") if dtype == "c64"
-                                    else "k_tile_enc2_fixed<13>"),
+                                    else "k_block_codes<13,4>"),
                          "hbm": {"achieved_GBps": achieved, "peak_GBps": HBM_PEAK_GBPS,
                                  "frac": achieved / HBM_PEAK_GBPS, "bytes_per_launch": kb / passes}},
             "amp_updates_per_s": len(circ) * float(1 << n) / (ms / 1e3),
