@@ -162,7 +162,7 @@ juqcs_status juqcs_apply_fused_k(juqcs_state* st, int k, const int* targets,
 typedef enum {
   JUQCS_PLAN_PLAIN = 0, /* one kernel pass per gate (the paper's scheme)   */
   JUQCS_PLAN_TILE = 1,  /* on-chip tile passes: every gate whose qubits lie
-                           in the chosen tile bits is applied in LDS, one
+                           in the chosen tile bits is applied there, one
                            HBM read+write per pass                        */
   JUQCS_PLAN_FUSED = 2, /* greedy fusion into dense k-qubit blocks applied
                            with juqcs_apply_fused_k's kernels             */
@@ -173,7 +173,9 @@ typedef enum {
 typedef struct {
   int32_t mode;        /* juqcs_plan_mode                                */
   int32_t fuse_k;      /* FUSED: block width 2..6 (0 = 5).  TILE: widest
-                          fused op inside a pass, 1..4 (0 = 3)            */
+                          fused op inside a pass, 1..4; 0 = gates one at a
+                          time from registers where the tile size and the
+                          gates allow it, else 3                          */
   int32_t mma;         /* FUSED: juqcs_mma                                */
   int32_t tile_bits;   /* TILE: total tile bits (0 = default for dtype)   */
   int32_t low_bits;    /* TILE: contiguous low bits per chunk (0 = default) */
@@ -304,7 +306,9 @@ juqcs_status juqcs_scale(juqcs_state* st, double factor);
  * for every qubit (Section 3), alpha = x, y, z: out[3*i + a], FP64 sums in
  * a fixed order.  Read-only passes over the state: the pair sums of up to
  * 13 bits come from one LDS-resident tile, so n qubits take
- * 1 + ceil((n - 13) / 8) passes for C128 (one for n <= 13).  Synchronises.
+ * 1 + ceil((n - 13) / 8) passes for C128 (one for n <= 13); ENC2 states of
+ * 24 qubits and more with block_bits >= 6 take 1 + ceil((n - 15) / 9), summing
+ * codes in integers.  Synchronises.
  * Errors: ARG, HIP. */
 juqcs_status juqcs_expectations(juqcs_state* st, double* out);
 
@@ -353,10 +357,11 @@ typedef struct juqcs_batch juqcs_batch; /* opaque */
  * state_offset[i] (each 8 * 2^n[i] bytes, 16-byte aligned, inside the buffer
  * and disjoint: JUQCS_ERR_SIZE / JUQCS_ERR_ARG otherwise, checked before any
  * device work); every circuit starts from |0...0>.  Each circuit is planned
- * on the host into on-chip tile passes (tiles of up to 2^12 amplitudes);
- * the fusion width inside a pass (1..4 qubits) is opts->fuse_k, or chosen
- * per circuit by a cost model when fuse_k is 0 (juqcs_batch_autotune
- * replaces it with timed trials).  No device memory is touched: bind a
+ * on the host into on-chip tile passes (tiles of up to 2^13 amplitudes).
+ * With fuse_k 0, circuits of 11 qubits and more apply their gates one at a
+ * time from registers (fusion width 1); else the fusion width inside a pass
+ * (1..4 qubits) is opts->fuse_k, or chosen per circuit by a cost model when
+ * fuse_k is 0 (juqcs_batch_autotune replaces it with timed trials).  No device memory is touched: bind a
  * workspace of juqcs_batch_bytes bytes before running.  Errors: ARG, SIZE,
  * QUBIT, NUMERIC. */
 juqcs_status juqcs_batch_create(juqcs_batch** out, int count, const int* n,
@@ -376,9 +381,9 @@ juqcs_status juqcs_batch_bind(juqcs_batch* b, void* d_work, size_t work_bytes,
                               void* hip_stream);
 
 /* Autotuner: for every qubit count of the batch, times one of its circuits
- * run alone with in-pass fusion widths 1..4 (on that circuit's state region
+ * run alone as planned and with in-pass fusion widths 1..4 (on that circuit's state region
  * and the bound workspace, on hip_stream) and re-plans every circuit with
- * the fastest width of its qubit count.  The batch is then unbound: query
+ * the fastest form of its qubit count.  The batch is then unbound: query
  * juqcs_batch_bytes and bind again.  Errors: ARG (not bound), HIP. */
 juqcs_status juqcs_batch_autotune(juqcs_batch* b, void* hip_stream);
 
@@ -454,7 +459,8 @@ juqcs_status juqcs_batch_destroy(juqcs_batch* b);
  * caller's device workspace (256-byte aligned) for the part states of a
  * group, the per-part indices, the running sum (4 P + 16 bytes per
  * bitstring, plus 8 words bytes for host bitstrings) and the tree rounds'
- * work lists; juqcs_branch_bytes gives its size.  group_size 0 takes the
+ * work lists; juqcs_branch_bytes gives its size, with up to 128 MiB more
+ * that speed up sums of 2^16 bitstrings and more where the buffer has them.  group_size 0 takes the
  * largest group that fits work_bytes; a group size that does not fit is
  * JUQCS_ERR_SIZE.  count = 0 needs no workspace. */
 juqcs_status juqcs_branch_amplitudes(int n, const juqcs_gate* gates,

@@ -36,6 +36,7 @@ bool finite(C a) { return std::isfinite(a.re) && std::isfinite(a.im); }
 // commute with them, then emits them as one gate.
 struct Rewriter {
   double tol;
+  bool f32;   // coefficients will be rounded to FP32
   bool keep;  // phases of 1 too, so that the gates' kinds do not depend on their values
   std::vector<BlkGate>* out;
   struct Open {
@@ -117,6 +118,15 @@ struct Rewriter {
       ok = finite(lam) && finite(g.ph) && finite(rest) && finite(div(C{1, 0}, g.ph)) && !zero(lam) &&
            absv(miss) <= tol * scale;
       if (ok) {
+        // the rounded t with the scalar that keeps |lam|^2 (1 + t^2): a rotation
+        // by a slightly other angle, instead of one that changes the norm
+        // (4096 circuits of up to 2000 gates: norms off by 1.4e-6, 2.0e-6 without)
+        const double t = f32 ? (double)(float)g.t : g.t;
+        if (t != g.t) {
+          const double f = std::sqrt((1.0 + g.t * g.t) / (1.0 + t * t));
+          lam = C{lam.re * f, lam.im * f};
+          g.t = t;
+        }
         g.lam = lam;
         out->push_back(g);
         w.m[0] = C{1, 0};
@@ -149,6 +159,7 @@ bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<
   out->clear();
   Rewriter rw;
   rw.tol = tol;
+  rw.f32 = tol > block_tol(true);
   rw.keep = keep;
   rw.out = out;
   rw.open.resize(n);
