@@ -670,14 +670,14 @@ template <int GK, bool ONE, typename Base, typename Scale>
 __device__ __forceinline__ void expect2_items(const v4i* sh, Base base, const int* row, Scale scale,
                                               Expect2Sums* s) {
   constexpr int R = 1 << GK, Q = ONE ? GK : GK * R / 2;  // sums: a bit's pairs together if ONE
-  int x[Q], y[Q], nrm[R];
+  int x[Q], y[Q], nrm[R], im[R];  // im: sums of imaginary codes (see turned)
 #pragma unroll 1
   for (int i = 0; i < 4; ++i) {
     if (ONE || i == 0) {
 #pragma unroll
       for (int q = 0; q < Q; ++q) x[q] = y[q] = 0;
 #pragma unroll
-      for (int r = 0; r < R; ++r) nrm[r] = 0;
+      for (int r = 0; r < R; ++r) nrm[r] = im[r] = 0;
     }
     const int u = base(i);
     v4i v[R];
@@ -685,11 +685,11 @@ __device__ __forceinline__ void expect2_items(const v4i* sh, Base base, const in
     for (int r = 0; r < R; ++r) v[r] = sh[u ^ row[r]];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      int t[R], im[R];
+      int t[R];
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         t[r] = turned(v[r][k]);
-        im[r] = dot4(v[r][k], kImag, 0);
+        im[r] = dot4(v[r][k], kImag, im[r]);
         nrm[r] = dot4(v[r][k], v[r][k], nrm[r]);
       }
       int q = 0;
@@ -700,7 +700,7 @@ __device__ __forceinline__ void expect2_items(const v4i* sh, Base base, const in
           if ((r >> j) & 1) continue;
           const int at = ONE ? j : q++;
           x[at] = dot4(v[r][k], v[r | 1 << j][k], x[at]);
-          y[at] = dot4(v[r][k], t[r | 1 << j], y[at]) + im[r];
+          y[at] = dot4(v[r][k], t[r | 1 << j], y[at]);
         }
       __builtin_amdgcn_sched_barrier(0);  // a dword's turned codes at a time (or they spill)
     }
@@ -710,7 +710,10 @@ __device__ __forceinline__ void expect2_items(const v4i* sh, Base base, const in
       for (int j = 0; j < GK; ++j) {
         int z = 0;
 #pragma unroll
-        for (int r = 0; r < R; ++r) z += (r >> j) & 1 ? -nrm[r] : nrm[r];
+        for (int r = 0; r < R; ++r) {
+          z += (r >> j) & 1 ? -nrm[r] : nrm[r];
+          y[j] += (r >> j) & 1 ? 0 : im[r];
+        }
         s->x[j] = fma(f2, (double)x[j], s->x[j]);
         s->y[j] = fma(f2, (double)y[j], s->y[j]);
         s->z[j] = fma(f2, (double)z, s->z[j]);
@@ -729,7 +732,7 @@ __device__ __forceinline__ void expect2_items(const v4i* sh, Base base, const in
         if ((r >> j) & 1) continue;
         const double ff = f[r] * f[r | 1 << j];
         s->x[j] = fma(ff, (double)x[q], s->x[j]);
-        s->y[j] = fma(ff, (double)y[q], s->y[j]);
+        s->y[j] = fma(ff, (double)(y[q] + im[r]), s->y[j]);
         s->z[j] = fma(f[r] * f[r], (double)nrm[r], s->z[j]);
         s->z[j] = fma(-(f[r | 1 << j] * f[r | 1 << j]), (double)nrm[r | 1 << j], s->z[j]);
         ++q;
