@@ -610,8 +610,8 @@ __global__ __launch_bounds__(kExpectThreads) void k_expect(const void* __restric
 // (two amplitudes), one FP64 multiplication with the two scales per sum of a
 // scale pair.  A tile is 2^15 amplitudes of raw codes (64 KiB of LDS, two
 // workgroups a CU), so that 2^33 amplitudes take three passes instead of the
-// five of decoded 2^13-amplitude tiles.  2^33 amplitudes: 26 ms for all 33
-// bits, 7.9 to 9.7 ms a pass (dot instructions and LDS reads; reading alone is
+// five of decoded 2^13-amplitude tiles.  2^33 amplitudes: 24 ms for all 33
+// bits, 7.7 to 8.8 ms a pass (dot instructions and LDS reads; reading alone is
 // 3.3 ms); decoded 93 ms, 18.6 ms a pass, FP64 and conversions.
 // Bits 0-2 lie inside a 16-byte vector of 8 amplitudes: every thread reduces
 // them on the vectors it has loaded.  The others form groups of three as in
