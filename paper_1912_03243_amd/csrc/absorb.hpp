@@ -2,6 +2,7 @@
 // of a list, in order, a set of bits lets through.
 #pragma once
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 #include <vector>
@@ -33,9 +34,13 @@ struct Absorb {
 // Weights that a growing set of bits takes.  What a set takes, a larger one
 // takes too (it leaves fewer gates behind), so a candidate is tried on the gates
 // that the set so far leaves behind only; eight candidates run side by side.
+// Gates after the point where a set is wholly blocked are not looked at.
 class AbsorbSearch {
  public:
-  AbsorbSearch(std::vector<AbsorbMask> gates, uint64_t set) : left_(std::move(gates)) { grow(set); }
+  AbsorbSearch(std::vector<AbsorbMask> gates, uint64_t set) : gates_(std::move(gates)) {
+    left_.reserve(std::min<size_t>(gates_.size(), 256));
+    grow(set);
+  }
   // The set takes on bits.
   void grow(uint64_t set) {
     Absorb ab(set);
@@ -45,13 +50,19 @@ class AbsorbSearch {
       else left_[k++] = left_[i];
     }
     left_.resize(k);
+    for (; next_ < gates_.size() && !ab.done(); ++next_) {
+      if (ab.take(gates_[next_])) taken_ += gates_[next_].weight;
+      else left_.push_back(gates_[next_]);
+    }
   }
   uint64_t taken() const { return taken_; }
   // out[i]: what set[i], a superset of the set so far, takes.
   void weights(const uint64_t* set, int count, uint64_t* out) const;
 
  private:
-  std::vector<AbsorbMask> left_;
+  std::vector<AbsorbMask> gates_;  // from next_ on: not looked at yet, all left behind
+  std::vector<AbsorbMask> left_;   // left behind before that
+  size_t next_ = 0;
   uint64_t taken_ = 0;
 };
 

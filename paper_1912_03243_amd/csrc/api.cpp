@@ -206,6 +206,13 @@ juqcs_status run_tile_plan(juqcs_state* st, const TilePlan& plan) {
   return JUQCS_OK;
 }
 
+// Whether a register-resident plan fits the workspace's ring at once (fused
+// plans of very many controlled phases are smaller).
+bool fits_ring(const juqcs_state* st, const BlkPlan& plan) {
+  const size_t bytes = block_layout(BlkSizes(plan), st->dt == JUQCS_C128).total;
+  return kRingOff + ((bytes + 255) & ~size_t(255)) <= st->work_bytes;
+}
+
 // Runs a register-resident plan: one upload, then every pass.
 juqcs_status run_block_plan(juqcs_state* st, const BlkPlan& plan) {
   if (plan.passes.empty()) return JUQCS_OK;
@@ -306,7 +313,8 @@ juqcs_status tile_gates(juqcs_state* st, const std::vector<Gate>& gates, int L, 
   std::vector<int> moved;  // moved[p]: physical bit that the qubit at bit p ends on
   if (block && block_sized(st->dt, std::min(b, st->n))) {
     BlkPlan bp;
-    if (plan_block(st->n, l, b, gates, st->dt == JUQCS_C128, std::max(pass_gates, 0), rl, &bp, &moved)) {
+    if (plan_block(st->n, l, b, gates, st->dt == JUQCS_C128, std::max(pass_gates, 0), rl, &bp, &moved) &&
+        fits_ring(st, bp)) {
       if (passes) *passes = (int64_t)bp.passes.size();
       if (juqcs_status rc = run_block_plan(st, bp)) return rc;
       if (rl)
@@ -337,7 +345,7 @@ juqcs_status tile_gates(juqcs_state* st, const std::vector<Gate>& gates, int L, 
   if (passes) *passes = (int64_t)plan.passes.size();
   BlkPlan bp;
   const bool codes = block && st->dt == JUQCS_ENC2 && block_codes_sized(st->B, std::min(b, st->n)) &&
-                     block_tile_plan(plan, st->B, &bp);
+                     block_tile_plan(plan, st->B, &bp) && fits_ring(st, bp);
   if (juqcs_status rc = codes ? run_block_plan(st, bp) : run_tile_plan(st, plan)) return rc;
   if (rl)
     for (int q = 0; q < st->n; ++q) st->phys[q] = moved[st->phys[q]];

@@ -405,7 +405,7 @@ struct TilePlan {
   // for every op: the gates folded into it, in merge order, so the matrices
   // can be rebuilt for gates with other values but the same structure
   std::vector<std::vector<int>> op_gates;
-  std::vector<Gate> src;  // those gates, on the physical bits of their passes
+  std::vector<Gate> src;  // those gates, on the physical bits of their passes (two-byte plans only)
   int64_t gates = 0;
 };
 

@@ -248,22 +248,26 @@ namespace {
 // Eight sets at a time, as two vectors of four words; all ones where a set
 // leaves the gate behind.  Sets that are wholly blocked take nothing more.
 #define JUQCS_ABSORB_EIGHT(NAME, ATTR)                                                              \
-  ATTR void NAME(const AbsorbMask* m, size_t n, const uint64_t* set, uint64_t* out) {               \
+  ATTR void NAME(const AbsorbMask* const* list, const size_t* size, const uint64_t* set, uint64_t* out) { \
     typedef uint64_t v4 __attribute__((vector_size(32)));                                           \
     v4 t[2], f[2] = {}, d[2] = {}, c[2] = {};                                                       \
     for (int h = 0; h < 2; ++h) t[h] = v4{set[4 * h], set[4 * h + 1], set[4 * h + 2], set[4 * h + 3]}; \
-    for (size_t i = 0; i < n; ++i) {                                                                \
-      const uint64_t w = m[i].weight;                                                               \
-      const v4 F = v4{} + m[i].full, D = v4{} + m[i].diag, W = v4{} + w;                            \
-      for (int h = 0; h < 2; ++h) {                                                                 \
-        const v4 bad = (v4)(((F & (~t[h] | f[h] | d[h])) | (D & f[h])) != 0) | (v4)(((F | D) & t[h]) == 0); \
-        c[h] += W & ~bad;                                                                           \
-        f[h] |= F & bad;                                                                            \
-        d[h] |= D & bad;                                                                            \
-      }                                                                                             \
-      if ((i & 7) == 7) {                                                                           \
-        const v4 open = (t[0] & ~f[0]) | (t[1] & ~f[1]);                                            \
-        if (!(open[0] | open[1] | open[2] | open[3])) break;                                        \
+    bool open = true;                                                                               \
+    for (int part = 0; part < 2; ++part) {                                                          \
+      const AbsorbMask* m = list[part];                                                             \
+      for (size_t i = 0; i < size[part] && open; ++i) {                                             \
+        const uint64_t w = m[i].weight;                                                             \
+        const v4 F = v4{} + m[i].full, D = v4{} + m[i].diag, W = v4{} + w;                          \
+        for (int h = 0; h < 2; ++h) {                                                               \
+          const v4 bad = (v4)(((F & (~t[h] | f[h] | d[h])) | (D & f[h])) != 0) | (v4)(((F | D) & t[h]) == 0); \
+          c[h] += W & ~bad;                                                                         \
+          f[h] |= F & bad;                                                                          \
+          d[h] |= D & bad;                                                                          \
+        }                                                                                           \
+        if ((i & 7) == 7) {                                                                         \
+          const v4 o = (t[0] & ~f[0]) | (t[1] & ~f[1]);                                             \
+          open = (o[0] | o[1] | o[2] | o[3]) != 0;                                                  \
+        }                                                                                           \
       }                                                                                             \
     }                                                                                               \
     for (int h = 0; h < 2; ++h)                                                                     \
@@ -282,14 +286,16 @@ void AbsorbSearch::weights(const uint64_t* set, int count, uint64_t* out) const 
 #ifdef JUQCS_ABSORB_AVX2
   static const bool avx2 = __builtin_cpu_supports("avx2");
 #endif
+  const AbsorbMask* const list[2] = {left_.data(), gates_.data() + next_};
+  const size_t size[2] = {left_.size(), gates_.size() - next_};
   for (int i = 0; i < count; i += 8) {
     uint64_t s[8] = {}, w[8];
     for (int k = 0; k < 8 && i + k < count; ++k) s[k] = set[i + k];
 #ifdef JUQCS_ABSORB_AVX2
-    if (avx2) absorb_eight_avx2(left_.data(), left_.size(), s, w);
+    if (avx2) absorb_eight_avx2(list, size, s, w);
     else
 #endif
-      absorb_eight(left_.data(), left_.size(), s, w);
+      absorb_eight(list, size, s, w);
     for (int k = 0; k < 8 && i + k < count; ++k) out[i + k] = taken_ + w[k];
   }
 }
@@ -701,7 +707,8 @@ void emit_schedule(const TileSchedule& sched, const std::vector<Gate>& gates, in
   plan->gates = sched.gates;
   kin = std::max(1, std::min(kin, 4));  // on-chip fusion width
   const std::vector<Gate>& src = sched.tgates.empty() ? gates : sched.tgates;
-  plan->src = src;
+  plan->src.clear();
+  if (!sched.passes.empty() && sched.passes[0].g.block_bits > 0) plan->src = src;  // (they are large)
   for (size_t i = 0; i < sched.passes.size(); ++i) {
     std::vector<Cluster> cl;
     fuse(src, sched.taken[i], kin, &cl);
