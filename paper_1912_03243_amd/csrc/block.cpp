@@ -626,7 +626,7 @@ void emit_layers(const StagePlan& p, int nthr, BlkStage base, BlkPlan* plan) {
     std::vector<EOp::Col> col[kBlkRegs];
     uint32_t sgn = 0;  // register bits in a sign change
   };
-  const auto push_op = [&](int kind, uint32_t tm, uint64_t gm, const double* c, int n) {
+  const auto push_op = [&](uint32_t kind, uint32_t tm, uint64_t gm, const double* c, int n) {
     BlkOp o{};
     o.kind = kind;
     o.tmask = tm;
@@ -639,7 +639,7 @@ void emit_layers(const StagePlan& p, int nthr, BlkStage base, BlkPlan* plan) {
     *c0 = (int32_t)plan->ops.size();
     for (const EOp::Col& c : col) {
       const double v[2] = {c.ph.re, c.ph.im};
-      push_op(BLK_COLLECT, outside(c.q) ? 0u : tmask_of(1u << c.q), outside(c.q) ? uint64_t(1) << (c.q - 64) : 0, v, 2);
+      push_op(0, outside(c.q) ? 0u : tmask_of(1u << c.q), outside(c.q) ? uint64_t(1) << (c.q - 64) : 0, v, 2);
     }
     *c1 = (int32_t)plan->ops.size();
   };
@@ -654,16 +654,23 @@ void emit_layers(const StagePlan& p, int nthr, BlkStage base, BlkPlan* plan) {
     for (size_t i = 0; i < cur.misc.size(); ++i) {
       const EOp& e = *cur.misc[i];
       double c[8] = {e.ph.re, e.ph.im, 0, 0, 0, 0, 0, 0};
-      int kind = 0;
+      uint32_t kind = 0;
+      int lo = 0, hi = 0;  // register control bits
+      if (e.cm) {
+        lo = __builtin_ctz(e.cm);
+        hi = 31 - __builtin_clz(e.cm);
+      }
       if (e.kind == E_DENSE) {
-        kind = BLK_DENSE + e.J;
+        kind = blk_dense(e.J);
         for (int k = 0; k < 4; ++k) c[2 * k] = e.m[k].re, c[2 * k + 1] = e.m[k].im;
       } else if (e.kind == E_SWAP) {
-        kind = BLK_SWAP + e.J;
+        kind = blk_swap(e.J, e.cm ? lo : e.J);
+      } else if (e.kind == E_SIGNS) {
+        kind = blk_signs(e.cm);
       } else {
-        kind = e.kind == E_SIGNS ? BLK_SIGNS : BLK_PHASE;
+        kind = e.cm ? blk_phase(lo, hi) : blk_phase();
       }
-      const int o = push_op(kind | (int)(e.cm << 8), tmask_of(e.tmask), e.gmask, c, 8);
+      const int o = push_op(kind, tmask_of(e.tmask), e.gmask, c, 8);
       plan->ops[o].col_begin = cols[i].first;
       plan->ops[o].col_end = cols[i].second;
     }

@@ -159,59 +159,46 @@ __device__ __forceinline__ void collect(Const<BlkOp> ops, Const<T> oc, int c0, i
 template <typename T, int K>
 __device__ __forceinline__ void run_misc(Regs<T, K>& v, Const<BlkOp> ops, Const<T> oc, int o0, int o1,
                                          uint32_t tid, uint64_t tau) {
+  static_assert(K == 4, "the kinds name four register bits");
   for (int o = o0; o < o1; ++o) {
     const uint32_t tm = ops[o].tmask;
     const uint64_t gm = ops[o].gmask;
-    const int all = ops[o].kind, cm = (all >> 8) & 0xff, kind = all & 0xff;
+    uint32_t kind = ops[o].kind;
+    asm volatile("" : "+s"(kind));  // independent bits, as far as the compiler knows
     T c[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) c[i] = oc[8 * o + i];
-    if (kind < BLK_SWAP) {
-      if (kind == BLK_DENSE + 0) v.template dense<0>(c);
-      if (kind == BLK_DENSE + 1) v.template dense<1>(c);
-      if (kind == BLK_DENSE + 2) v.template dense<2>(c);
-      if (kind == BLK_DENSE + 3) v.template dense<3>(c);
-    } else if (kind < BLK_PHASE) {
-      const bool on = (tid & tm) == tm && (tau & gm) == gm;
+    const bool on = (tid & tm) == tm && (tau & gm) == gm;
+    if (kind & blk_dense(0)) v.template dense<0>(c);
+    if (kind & blk_dense(1)) v.template dense<1>(c);
+    if (kind & blk_dense(2)) v.template dense<2>(c);
+    if (kind & blk_dense(3)) v.template dense<3>(c);
 #define JUQCS_SWAP(J, I) \
-  if (kind == BLK_SWAP + J && cm == (I < 0 ? 0 : 1 << (I & 7))) v.template swap_if<J, (I < 0 ? 0 : 1 << (I & 7))>(on);
-      if (kind == BLK_SWAP + 0) {
-        JUQCS_SWAP(0, -1)
-        JUQCS_SWAP(0, 1)
-        JUQCS_SWAP(0, 2)
-        JUQCS_SWAP(0, 3)
-      }
-      if (kind == BLK_SWAP + 1) {
-        JUQCS_SWAP(1, -1)
-        JUQCS_SWAP(1, 0)
-        JUQCS_SWAP(1, 2)
-        JUQCS_SWAP(1, 3)
-      }
-      if (kind == BLK_SWAP + 2) {
-        JUQCS_SWAP(2, -1)
-        JUQCS_SWAP(2, 0)
-        JUQCS_SWAP(2, 1)
-        JUQCS_SWAP(2, 3)
-      }
-      if (kind == BLK_SWAP + 3) {
-        JUQCS_SWAP(3, -1)
-        JUQCS_SWAP(3, 0)
-        JUQCS_SWAP(3, 1)
-        JUQCS_SWAP(3, 2)
-      }
+  if (kind & blk_swap(J, I)) v.template swap_if<J, (I == J ? 0 : 1 << I)>(on);
+#define JUQCS_SWAPS(J)                        \
+  if (kind & (blk_swap(J, 0) * 15)) {         \
+    JUQCS_SWAP(J, 0)                          \
+    JUQCS_SWAP(J, 1)                          \
+    JUQCS_SWAP(J, 2)                          \
+    JUQCS_SWAP(J, 3)                          \
+  }
+    JUQCS_SWAPS(0)
+    JUQCS_SWAPS(1)
+    JUQCS_SWAPS(2)
+    JUQCS_SWAPS(3)
+#undef JUQCS_SWAPS
 #undef JUQCS_SWAP
-    } else if (kind == BLK_SIGNS) {
-      v.signs(cm, parity_sign(tid & tm, tau & gm));
-    } else {  // BLK_PHASE on two register bits, or on none (a phase per thread)
+    if (kind & blk_signs(0)) v.signs((int)(kind >> 28), parity_sign(tid & tm, tau & gm));
+    if (kind & (blk_phase() * 127)) {
       T C = c[0], S = c[1];
       collect(ops, oc, ops[o].col_begin, ops[o].col_end, tid, tau, &C, &S);
-      if (cm == 0) v.template phase<0>(C, S);
-      if (cm == 3) v.template phase<3>(C, S);
-      if (cm == 5) v.template phase<5>(C, S);
-      if (cm == 9) v.template phase<9>(C, S);
-      if (cm == 6) v.template phase<6>(C, S);
-      if (cm == 10) v.template phase<10>(C, S);
-      if (cm == 12) v.template phase<12>(C, S);
+      if (kind & blk_phase()) v.template phase<0>(C, S);
+      if (kind & blk_phase(0, 1)) v.template phase<3>(C, S);
+      if (kind & blk_phase(0, 2)) v.template phase<5>(C, S);
+      if (kind & blk_phase(0, 3)) v.template phase<9>(C, S);
+      if (kind & blk_phase(1, 2)) v.template phase<6>(C, S);
+      if (kind & blk_phase(1, 3)) v.template phase<10>(C, S);
+      if (kind & blk_phase(2, 3)) v.template phase<12>(C, S);
     }
   }
 }

@@ -172,19 +172,23 @@ enum BlkFlags : int32_t {  // J: register bit
 };
 // Bit of a pair of register bits: neighbours first (0-2), then the others.
 constexpr int pair_bit(int i, int j) { return j == i + 1 ? i : j == i + 2 ? 3 + i : 5; }
-enum BlkKind : int32_t {  // misc ops
-  BLK_DENSE = 0,    // + J: dense 2x2, 8 reals
-  BLK_SWAP = 8,     // + J: the halves trade places where all control bits are set
-  BLK_PHASE = 16,   // C + i S where all register control bits (none or two) are set
-  BLK_COLLECT = 17, // entry of a col list: C + i S where all mask bits are set
-  BLK_SIGNS = 18,   // sign by the parity of the masked thread bits and of the register control bits
-  // bits 8..15: register control bits (BLK_SWAP, BLK_PHASE, BLK_SIGNS)
-};
+// Kinds of misc ops: one bit each, so that the kernels test them one by one (a
+// chain of comparisons is made a tree of branches whose joins copy all
+// amplitudes).
+constexpr uint32_t blk_dense(int j) { return 1u << j; }  // dense 2x2 on register bit j, 8 reals
+// the halves of register bit j trade places where bit i is set (i = j: where
+// all mask bits are)
+constexpr uint32_t blk_swap(int j, int i) { return 1u << (4 + 4 * j + i); }
+// C + i S where all mask bits and both register bits (i < j) are set; on none
+constexpr uint32_t blk_phase() { return 1u << 21; }
+constexpr uint32_t blk_phase(int i, int j) { return 1u << (22 + pair_bit(i, j)); }
+// sign by the parity of the masked bits and of the register bits cm
+constexpr uint32_t blk_signs(uint32_t cm) { return 1u << 20 | cm << 28; }
 struct BlkOp {     // coefficients: 8 reals per op
-  int32_t kind;
+  uint32_t kind;   // (entries of a col list, C + i S where all mask bits are set: 0)
   uint32_t tmask;  // thread bits (of the thread index)
   uint64_t gmask;  // bits of the tile number
-  int32_t col_begin, col_end;  // BLK_PHASE: phases that join per thread
+  int32_t col_begin, col_end;  // phases: phases that join per thread
 };
 enum BlkExchange : int32_t { BLK_STAY, BLK_WAVE, BLK_CROSS };  // nothing, within waves, across waves
 struct BlkStage {
