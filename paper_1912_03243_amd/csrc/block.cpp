@@ -897,10 +897,10 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
   // phases (8 lanes of 16 bytes, 16 of 8) reach distinct bank slots
   std::vector<int> wv;
   constexpr int phase = 4;
-  // at[s][b]: where (in which old element's slot) the tile element 1 << b of
-  // stage s lies: the CNOTs done by the exchanges so far, linear over XOR
-  std::vector<std::vector<int>> at(st.size(), std::vector<int>(tb));
-  std::vector<char> crosses(st.size(), 0);
+  // at[s][b]: where (in which of the first stage's elements' slots) the tile
+  // element 1 << b of stage s lies: the CNOTs done by the exchanges so far,
+  // linear over XOR; from[s][b]: the same in the elements of the stage before
+  std::vector<std::vector<int>> at(st.size(), std::vector<int>(tb)), from = at;
   for (int b = 0; b < tb; ++b) at[0][b] = 1 << b;
   for (size_t s = 0; s < st.size(); ++s) {
     StagePlan& p = st[s];
@@ -911,6 +911,7 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
           if ((x >> p.lin[i].first) & 1) x ^= 1 << p.lin[i].second;
         for (int c = 0; c < tb; ++c)
           if ((x >> c) & 1) y ^= at[s - 1][c];
+        from[s][b] = x;
         at[s][b] = y;
       }
     const bool f = s == 0, l = s + 1 == st.size();
@@ -953,10 +954,6 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
       }
     for (int i = 0; i < lanes; ++i) p.thr[i] = ln[i];
     for (int i = 0; i < waves; ++i) p.thr[lanes + i] = wv[i];
-    // a CNOT onto a wave bit (of either side) moves amplitudes between waves
-    for (const auto& g : p.lin)
-      for (int i = lanes; i < nthr; ++i)
-        if (g.second == p.thr[i] || g.second == st[s - 1].thr[i]) crosses[s] = 1;
   }
   // serialise
   BlkPass out{};
@@ -976,18 +973,25 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
     g.ld_reg[j] = phys(st.front().reg[j]);
     g.st_reg[j] = phys(dest[st.back().reg[j]]);
   }
-  auto same_waves = [&](const StagePlan& a, const StagePlan& b) {
-    return std::equal(a.thr + lanes, a.thr + nthr, b.thr + lanes);
+  // Whether every wave's elements of stage b lie in slots of its own elements of
+  // stage a.  in: the element of a in whose slot each element 1 << e of b lies.
+  auto same_slots = [&](const StagePlan& a, const StagePlan& b, const std::vector<int>& in) {
+    for (int i = lanes; i < nthr; ++i)
+      for (int e = 0; e < tb; ++e)
+        if (((in[e] >> a.thr[i]) & 1) != (e == b.thr[i])) return false;
+    return true;
   };
-  g.tile_sync = st.size() > 1 && (!same_waves(st.front(), st.back()) ||
-                                  std::find(crosses.begin(), crosses.end(), 1) != crosses.end());
+  // A tile's first exchange writes the first stage's slots, which other waves
+  // may still read in the last exchange of the tile before unless they are
+  // the wave's own there.
+  g.tile_sync = st.size() > 1 && !same_slots(st.front(), st.back(), at.back());
   for (int b = 0; b < tb; ++b)
     if ((fr.flip >> b) & 1) g.st_flip |= uint64_t(1) << phys(dest[b]);
   out.stage_begin = (int32_t)plan->stages.size();
   for (size_t s = 0; s < st.size(); ++s) {
     const StagePlan& p = st[s];
     BlkStage x{};
-    x.exchange = s > 0 && (!same_waves(st[s - 1], p) || crosses[s]) ? BLK_CROSS : BLK_WAVE;
+    x.exchange = s > 0 && !same_slots(st[s - 1], p, from[s]) ? BLK_CROSS : BLK_WAVE;
     for (int j = 0; j < K; ++j) x.row[j] = slot(at[s][p.reg[j]]) * kSlotBytes;
     for (int i = 0; i < nthr; ++i) x.thr[i] = slot(at[s][p.thr[i]]) * kSlotBytes;
     emit_layers(p, nthr, x, plan);

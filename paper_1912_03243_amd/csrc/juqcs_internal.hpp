@@ -202,7 +202,7 @@ struct BlkGeom {
   int32_t n, b, L, H;            // as TileGeom
   int32_t hbits[kMaxGather];
   int32_t nst;                   // stages
-  int32_t tile_sync;             // the first and last stage have different wave bits
+  int32_t tile_sync;             // waves hold other LDS slots in the last stage than in the first
   int32_t block_bits;            // ENC2 only
   // physical bit of each thread and register bit as the tile is read and as
   // it is written (through the pass's relabel swaps)
