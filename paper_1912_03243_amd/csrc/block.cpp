@@ -821,8 +821,10 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
     for (int b = 0; b < tb; ++b)
       if ((regs >> b) & 1 && std::find(s->reg, s->reg + k, b) == s->reg + k) s->reg[k++] = b;
   };
-  bool vec_same = true;
-  for (int b = 0; b < vec; ++b) vec_same = vec_same && dest[b] == b;
+  // A stage that is both the first and the last has to lay out a scale block
+  // as it is read and as it is written.
+  bool block_same = true;
+  for (int b = 0; b < codes; ++b) block_same = block_same && dest[b] == b;
   std::vector<StagePlan> st;
   Frame fr;
   std::vector<std::pair<int, int>> lin;
@@ -866,7 +868,7 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
     return (int)st.size() + 1;
   };
   // the tile is written from lanes that hold the destination's low bits
-  if (!writes(st.back().regs) || (st.size() == 1 && (low_src != low_dst || !vec_same)) || !lin.empty()) {
+  if (!writes(st.back().regs) || (st.size() == 1 && (low_src != low_dst || !block_same)) || !lin.empty()) {
     StagePlan s;
     s.lin.swap(lin);
     // bits that stay where they are first, then the highest

@@ -35,3 +35,21 @@ def test_waves_share_slots_only_across_barriers(P, tile, dtype):
         assert rep.races == 0 and rep.misplaced == 0, (seed, rep.races, rep.misplaced)
         err = float(np.linalg.norm(got - sv.run_circuit(n, circ)))
         assert err <= 8.0 * EPS[dtype] * len(circ) * growth(circ), seed
+
+
+# a pass whose relabel swap takes a bit of the scale block for a gathered one
+SWAPPED_BLOCK = W.concat(W.gate(W.OP_H, 1), W.gate(W.OP_CNOT, 14, 5), W.gate(W.OP_H, 11),
+                         W.gate(W.OP_CNOT, 15, 12), W.gate(W.OP_CNOT, 6, 7), W.gate(W.OP_CNOT, 0, 10),
+                         W.gate(W.OP_CNOT, 2, 9), W.gate(W.OP_H, 1))
+
+
+@pytest.mark.parametrize("pass_gates", [1, 2, 3, 4])
+@pytest.mark.parametrize("block", [3, 4, 5, 6, 9])
+def test_scale_blocks_stay_in_neighbouring_lanes(P, block, pass_gates):
+    # the kernel takes a block's maximum over the lowest block - 3 lane bits
+    for seed in range(-1, 10):
+        n = 16 if seed < 0 else 14 + seed % 3
+        circ = SWAPPED_BLOCK if seed < 0 else circuit(n, 12, seed, False)
+        got, rep = P.run(n, circ, "enc2", low=max(3, block), pass_gates=pass_gates, block=block)
+        assert rep.blocks == 0 and rep.races == 0 and rep.misplaced == 0, seed
+        assert np.linalg.norm(got - sv.run_circuit(n, circ)) <= 8.0 * EPS["c64"] * len(circ)

@@ -81,3 +81,22 @@ def test_flips_within_a_group_of_codes(J, flips):
     before = oenc2.decode(codes, scales, block)
     want = before[np.arange(1 << n) ^ mask]
     assert np.array_equal(oenc2.decode(codes2, scales2, block), want)
+
+
+@pytest.mark.parametrize("pass_gates", [1, 3])
+@pytest.mark.parametrize("block", [4, 5])
+def test_codes_with_short_chunks(J, block, pass_gates):
+    # chunks of one scale block and passes of few gates: relabel swaps reach the
+    # block's own bits
+    print("CASE enc2 short chunks", block, pass_gates, flush=True)
+    H, C = W.OP_H, W.OP_CNOT
+    swapped = W.concat(W.gate(H, 1), W.gate(C, 14, 5), W.gate(H, 11), W.gate(C, 15, 12), W.gate(C, 6, 7),
+                       W.gate(C, 0, 10), W.gate(C, 2, 9), W.gate(H, 1))
+    opts = dict(mode="tile", low_bits=block, pass_gates=pass_gates)
+    for circ in (swapped, W.concat(*[W.gate(H, q) for q in range(0, 16, 3)], swapped), general(16, 40 + block)):
+        got, layout, passes = state(J, 16, block, circ, **opts)
+        want, layout3, passes3 = state(J, 16, block, circ, fuse_k=3, **opts)
+        assert layout == layout3 and passes == passes3
+        flip = 8 * len(circ) * 127 * 2.0 ** -24
+        bound = np.sqrt(passes * flip) * 6 / 127
+        assert np.linalg.norm(got - want) < bound * np.linalg.norm(want)
