@@ -292,7 +292,7 @@ uint32_t pick_regs(const std::vector<AbsorbMask>& rem, int tb, int K, uint32_t a
   return P;
 }
 
-enum EKind { E_ROT, E_DENSE, E_SWAP, E_PHASE, E_PAIR, E_NEG, E_SIGNS };
+enum EKind { E_ROT, E_DENSE, E_SWAP, E_PHASE, E_PAIR, E_NEG, E_SIGNS, E_SCALE };
 
 struct EOp {  // an op of a stage before it is put into layers
   EKind kind = E_ROT;
@@ -566,13 +566,19 @@ void settle_frame(Frame& fr, StagePlan& st, int tb, int K) {
 }
 
 // Scalar parts of the pass's gates: their product goes into the matrix of a
-// rotation without outer signs or phases (any op can carry a scalar), as a
-// dense 2x2; on the way it is kept within 2^+-20 of what the registers hold.
+// rotation without outer signs or phases, as a dense 2x2, or (none there) into
+// an op of its own.  On the way it is kept within 2^+-20 of what the registers
+// hold (a rotation [[1, -t], [t, 1]] enlarges them by up to sqrt(2)); where
+// every rotation has outer signs or phases, an op of its own does that from
+// 2^+-24 on: a scalar left over a pass of 300 such rotations would round to
+// zero in FP32.
 void place_scalars(std::vector<StagePlan>& st) {
   C run{1, 0};
-  EOp* last = nullptr;
+  int at_stage = -1, at_op = 0;  // the last op that can carry a scalar
   auto carry = [](EOp* e, C s) {
-    if (e->kind == E_ROT) {
+    if (e->kind == E_SCALE) {
+      e->ph = mul(e->ph, s);
+    } else if (e->kind == E_ROT) {
       e->kind = E_DENSE;
       e->m[0] = s;
       e->m[1] = mul(s, C{-e->t * e->ph.re, -e->t * e->ph.im});
@@ -582,30 +588,38 @@ void place_scalars(std::vector<StagePlan>& st) {
       for (C& z : e->m) z = mul(s, z);
     }
   };
-  for (StagePlan& s : st) {
-    run = mul(run, s.scal);
-    for (EOp& e : s.ops) {
-      run = mul(run, e.lam);
-      if ((e.kind == E_ROT && e.plain()) || e.kind == E_DENSE) {
-        last = &e;
-        const double a = absv(run);
-        if (a > 0x1p20 || a < 0x1p-20) {
-          carry(last, run);
-          run = C{1, 0};
-        }
+  for (size_t i = 0; i < st.size(); ++i) {
+    std::vector<EOp>& ops = st[i].ops;
+    run = mul(run, st[i].scal);
+    for (size_t k = 0; k < ops.size(); ++k) {
+      run = mul(run, ops[k].lam);
+      const double a = absv(run);
+      if ((ops[k].kind == E_ROT && ops[k].plain()) || ops[k].kind == E_DENSE) {
+        at_stage = (int)i;
+        at_op = (int)k;
+        if (a <= 0x1p20 && a >= 0x1p-20) continue;
+        carry(&ops[k], run);
+      } else {
+        if (a <= 0x1p24 && a >= 0x1p-24) continue;
+        EOp e;
+        e.kind = E_SCALE;
+        e.ph = run;
+        ops.insert(ops.begin() + (std::ptrdiff_t)++k, std::move(e));
+        at_stage = (int)i;
+        at_op = (int)k;
       }
+      run = C{1, 0};
     }
   }
   if (one(run)) return;
-  if (!last) {
+  if (at_stage < 0) {
     EOp e;
-    e.kind = E_DENSE;
-    e.m[0] = e.m[3] = C{1, 0};
-    e.m[1] = e.m[2] = C{0, 0};
+    e.kind = E_SCALE;
+    at_stage = (int)st.size() - 1;
+    at_op = (int)st.back().ops.size();
     st.back().ops.push_back(std::move(e));
-    last = &st.back().ops.back();
   }
-  carry(last, run);
+  carry(&st[at_stage].ops[at_op], run);
 }
 
 // Puts a stage's ops into layers and appends them to the plan as device
@@ -708,7 +722,8 @@ void emit_layers(const StagePlan& p, int nthr, BlkStage base, BlkPlan* plan) {
   for (const EOp& e : p.ops) {
     const uint32_t jb = 1u << e.J;
     const uint32_t u = e.kind == E_ROT || e.kind == E_NEG || e.kind == E_DENSE ? jb
-                       : e.kind == E_SWAP ? jb | e.cm : e.cm;
+                       : e.kind == E_SWAP ? jb | e.cm
+                       : e.kind == E_SCALE ? (1u << kBlkRegs) - 1 : e.cm;
     int l = 0;
     for (int j = 0; j < kBlkRegs; ++j)
       if ((u >> j) & 1) l = std::max(l, level[j]);
@@ -1071,6 +1086,33 @@ double plan_ms(const BlkPlan& p, bool fp64) {
   return total;
 }
 
+// Whether every op's coefficients can be held in the state's precision: the
+// largest of an op's neither overflows nor vanishes, nor comes near it (the
+// amplitudes take the ops one by one).  Matrices far from unitary ones may not
+// be; the fused passes multiply them in FP64 first.
+bool in_range(const BlkPlan& p, bool fp64) {
+  const double most = fp64 ? 0x1p500 : 0x1p60, least = 1.0 / most;
+  const auto ok = [&](double x) { return x >= least && x <= most; };
+  for (const BlkLayer<double>& y : p.layers)
+    for (int j = 0; j < kBlkRegs; ++j)
+      if ((y.flags & (BLK_ROT << j)) && !(ok(std::hypot(y.c[3 * j], y.c[3 * j + 1])) && std::isfinite(y.c[3 * j + 2])))
+        return false;
+  for (size_t o = 0; o < p.ops.size(); ++o) {
+    const uint32_t kind = p.ops[o].kind;
+    const double* c = &p.ocoef[8 * o];
+    if ((kind == 0 || (kind & (blk_phase() * 127))) && !ok(std::hypot(c[0], c[1]))) return false;
+    if (kind & (blk_dense(0) * 15)) {
+      double m = 0.0;
+      for (int i = 0; i < 8; ++i) {
+        if (!std::isfinite(c[i])) return false;
+        m = std::max(m, std::fabs(c[i]));
+      }
+      if (!ok(m)) return false;
+    }
+  }
+  return true;
+}
+
 }  // namespace
 
 // The qubits of the gates alone, for the tile selection.  strict: a gate is
@@ -1118,7 +1160,7 @@ bool block_build(const BlkSchedule& bs, const std::vector<BlkGate>& bg, bool fp6
     for (int t : sched.taken[i]) mine.push_back(bg[sched.tsrc.empty() ? t : sched.tsrc[t]]);
     plan_block_pass(sched.passes[i].g, mine, sched.taken[i], src, fp64, std::min(bs.low, fp64 ? 5 : 6), plan);
   }
-  return true;
+  return in_range(*plan, fp64);
 }
 
 bool block_tile_plan(const TilePlan& tp, int block_bits, BlkPlan* plan) {
@@ -1138,7 +1180,7 @@ bool block_tile_plan(const TilePlan& tp, int block_bits, BlkPlan* plan) {
     }
     plan_block_pass(ps.g, bg, taken, where, false, 0, plan, block_bits);
   }
-  return true;
+  return in_range(*plan, false);
 }
 
 void append_plan(const BlkPlan& p, BlkPlan* all) {

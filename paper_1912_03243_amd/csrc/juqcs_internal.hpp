@@ -506,12 +506,13 @@ struct BlkSchedule {
 };
 void block_schedule(int n, int L, int b, const std::vector<BlkGate>& bg, int max_take, bool relabel, bool strict,
                     BlkSchedule* out);
-// Appends the schedule's passes with bg's values; false when bg has another shape.
+// Appends the schedule's passes with bg's values; false when bg has another shape
+// or coefficients that the precision cannot hold.
 bool block_build(const BlkSchedule& bs, const std::vector<BlkGate>& bg, bool fp64, BlkPlan* plan);
 
 // The passes of a tile plan of two-byte amplitudes (scale blocks of 2^block_bits)
 // as register-resident programs: the same gates between the same encodings.
-// False if a pass has gates that they do not do.
+// False if a pass has gates that they do not do, or coefficients out of range.
 bool block_tile_plan(const TilePlan& tp, int block_bits, BlkPlan* plan);
 
 // Byte image of a plan for the device (reals in the state's precision) and

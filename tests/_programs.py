@@ -6,6 +6,8 @@ import subprocess
 
 import numpy as np
 
+from paper_1912_03243_amd import workloads as W
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1912_03243_amd", "csrc")
 
@@ -47,3 +49,19 @@ class Programs:
                                   ct.c_void_p(v.ctypes.data), ct.byref(rep))
         assert rc in (0, 1), rc
         return (v if rc == 0 else None), rep
+
+
+def signed_rotations(count, qubits, n, theta=None):
+    """Rotations that all carry a sign or a phase of a qubit that does not rotate any more."""
+    recs = [W.gate(W.OP_H, q) for q in range(4, n)]
+    for i in range(count):
+        for q in range(qubits):
+            other = 4 + (i + q) % (n - 4)
+            recs.append(W.gate(W.OP_H, q))
+            recs.append(W.gate(W.OP_CZ, q, other) if theta is None else W.gate(W.OP_CP, q, other, theta=theta))
+    return W.concat(*recs)
+
+
+# (dtype, qubits, repetitions, qubits that rotate, angle of the controlled phases or None: CZ)
+SIGNED = [("c64", 13, 300, 1, None), ("c64", 13, 300, 1, 0.3), ("c64", 14, 300, 2, None), ("c64", 13, 100, 4, 0.3),
+          ("c128", 12, 2300, 1, None), ("c128", 13, 1200, 1, 0.3)]

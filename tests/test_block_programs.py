@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 
 import _programs
+from _programs import SIGNED, signed_rotations
 from oracle import statevector as sv
 from paper_1912_03243_amd import workloads as W
 from test_gpu_blocks import EPS, circuit, growth
@@ -53,3 +54,46 @@ def test_scale_blocks_stay_in_neighbouring_lanes(P, block, pass_gates):
         got, rep = P.run(n, circ, "enc2", low=max(3, block), pass_gates=pass_gates, block=block)
         assert rep.blocks == 0 and rep.races == 0 and rep.misplaced == 0, seed
         assert np.linalg.norm(got - sv.run_circuit(n, circ)) <= 8.0 * EPS["c64"] * len(circ)
+
+
+@pytest.mark.parametrize("dtype, n, count, qubits, theta", SIGNED)
+def test_scalars_of_signed_rotations(P, dtype, n, count, qubits, theta):
+    # [[1, -t], [t, 1]] enlarges the state by sqrt(1 + t^2): the scalars cannot
+    # wait for a rotation without signs and phases
+    circ = signed_rotations(count, qubits, n, theta)
+    got, rep = P.run(n, circ, dtype)
+    want = sv.run_circuit(n, circ)
+    assert np.linalg.norm(got - want) <= 8.0 * EPS[dtype] * len(circ)
+    assert 2.0 ** -50 <= rep.least and rep.most <= 2.0 ** 30
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_matrices_far_from_unitary(P, dtype):
+    # diagonals and rotations of very different sizes: planned so that the
+    # coefficients hold them, or left to the fused passes
+    left = 0
+    for seed in range(60):
+        rng = np.random.default_rng([seed, 77])
+        n, recs = 13, []
+        most = 10.0 ** [2, 12, 25][seed % 3]
+        for _ in range(40):
+            a, b = (int(x) for x in rng.choice(n, 2, replace=False))
+            size = float(most ** rng.uniform(-1, 1))
+            m = [np.diag([1.0, size * np.exp(1j * rng.uniform(0, 6))]), W.haar_u2(rng) @ np.diag([1.0, size]),
+                 np.diag([size, 1.0]) @ W.haar_u2(rng), size * W.haar_u2(rng)][int(rng.integers(4))]
+            recs.append(W.gate(W.OP_U, a, u=m) if rng.random() < 0.3 else
+                        W.gate(W.OP_X, a) if rng.random() < 0.3 else W.gate(W.OP_CNOT, a, b))
+        circ = W.concat(*recs)
+        psi = sv.run_circuit(n, W.concat(*[W.gate(W.OP_U, q, u=W.haar_u2(rng)) for q in range(n)]))
+        if dtype == "c64":
+            psi = psi.astype(np.complex64).astype(np.complex128)
+        got, rep = P.run(n, circ, dtype, psi=psi)
+        if got is None:
+            left += 1
+            continue
+        want = sv.run_circuit(n, circ, psi=psi.copy())
+        limit = np.finfo(np.float32 if dtype == "c64" else np.float64)
+        if np.abs(want).max() > limit.max / 2 ** 10 or np.linalg.norm(want) < limit.tiny * 2 ** 40:
+            continue  # outside what the amplitudes can hold
+        assert np.linalg.norm(got - want) <= 8.0 * EPS[dtype] * len(circ) * growth(circ), seed
+    assert left < 60

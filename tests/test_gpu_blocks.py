@@ -14,6 +14,7 @@ gates' largest singular values; it grows at most linearly in the gates.
 import numpy as np
 import pytest
 
+from _programs import SIGNED, signed_rotations
 from oracle import decomposition as odec
 from oracle import statevector as sv
 from paper_1912_03243_amd import workloads as W
@@ -179,3 +180,24 @@ def test_branch_tile_sizes(J, nloc, per_run, group):
     got = J.juqcs_branch_amplitudes(n, circ, side, z, group_size=group)
     want = odec.branch_amplitudes(n, circ, side, z)
     assert np.max(np.abs(got - want)) / np.abs(want).max() < 1e-5
+
+
+@pytest.mark.parametrize("dtype, n, count, qubits, theta", SIGNED)
+def test_scalars_of_signed_rotations(J, dtype, n, count, qubits, theta):
+    # rotations that all carry signs or phases: their scalars would leave FP32's
+    # (and FP64's) range over a pass
+    print("CASE blocks-signed", dtype, n, count, qubits, theta, flush=True)
+    circ = signed_rotations(count, qubits, n, theta)
+    want = sv.run_circuit(n, circ)
+    bound = 8.0 * EPS[dtype] * len(circ)
+    with J.State(n, dtype) as s:
+        s.init(0)
+        s.run(circ, mode="tile")
+        assert np.linalg.norm(s.state_vector() - want) <= bound
+    if dtype == "c64":
+        b = J.Batch([(n, circ)])
+        b.run()
+        b.wait()
+        assert b.fusion()[0] == 1
+        assert np.linalg.norm(b.state_vector(0) - want) <= bound
+        b.close()
