@@ -15,28 +15,35 @@ namespace juqcs {
 
 namespace {
 
-using C = cplx<double>;
+using R = BlkReal;
+using C = cplx<R>;
 
+C widen(cplx<double> a) { return C{a.re, a.im}; }
 C mul(C a, C b) { return C{a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
-C div(C a, C b) {
-  // scaled by the larger part of b (Smith), so that |b|^2 cannot overflow
-  if (std::fabs(b.re) >= std::fabs(b.im)) {
-    const double r = b.im / b.re, d = b.re + b.im * r;
-    return C{(a.re + a.im * r) / d, (a.im - a.re * r) / d};
-  }
-  const double r = b.re / b.im, d = b.re * r + b.im;
-  return C{(a.re * r + a.im) / d, (a.im * r - a.re) / d};
+// a *= b, where b is 1 most of the time
+void join(C* a, const C& b) {
+  if (b.re != 1 || b.im != 0) *a = mul(*a, b);
 }
-double absv(C a) { return std::hypot(a.re, a.im); }
-bool zero(C a) { return a.re == 0.0 && a.im == 0.0; }
-bool one(C a) { return a.re == 1.0 && a.im == 0.0; }
-bool finite(C a) { return std::isfinite(a.re) && std::isfinite(a.im); }
+// (the exponents of the wider type leave room for the squares)
+R norm2(C a) { return a.re * a.re + a.im * a.im; }
+// a conj(b) f
+C times(C a, C b, R f) { return C{(a.re * b.re + a.im * b.im) * f, (a.im * b.re - a.re * b.im) * f}; }
+C div(C a, C b) { return times(a, b, 1 / norm2(b)); }
+bool zero(C a) { return a.re == 0 && a.im == 0; }
+// Equal up to what an FP64 value of that size cannot tell apart.
+bool equal(C a, R re) { return std::fabs(a.re - re) <= 0x1p-58L && std::fabs(a.im) <= 0x1p-58L; }
+bool one(C a) { return equal(a, 1); }
+bool minus_one(C a) { return equal(a, -1); }
+// Neither a nor 1 / a overflows in FP64 (zero does).
+bool ranged(C a) {
+  const R n = norm2(a);
+  return n >= 0x1p-2040L && n <= 0x1p2040L;
+}
 
 // Collects the single-qubit gates of each qubit until a gate that does not
 // commute with them, then emits them as one gate.
 struct Rewriter {
-  double tol;
-  bool f32;   // coefficients will be rounded to FP32
+  R tol;
   bool keep;  // phases of 1 too, so that the gates' kinds do not depend on their values
   std::vector<BlkGate>* out;
   struct Open {
@@ -45,16 +52,27 @@ struct Rewriter {
   };
   std::vector<Open> open;
 
-  void single(int q, const C* u) {
+  void single(int q, const cplx<double>* u) {
     Open& w = open[q];
     if (!w.any) {
       w.any = true;
-      for (int i = 0; i < 4; ++i) w.m[i] = u[i];
+      for (int i = 0; i < 4; ++i) w.m[i] = widen(u[i]);
+      return;
+    }
+    if (zero(w.m[1]) && zero(w.m[2])) {  // a diagonal that an earlier gate left
+      const C x = w.m[0], y = w.m[3];
+      for (int i = 0; i < 4; ++i) {
+        const C z = widen(u[i]);
+        w.m[i] = i & 1 ? mul(z, y) : x.re == 1 && x.im == 0 ? z : mul(z, x);
+      }
       return;
     }
     C r[4];
     for (int i = 0; i < 2; ++i)
-      for (int j = 0; j < 2; ++j) r[2 * i + j] = cmad(u[2 * i + 1], w.m[2 + j], mul(u[2 * i], w.m[j]));
+      for (int j = 0; j < 2; ++j) {
+        const C x = mul(widen(u[2 * i]), w.m[j]), y = mul(widen(u[2 * i + 1]), w.m[2 + j]);
+        r[2 * i + j] = C{x.re + y.re, x.im + y.im};
+      }
     for (int i = 0; i < 4; ++i) w.m[i] = r[i];
   }
 
@@ -68,66 +86,75 @@ struct Rewriter {
     out->push_back(g);
   }
 
+  // The rotation form needs b c / (a d) real and negative (t^2 is its size).
+  // Turns the entries until it is, the small ones most: by angles in
+  // proportion to 1 / |entry|^2, the least change of the matrix (n2: |a|^2,
+  // |b|^2, ..).  False where an entry would change by more than the root of
+  // miss2.  (A pair of zeros has the form.)
+  static bool fit(C* m, const R* n2, R miss2) {
+    if ((zero(m[1]) && zero(m[2])) || (zero(m[0]) && zero(m[3]))) return true;
+    const C ad = mul(m[0], m[3]), bc = mul(m[1], m[2]);
+    const R re = -(bc.re * ad.re + bc.im * ad.im), im = bc.re * ad.im - bc.im * ad.re;
+    if (!(re > 0)) return false;
+    if (im == 0) return true;
+    // weights 1 / n2, over their sum, without a division each
+    const R ad2 = n2[0] * n2[3], bc2 = n2[1] * n2[2];
+    const R w[4] = {n2[3] * bc2, n2[2] * ad2, n2[1] * ad2, n2[0] * bc2};
+    const R off = im / (re * (w[0] + w[1] + w[2] + w[3]));
+    for (int i = 0; i < 4; ++i)
+      if (!(off * off * w[i] * w[i] * n2[i] <= miss2)) return false;
+    for (int i = 0; i < 4; ++i) {
+      const R turn = i == 0 || i == 3 ? off * w[i] : -off * w[i];
+      m[i] = C{m[i].re - turn * m[i].im, m[i].im + turn * m[i].re};
+    }
+    return true;
+  }
+
   // Emits what is open on qubit q.  all = false: a diagonal may stay open
   // (the next gate on q commutes with diagonals).
   void flush(int q, bool all) {
     Open& w = open[q];
     if (!w.any) return;
-    const C a = w.m[0], b = w.m[1], c = w.m[2], d = w.m[3];
-    if (zero(b) && zero(c)) {
+    C m[4] = {w.m[0], w.m[1], w.m[2], w.m[3]};
+    R n2[4];
+    for (int i = 0; i < 4; ++i) n2[i] = norm2(m[i]);
+    const R miss2 = tol * tol * std::max(std::max(n2[0], n2[1]), std::max(n2[2], n2[3]));
+    if (zero(m[1]) && zero(m[2])) {
       if (!all) return;
       w.any = false;
-      const C ph = zero(a) ? C{0, 0} : div(d, a);
-      if (!zero(a) && finite(ph) && finite(div(C{1, 0}, ph))) {
-        push_phase(q, a, ph);
-        return;
-      }
-      dense(q, w.m);
+      const C ph = zero(m[0]) ? C{0, 0} : div(m[3], m[0]);
+      if (ranged(m[0]) && ranged(ph)) push_phase(q, m[0], ph);
+      else dense(q, w.m);
       return;
     }
-    // diag(lam, mu) R diag(1, p) with R = [[1, -t], [t, 1]] (|a| >= |c|) or
-    // [[t, -1], [1, t]]: three entries are met by construction, the fourth
-    // tells whether the matrix has this form
-    const double na = absv(a), nc = absv(c);
-    const double scale = std::max(std::max(na, nc), std::max(absv(b), absv(d)));
+    // diag(lam, mu) R diag(1, p) with R = [[1, -t], [t, 1]] (|a d| >= |b c|) or
+    // [[t, -1], [1, t]]
     BlkGate g;
     g.kind = BlkGate::ROT;
     g.q[0] = q;
-    C lam, mu, miss;
-    bool ok = false;
-    g.formb = nc > na;
-    if (!g.formb && nc > 0.0) {
-      g.t = nc / na;
-      lam = a;
-      mu = C{c.re / g.t, c.im / g.t};
-      g.ph = div(d, mu);
-      const C x = mul(lam, g.ph);
-      miss = C{b.re + g.t * x.re, b.im + g.t * x.im};
-      ok = g.t > 0.0;
-    } else if (g.formb) {
-      g.t = na / nc;
-      mu = c;
-      lam = g.t > 0.0 ? C{a.re / g.t, a.im / g.t} : mu;
-      g.ph = div(C{-b.re, -b.im}, lam);
-      const C x = mul(mu, g.ph);
-      miss = C{d.re - g.t * x.re, d.im - g.t * x.im};
-      ok = true;
-    }
-    if (ok) {
-      const C rest = div(mu, lam);
-      ok = finite(lam) && finite(g.ph) && finite(rest) && finite(div(C{1, 0}, g.ph)) && !zero(lam) &&
-           absv(miss) <= tol * scale;
-      if (ok) {
-        // the rounded t with the scalar that keeps |lam|^2 (1 + t^2): a rotation
-        // by a slightly other angle, instead of one that changes the norm
-        // (4096 circuits of up to 2000 gates: norms off by 1.4e-6, 2.0e-6 without)
-        const double t = f32 ? (double)(float)g.t : g.t;
-        if (t != g.t) {
-          const double f = std::sqrt((1.0 + g.t * g.t) / (1.0 + t * t));
-          lam = C{lam.re * f, lam.im * f};
-          g.t = t;
-        }
-        g.lam = lam;
+    const R ad2 = n2[0] * n2[3], bc2 = n2[1] * n2[2];
+    g.formb = bc2 > ad2;
+    if (fit(m, n2, miss2)) {
+      // (one division for two quotients: they are slow in this type)
+      C rest;
+      if (!g.formb) {  // mu = c / t, p = d / mu, rest = mu / a
+        g.t = std::sqrt(std::sqrt(bc2 / ad2));
+        g.lam = m[0];
+        const R ta2 = g.t * norm2(m[0]), c2 = norm2(m[2]), f = 1 / (ta2 * c2);
+        g.ph = times(m[3], m[2], g.t * ta2 * f);
+        rest = times(m[2], m[0], c2 * f);
+      } else if (zero(m[0])) {
+        g.lam = m[2];
+        g.ph = times(C{-m[1].re, -m[1].im}, m[2], 1 / norm2(m[2]));
+        rest = C{1, 0};
+      } else {  // lam = a / t, p = -b / lam, rest = c / lam
+        g.t = std::sqrt(std::sqrt(ad2 / bc2));
+        const R a2 = norm2(m[0]), f = 1 / (g.t * a2), h = g.t * g.t * f;
+        g.lam = C{m[0].re * a2 * f, m[0].im * a2 * f};
+        g.ph = times(C{-m[1].re, -m[1].im}, m[0], h);
+        rest = times(m[2], m[0], h);
+      }
+      if (ranged(g.lam) && ranged(g.ph) && ranged(rest)) {
         out->push_back(g);
         w.m[0] = C{1, 0};
         w.m[1] = w.m[2] = C{0, 0};
@@ -157,9 +184,9 @@ struct Rewriter {
 
 bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<BlkGate>* out, bool keep) {
   out->clear();
+  out->reserve(gates.size() + n);
   Rewriter rw;
   rw.tol = tol;
-  rw.f32 = tol > block_tol(true);
   rw.keep = keep;
   rw.out = out;
   rw.open.resize(n);
@@ -168,7 +195,9 @@ bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<
       rw.single(g.q[0], g.m);
       continue;
     }
-    const C* m = g.m;  // index b_q0 + 2 b_q1
+    const cplx<double>* m = g.m;  // index b_q0 + 2 b_q1
+    const auto zero = [](cplx<double> a) { return a.re == 0.0 && a.im == 0.0; };
+    const auto one = [](cplx<double> a) { return a.re == 1.0 && a.im == 0.0; };
     BlkGate b;
     b.q[0] = g.q[0];
     b.q[1] = g.q[1];
@@ -177,9 +206,9 @@ bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<
       if (i != 0 && i != 5 && i != 10 && i != 15 && !zero(m[i])) diag = false;
       if (i != 0 && i != 10 && i != 7 && i != 13 && !zero(m[i])) cnot = false;
     }
-    if (diag && finite(div(C{1, 0}, m[15]))) {
+    if (diag && ranged(widen(m[15]))) {
       b.kind = BlkGate::CPHASE;
-      b.ph = m[15];
+      b.ph = widen(m[15]);
       rw.flush(b.q[0], false);
       rw.flush(b.q[1], false);
     } else if (cnot) {
@@ -301,8 +330,8 @@ struct EOp {  // an op of a stage before it is put into layers
   uint32_t tmask = 0;   // tile-local bits (thread bits of the stage)
   uint64_t gmask = 0;
   C ph{1, 0};
-  double t = 0.0;
-  C m[4];
+  R t = 0;
+  std::vector<C> m;     // DENSE: the matrix
   C lam{1, 0};
   struct Col {          // phase where an outer bit is set
     C ph;
@@ -410,7 +439,7 @@ struct Emitter {
 
   void take_wait(EOp& e, int j) {
     Wait& w = wait[j];
-    e.ph = mul(e.ph, w.ph);
+    join(&e.ph, w.ph);
     e.tmask = w.tmask;
     e.gmask = w.gmask;
     e.col = std::move(w.col);
@@ -462,10 +491,8 @@ struct Emitter {
         const C p = wait[j].ph;  // a plain phase joins the matrix's second column
         wait[j] = Wait();
         e.kind = E_DENSE;
-        e.m[0] = f0 ? g.m[3] : g.m[0];
-        e.m[1] = mul(f0 ? g.m[2] : g.m[1], p);
-        e.m[2] = f0 ? g.m[1] : g.m[2];
-        e.m[3] = mul(f0 ? g.m[0] : g.m[3], p);
+        if (f0) e.m = {g.m[3], mul(g.m[2], p), g.m[1], mul(g.m[0], p)};
+        else e.m = {g.m[0], mul(g.m[1], p), g.m[2], mul(g.m[3], p)};
         st.ops.push_back(std::move(e));
         break;
       }
@@ -482,7 +509,7 @@ struct Emitter {
         if (f0) phase_on(q1, f1 ? ip : p);
         if (f1) phase_on(q0, f0 ? ip : p);
         const C pp = f0 != f1 ? ip : p;
-        const bool neg = pp.re == -1.0 && pp.im == 0.0;
+        const bool neg = minus_one(pp);
         const int j1 = jof(q1);
         if (j >= 0 && j1 >= 0) {
           e.kind = neg ? E_PAIR : E_PHASE;
@@ -535,7 +562,7 @@ void settle_frame(Frame& fr, StagePlan& st, int tb, int K) {
     int j = -1;
     for (int i = 0; i < K; ++i)
       if (st.reg[i] == b) j = i;
-    if (p.re == -1.0 && p.im == 0.0) {
+    if (minus_one(p)) {
       if (j >= 0) s.cm |= 1u << j;
       else s.tmask |= 1u << b;
     } else {
@@ -557,12 +584,45 @@ void settle_frame(Frame& fr, StagePlan& st, int tb, int K) {
   for (int b = 0; b < 64; ++b) {
     const C p = fr.outer[b];
     if (one(p)) continue;
-    if (p.re == -1.0 && p.im == 0.0) s.gmask |= uint64_t(1) << b;
+    if (minus_one(p)) s.gmask |= uint64_t(1) << b;
     else outer.col.push_back({p, 64 + b});
   }
   if (!outer.col.empty()) rest.push_back(std::move(outer));
   if (s.cm || s.tmask || s.gmask) st.ops.push_back(std::move(s));
   for (EOp& e : rest) st.ops.push_back(std::move(e));
+}
+
+R rounded(R x, bool fp64) { return fp64 ? (R)(double)x : (R)(float)(double)x; }
+
+// Rounds the phases and tangents of the ops to the state's precision.  What the
+// rounding multiplies a half (or quarter) of the state by is divided out of the
+// whole on average, with the scalars of the pass: left to itself, each rounding
+// changes the norm and turns that part of the state.
+void round_phases(std::vector<StagePlan>& st, bool fp64) {
+  for (StagePlan& s : st)
+    for (EOp& e : s.ops) {
+      const auto phase = [&](C* p, double share) {
+        const C r{rounded(p->re, fp64), rounded(p->im, fp64)};
+        const double x = (double)(p->re - r.re), y = (double)(p->im - r.im);  // far below r: to first order
+        const double u = (double)r.re, v = (double)r.im, f = share / (u * u + v * v);
+        if ((x == 0.0 && y == 0.0) || !std::isfinite(f)) return;
+        e.lam = mul(e.lam, C{1 + (R)((x * u + y * v) * f), (R)((y * u - x * v) * f)});
+        *p = r;
+      };
+      if (e.kind != E_ROT && e.kind != E_PHASE) continue;
+      const double share = e.kind == E_ROT ? 0.5 : 1.0 / (1 << __builtin_popcount(e.cm));
+      phase(&e.ph, share);
+      for (EOp::Col& c : e.col) phase(&c.ph, share / 2);
+      if (e.kind == E_ROT) {
+        const R t = rounded(e.t, fp64);
+        if (t != e.t) {
+          const double u = (double)t;
+          const R f = 1 + (R)((double)(e.t - t) * u / (1.0 + u * u));
+          e.lam = C{e.lam.re * f, e.lam.im * f};
+          e.t = t;
+        }
+      }
+    }
 }
 
 // Scalar parts of the pass's gates: their product goes into the matrix of a
@@ -580,27 +640,24 @@ void place_scalars(std::vector<StagePlan>& st) {
       e->ph = mul(e->ph, s);
     } else if (e->kind == E_ROT) {
       e->kind = E_DENSE;
-      e->m[0] = s;
-      e->m[1] = mul(s, C{-e->t * e->ph.re, -e->t * e->ph.im});
-      e->m[2] = C{s.re * e->t, s.im * e->t};
-      e->m[3] = mul(s, e->ph);
+      e->m = {s, mul(s, C{-e->t * e->ph.re, -e->t * e->ph.im}), C{s.re * e->t, s.im * e->t}, mul(s, e->ph)};
     } else {
       for (C& z : e->m) z = mul(s, z);
     }
   };
   for (size_t i = 0; i < st.size(); ++i) {
     std::vector<EOp>& ops = st[i].ops;
-    run = mul(run, st[i].scal);
+    join(&run, st[i].scal);
     for (size_t k = 0; k < ops.size(); ++k) {
-      run = mul(run, ops[k].lam);
-      const double a = absv(run);
+      join(&run, ops[k].lam);
+      const double a = (double)norm2(run);
       if ((ops[k].kind == E_ROT && ops[k].plain()) || ops[k].kind == E_DENSE) {
         at_stage = (int)i;
         at_op = (int)k;
-        if (a <= 0x1p20 && a >= 0x1p-20) continue;
+        if (a <= 0x1p40 && a >= 0x1p-40) continue;
         carry(&ops[k], run);
       } else {
-        if (a <= 0x1p24 && a >= 0x1p-24) continue;
+        if (a <= 0x1p48 && a >= 0x1p-48) continue;
         EOp e;
         e.kind = E_SCALE;
         e.ph = run;
@@ -652,7 +709,7 @@ void emit_layers(const StagePlan& p, int nthr, BlkStage base, BlkPlan* plan) {
   const auto push_cols = [&](const std::vector<EOp::Col>& col, int32_t* c0, int32_t* c1) {
     *c0 = (int32_t)plan->ops.size();
     for (const EOp::Col& c : col) {
-      const double v[2] = {c.ph.re, c.ph.im};
+      const double v[2] = {(double)c.ph.re, (double)c.ph.im};
       push_op(0, outside(c.q) ? 0u : tmask_of(1u << c.q), outside(c.q) ? uint64_t(1) << (c.q - 64) : 0, v, 2);
     }
     *c1 = (int32_t)plan->ops.size();
@@ -667,7 +724,7 @@ void emit_layers(const StagePlan& p, int nthr, BlkStage base, BlkPlan* plan) {
     base.misc_begin = (int32_t)plan->ops.size();
     for (size_t i = 0; i < cur.misc.size(); ++i) {
       const EOp& e = *cur.misc[i];
-      double c[8] = {e.ph.re, e.ph.im, 0, 0, 0, 0, 0, 0};
+      double c[8] = {(double)e.ph.re, (double)e.ph.im, 0, 0, 0, 0, 0, 0};
       uint32_t kind = 0;
       int lo = 0, hi = 0;  // register control bits
       if (e.cm) {
@@ -676,7 +733,7 @@ void emit_layers(const StagePlan& p, int nthr, BlkStage base, BlkPlan* plan) {
       }
       if (e.kind == E_DENSE) {
         kind = blk_dense(e.J);
-        for (int k = 0; k < 4; ++k) c[2 * k] = e.m[k].re, c[2 * k + 1] = e.m[k].im;
+        for (int k = 0; k < 4; ++k) c[2 * k] = (double)e.m[k].re, c[2 * k + 1] = (double)e.m[k].im;
       } else if (e.kind == E_SWAP) {
         kind = blk_swap(e.J, e.cm ? lo : e.J);
       } else if (e.kind == E_SIGNS) {
@@ -744,9 +801,9 @@ void emit_layers(const StagePlan& p, int nthr, BlkStage base, BlkPlan* plan) {
           y.y.flags |= (BLK_OUTER | BLK_COL) << e.J;
           y.col[e.J] = e.col;
         }
-        y.y.c[3 * e.J] = e.ph.re;
-        y.y.c[3 * e.J + 1] = e.ph.im;
-        y.y.c[3 * e.J + 2] = e.t;
+        y.y.c[3 * e.J] = (double)e.ph.re;
+        y.y.c[3 * e.J + 1] = (double)e.ph.im;
+        y.y.c[3 * e.J + 2] = (double)e.t;
         break;
       case E_PAIR:
         {
@@ -785,7 +842,7 @@ constexpr int kSlotBytes = 8;
 
 }  // namespace
 
-void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, const std::vector<int>& taken,
+void plan_block_pass(const TileGeom& tg, const std::vector<const BlkGate*>& gates, const std::vector<int>& taken,
                      const std::vector<Gate>& where, bool fp64, int low, BlkPlan* plan, int codes) {
   const int tb = tg.b, K = kBlkRegs, nthr = tb - K, lanes = std::min(6, nthr), waves = nthr - lanes;
   // tile-local bit of a physical bit, or 64 + its bit in the tile number
@@ -802,7 +859,7 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
   std::vector<int> rem;
   for (size_t i = 0; i < taken.size(); ++i) {
     Local l;
-    l.g = &gates[i];
+    l.g = gates[i];
     for (int j = 0; j < 2; ++j) l.q[j] = j < where[taken[i]].nq ? local_of[where[taken[i]].q[j]] : -1;
     gs.push_back(l);
     rem.push_back((int)i);
@@ -846,14 +903,16 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
   bool stuck = false;  // the last stage and exchange took nothing
   do {
     std::vector<AbsorbMask> rm;
-    uint64_t got = 0, sum = 0;
+    uint64_t got = 0, sum = 0, need = vec_dst;
     for (int i : rem) {
       rm.push_back(stage_mask(gs[i]));
       sum += rm.back().weight;
+      need |= rm.back().full;
     }
     const uint32_t first = st.empty() ? low_src : 0u;
     uint32_t P = pick_regs(rm, tb, K, all & ~first, &got, st.empty() ? vec_src : 0u);
-    if (!writes(P) && !st.empty()) {  // a last stage that needs no further exchange, if one finishes the pass
+    // a last stage that needs no further exchange, if one finishes the pass
+    if (!writes(P) && !st.empty() && !(need & low_dst) && __builtin_popcountll(need) <= K) {
       const uint32_t P2 = pick_regs(rm, tb, K, all & ~low_dst, &got, vec_dst);
       if (got == sum) P = P2;
     }
@@ -867,6 +926,7 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
     if (!stuck) leave_cnots(gs, &take, &keep);
     stuck = take.empty();
     order_regs(P, st.empty(), &s);
+    s.ops.reserve(take.size() + K);
     Emitter em(gs, fr, s, K);
     for (int i : take) em.gate(gs[i]);
     em.finish();
@@ -908,6 +968,7 @@ void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, cons
     st.push_back(std::move(s));
   }
   settle_frame(fr, st.back(), tb, K);
+  round_phases(st, fp64);
   place_scalars(st);
   // thread bits: wave bits kept from stage to stage while they can be, else
   // those that are needed again last; lane bits in an order whose LDS access
@@ -1156,8 +1217,9 @@ bool block_build(const BlkSchedule& bs, const std::vector<BlkGate>& bg, bool fp6
   const TileSchedule& sched = bs.sched;
   const std::vector<Gate>& src = sched.tgates.empty() ? bs.shape : sched.tgates;
   for (size_t i = 0; i < sched.passes.size(); ++i) {
-    std::vector<BlkGate> mine;
-    for (int t : sched.taken[i]) mine.push_back(bg[sched.tsrc.empty() ? t : sched.tsrc[t]]);
+    std::vector<const BlkGate*> mine;
+    mine.reserve(sched.taken[i].size());
+    for (int t : sched.taken[i]) mine.push_back(&bg[sched.tsrc.empty() ? t : sched.tsrc[t]]);
     plan_block_pass(sched.passes[i].g, mine, sched.taken[i], src, fp64, std::min(bs.low, fp64 ? 5 : 6), plan);
   }
   return in_range(*plan, fp64);
@@ -1173,12 +1235,14 @@ bool block_tile_plan(const TilePlan& tp, int block_bits, BlkPlan* plan) {
     if (!block_gates(ps.g.n, gates, block_tol(false), &bg)) return false;
     std::vector<Gate> where(bg.size());
     std::vector<int> taken(bg.size());
+    std::vector<const BlkGate*> mine(bg.size());
     for (size_t i = 0; i < bg.size(); ++i) {
+      mine[i] = &bg[i];
       taken[i] = (int)i;
       where[i].nq = bg[i].kind == BlkGate::CPHASE || bg[i].kind == BlkGate::CNOT ? 2 : 1;
       for (int j = 0; j < 2; ++j) where[i].q[j] = bg[i].q[j];
     }
-    plan_block_pass(ps.g, bg, taken, where, false, 0, plan, block_bits);
+    plan_block_pass(ps.g, mine, taken, where, false, 0, plan, block_bits);
   }
   return in_range(*plan, false);
 }

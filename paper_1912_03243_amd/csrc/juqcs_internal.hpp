@@ -456,16 +456,20 @@ void plan_tiles(int n, int L, int b, int block_bits, const std::vector<Gate>& ga
                 TilePlan* plan, int kin = 2, int max_mats = 0, int max_take = 0,
                 int max_mma = 0, bool relabel = false, std::vector<int>* final_pos = nullptr);
 
+// Host values of register-resident programs: eleven bits more than FP64, so that
+// what is rounded to a state's precision is rounded once.
+using BlkReal = long double;
+
 // A gate of a register-resident tile program (block.cpp).
 struct BlkGate {
   enum Kind { ROT, DENSE, PHASE1, CPHASE, CNOT } kind = DENSE;
   int q[2] = {0, -1};       // CNOT: control, target
   bool formb = false;       // ROT: lam R diag(1, ph), R = [[1, -t], [t, 1]] or (formb) [[t, -1], [1, t]]
                             // = [[1, t], [-t, 1]] [[0, -1], [1, 0]]
-  double t = 0.0;
-  cplx<double> ph{1, 0};    // phase of the set half (ROT, PHASE1) or quarter (CPHASE)
-  cplx<double> lam{1, 0};   // scalar factor (ROT, PHASE1)
-  cplx<double> m[4];        // DENSE
+  BlkReal t = 0;
+  cplx<BlkReal> ph{1, 0};   // phase of the set half (ROT, PHASE1) or quarter (CPHASE)
+  cplx<BlkReal> lam{1, 0};  // scalar factor (ROT, PHASE1)
+  cplx<BlkReal> m[4];       // DENSE
 };
 struct BlkPlan {
   std::vector<BlkPass> passes;
@@ -486,7 +490,7 @@ bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<
 // Appends one pass: geometry tg, its gates (on the physical bits of where[taken[i]]).
 // low: low bits that the first and the last stage keep on lanes (contiguous
 // accesses of 2^low amplitudes).
-void plan_block_pass(const TileGeom& tg, const std::vector<BlkGate>& gates, const std::vector<int>& taken,
+void plan_block_pass(const TileGeom& tg, const std::vector<const BlkGate*>& gates, const std::vector<int>& taken,
                      const std::vector<Gate>& where, bool fp64, int low, BlkPlan* plan, int codes = 0);
 // Plans a circuit as register-resident passes (arguments as plan_tiles);
 // false when it holds gates they do not take.
@@ -494,8 +498,8 @@ bool plan_block(int n, int L, int b, const std::vector<Gate>& gates, bool fp64, 
                 BlkPlan* plan, std::vector<int>* final_pos);
 
 // The relative miss of a matrix entry by the rotation form up to which a
-// gate is not kept dense: a few FP64 roundings, or far below an FP32 one.
-inline double block_tol(bool fp64) { return fp64 ? 2e-15 : 1e-9; }
+// gate is not kept dense: an FP64 rounding step, or far below an FP32 one.
+inline double block_tol(bool fp64) { return fp64 ? 0x1p-52 : 1e-9; }
 // Tile selection of a rewritten circuit; plans of circuits of the same shape
 // (kinds and qubits) can be built on it with other values.
 struct BlkSchedule {

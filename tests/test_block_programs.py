@@ -97,3 +97,58 @@ def test_matrices_far_from_unitary(P, dtype):
             continue  # outside what the amplitudes can hold
         assert np.linalg.norm(got - want) <= 8.0 * EPS[dtype] * len(circ) * growth(circ), seed
     assert left < 60
+
+
+def exact_state(n, circ):
+    """The circuit's product in extended precision, from the gates' FP64 entries."""
+    v = np.zeros(1 << n, np.clongdouble)
+    v[0] = 1
+    for g in circ:
+        a, b = int(g["q0"]), int(g["q1"])
+        if int(g["op"]) == W.OP_CZ:
+            idx = np.arange(1 << n)
+            v[((idx >> a) & (idx >> b) & 1) == 1] *= -1
+            continue
+        assert int(g["op"]) == W.OP_U
+        u = g["u"].reshape(2, 2, 2).astype(np.longdouble)
+        u = u[..., 0] + 1j * u[..., 1]
+        w = v.reshape(-1, 2, 1 << a)
+        w[:] = np.stack([u[0, 0] * w[:, 0] + u[0, 1] * w[:, 1], u[1, 0] * w[:, 0] + u[1, 1] * w[:, 1]], axis=1)
+    return v
+
+
+# A rounding's error has a standard deviation of about 0.41 2^-p of the value (p
+# = 53, 24).  A rotation rounds the set half three times and the other half
+# once, after its partner's, and its two or three coefficients once each, the
+# phase's shared by both halves: less than six roundings, independent of each
+# other.
+ROUNDING = {"c128": 0.41 * 2.0 ** -53, "c64": 0.41 * 2.0 ** -24}
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("n, layers", [(12, 20), (13, 40)])
+def test_a_rotation_is_a_few_roundings(P, n, layers, dtype):
+    errs = []
+    for seed in range(4):
+        circ = W.layered_brick(n, layers, seed=seed)
+        got, _ = P.run(n, circ, dtype)
+        errs.append(float(np.linalg.norm((got - exact_state(n, circ)).astype(complex))))
+    assert np.sqrt(np.mean(np.square(errs))) <= ROUNDING[dtype] * np.sqrt(6 * n * layers)
+
+
+@pytest.mark.parametrize("n, layers", [(12, 20), (13, 40)])
+def test_rounded_phases_keep_the_norm(P, n, layers):
+    # A phase rounded to FP32 changes the norm squared of the half that it acts on
+    # by one rounding times that half's weight, and the pass's scalar takes back
+    # what that is on average: what is left is in proportion to how far the
+    # weight is from 1/2.  Squared and summed over a qubit's layers that is the
+    # first rotation's 1 (on |0>) and less than 1 for the rest, while the qubits
+    # become entangled.  The few dense ops that carry the scalars round once more.
+    drift, left = [], 0
+    for seed in range(8):
+        circ = W.layered_brick(n, layers, seed=seed)
+        got, rep = P.run(n, circ, "c64")
+        exact = np.sum(np.abs(exact_state(n, circ)) ** 2)
+        drift.append(float(np.sum(np.abs(got.astype(np.clongdouble)) ** 2) / exact - 1))
+        left = max(left, 2 * n + rep.misc)
+    assert np.sqrt(np.mean(np.square(drift))) <= ROUNDING["c64"] * np.sqrt(left)
