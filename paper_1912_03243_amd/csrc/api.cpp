@@ -306,6 +306,10 @@ juqcs_status tile_gates(juqcs_state* st, const std::vector<Gate>& gates, int L, 
   if (kin > 4) return fail(JUQCS_ERR_ARG, "in-pass fusion width must be 1..4");
   if (pass_gates < -1) return fail(JUQCS_ERR_ARG, "pass_gates must be >= -1");
   if (relabel < -1 || relabel > 1) return fail(JUQCS_ERR_ARG, "relabel must be -1, 0 or 1");
+  if (gates.empty()) {  // (a register-resident plan of no gates writes the state as it is)
+    if (passes) *passes = 0;
+    return JUQCS_OK;
+  }
   const int cap = tile_mat_cap(st->dt, std::min(b, st->n));
   const int mcap = tile_mma_cap(st->dt, std::min(b, st->n));
   const int l = std::min(L, st->n);

@@ -201,3 +201,15 @@ def test_scalars_of_signed_rotations(J, dtype, n, count, qubits, theta):
         assert b.fusion()[0] == 1
         assert np.linalg.norm(b.state_vector(0) - want) <= bound
         b.close()
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64", "enc2"])
+@pytest.mark.parametrize("n", [10, 12, 14])
+def test_no_gates_no_pass(J, n, dtype):
+    print("CASE blocks-empty", n, dtype, flush=True)
+    with J.State(n, dtype) as s:
+        s.init(3)
+        for opts in (dict(), dict(mode="tile"), dict(mode="tile", relabel=-1)):
+            assert s.run(W.empty_circuit(0), **opts).passes == 0
+        got = s.state_vector()
+    assert got[3] == 1 and np.count_nonzero(got) == 1
