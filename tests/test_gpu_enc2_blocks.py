@@ -100,3 +100,22 @@ def test_codes_with_short_chunks(J, block, pass_gates):
         flip = 8 * len(circ) * 127 * 2.0 ** -24
         bound = np.sqrt(passes * flip) * 6 / 127
         assert np.linalg.norm(got - want) < bound * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("relabel", [-1, 0])
+def test_scales_up_to_the_largest(J, relabel):
+    # 2^14 amplitudes of 2^-7 times a factor that brings the scales next to FP32's
+    # largest number: X gates move the codes and nothing else
+    print("CASE enc2 largest scales", relabel, flush=True)
+    n, block = 14, 8
+    with J.State(n, "enc2", block_bits=block) as s:
+        s.init(5)
+        s.run(W.hadamard_all(n))
+        s.scale(2.0 ** 7)
+        s.scale(3.395e38)
+        codes, scales = (np.array(v) for v in s.raw_codes())
+        s.run(W.concat(W.gate(W.OP_X, 1), W.gate(W.OP_X, 9), W.gate(W.OP_X, 13)), mode="tile", relabel=relabel)
+        got = s.state_vector()
+    assert scales.max() > np.float32(127 / 128) * np.finfo(np.float32).max
+    want = oenc2.decode(codes, scales, block)[np.arange(1 << n) ^ (1 << 1 | 1 << 9 | 1 << 13)]
+    assert np.isfinite(want).all() and np.array_equal(got, want)
