@@ -462,7 +462,10 @@ juqcs_status juqcs_batch_destroy(juqcs_batch* b);
  * work lists; juqcs_branch_bytes gives its size, with up to 128 MiB more
  * that speed up sums of 2^16 bitstrings and more where the buffer has them.  group_size 0 takes the
  * largest group that fits work_bytes; a group size that does not fit is
- * JUQCS_ERR_SIZE.  count = 0 needs no workspace. */
+ * JUQCS_ERR_SIZE.  (Work lists of gates applied one at a time can be larger
+ * than those of fused gates: where only the latter leave room for group_size,
+ * smaller groups run, and where only theirs leave room for one branch, fused
+ * gates, with other FP32 roundings.)  count = 0 needs no workspace. */
 juqcs_status juqcs_branch_amplitudes(int n, const juqcs_gate* gates,
                                      size_t gate_count, const uint8_t* side,
                                      const uint64_t* z, size_t count,

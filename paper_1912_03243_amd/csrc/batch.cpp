@@ -1188,16 +1188,19 @@ int group_bits(int m, int group_size) {
   return m - lg;
 }
 
+juqcs_status scratch_on_current_device(void** ptr);
+
 // Eq. (3) for count bitstrings of words 64-bit words each (see
 // juqcs_branch_amplitudes_wide), in the caller's workspace.  dev: z and out
 // are device pointers (the bitstrings are checked on the device), else host
 // arrays.
 juqcs_status branch_amplitudes(int n, const juqcs_gate* gates, size_t gate_count, const uint8_t* side,
                                const uint64_t* z, int words, size_t count, int group_size, double* out,
-                               void* d_work, size_t work_bytes, hipStream_t s, bool dev, bool block = true) {
+                               void* d_work, size_t work_bytes, hipStream_t s, bool dev, bool scratch = false) {
   if (count > 0 && (!z || !out)) return fail(JUQCS_ERR_ARG, "null argument");
   auto J = std::make_unique<BranchJob>();
-  if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, !dev, block, J.get())) return rc;
+  if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, !dev, true, J.get()))
+    return rc;
   // bits at or above n must be clear (only the words that can hold them)
   for (int w = n / 64; !dev && w < words; ++w) {
     const int lo = std::max(0, n - 64 * w);
@@ -1206,10 +1209,9 @@ juqcs_status branch_amplitudes(int n, const juqcs_gate* gates, size_t gate_count
       if (z[k * words + w] & bad) return fail(JUQCS_ERR_ARG, "bitstring >= 2^n");
   }
   if (count == 0) return JUQCS_OK;
-  if (!d_work) return fail(JUQCS_ERR_ARG, "null workspace (juqcs_branch_bytes gives its size)");
+  if (!d_work && !scratch) return fail(JUQCS_ERR_ARG, "null workspace (juqcs_branch_bytes gives its size)");
   if (((uintptr_t)d_work & 255) != 0) return fail(JUQCS_ERR_ARG, "workspace not 256-byte aligned");
   const int P = J->P, m = J->m;
-  BranchPart* parts = J->parts;
   // Branches are grouped by the bits of the first L crossings (circuit
   // order; those bits are fixed within a group, the others free).  Inside a
   // group a part's states form a tree: the gates before its first crossing
@@ -1217,16 +1219,40 @@ juqcs_status branch_amplitudes(int n, const juqcs_gate* gates, size_t gate_count
   // copy per setting of their free bits, which then runs the gates up to
   // the next run.  The leaves are the part's states for every setting of
   // its own free crossings; branches that agree on those share a leaf.
-  BranchLayout lay;
-  if (group_size > 0) {
-    lay = branch_layout(*J, group_bits(m, group_size));
-    if (lay.total > work_bytes) return fail(JUQCS_ERR_SIZE, "workspace too small for the group size");
-  } else {
-    int L = 0;
-    while (L < m && branch_layout(*J, L).total > work_bytes) ++L;
-    lay = branch_layout(*J, L);
-    if (lay.total > work_bytes) return fail(JUQCS_ERR_SIZE, "workspace too small for one branch");
+  // The register-resident passes of a circuit run wherever those of one branch
+  // fit the workspace, so that its part states hold the same bits for any group
+  // size; their work lists can be larger than those of the fused passes, which
+  // take over where only theirs fit.  A group size that the fused passes have
+  // room for is taken, with smaller groups where the others have not.
+  const int want = group_size > 0 ? group_bits(m, group_size) : 0;
+  const auto largest = [&](const BranchJob& job, int from) {
+    int L = from;
+    BranchLayout l = branch_layout(job, L);
+    while (L < m && l.total > work_bytes) l = branch_layout(job, ++L);
+    return l;
+  };
+  BranchLayout lay = largest(*J, want);
+  if (lay.total > work_bytes || (group_size > 0 && lay.L > want)) {
+    auto F = std::make_unique<BranchJob>();
+    if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, !dev, false, F.get()))
+      return rc;
+    const BranchLayout fused = group_size > 0 ? branch_layout(*F, want) : largest(*F, 0);
+    if (fused.total > work_bytes) {
+      const size_t need = std::min(fused.total, branch_layout(*J, group_size > 0 ? want : m).total);
+      if (scratch)
+        return fail(JUQCS_ERR_SIZE, "the decomposition needs " + std::to_string(need) +
+                                        " bytes of workspace; the static scratch holds " + std::to_string(work_bytes));
+      return fail(JUQCS_ERR_SIZE, group_size > 0 ? "workspace too small for the group size"
+                                                 : "workspace too small for one branch");
+    }
+    if (lay.total > work_bytes) {
+      J.swap(F);
+      lay = fused;
+    }
   }
+  if (scratch)
+    if (juqcs_status rc = scratch_on_current_device(&d_work)) return rc;
+  BranchPart* parts = J->parts;
   const int L = lay.L;
   const long long gsize = lay.gsize, ngroups = lay.ngroups;
   for (int p = 0; p < P; ++p) set_free(&parts[p], L);
@@ -1493,28 +1519,8 @@ extern "C" juqcs_status juqcs_branch_amplitudes_noalloc(int n, const juqcs_gate*
                                                         int group_size, double* d_out,
                                                         void* hip_stream) {
   std::lock_guard<std::mutex> lock(g_scratch_mu);
-  size_t need = 0;
-  bool block = true;
-  if (count > 0) {
-    // the fused passes where only their work list fits the scratch
-    for (int fused = 0; fused < 2 && (fused == 0 || need > (size_t)JUQCS_NOALLOC_SCRATCH_BYTES); ++fused) {
-      auto J = std::make_unique<BranchJob>();
-      block = fused == 0;
-      if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, false, block, J.get()))
-        return rc;
-      need = branch_layout(*J, group_size > 0 ? group_bits(J->m, group_size) : J->m).total;
-    }
-    if (need > (size_t)JUQCS_NOALLOC_SCRATCH_BYTES)
-      return fail(JUQCS_ERR_SIZE, "the decomposition needs " + std::to_string(need) +
-                                      " bytes of workspace; the static scratch holds " +
-                                      std::to_string((size_t)JUQCS_NOALLOC_SCRATCH_BYTES));
-  }
-  void* ws = nullptr;
-  if (count > 0)
-    if (juqcs_status rc = scratch_on_current_device(&ws)) return rc;
-  return branch_amplitudes(n, gates, gate_count, side, d_z, words, count, group_size, d_out, ws,
-                           count > 0 ? (size_t)JUQCS_NOALLOC_SCRATCH_BYTES : 0, (hipStream_t)hip_stream,
-                           true, block);
+  return branch_amplitudes(n, gates, gate_count, side, d_z, words, count, group_size, d_out, nullptr,
+                           (size_t)JUQCS_NOALLOC_SCRATCH_BYTES, (hipStream_t)hip_stream, true, true);
 }
 
 extern "C" juqcs_status juqcs_branch_last_stats(juqcs_branch_stats* out) {

@@ -5,6 +5,7 @@ products in the same order, so every way gives the same bits."""
 import numpy as np
 import pytest
 
+from oracle import decomposition as odec
 from oracle import statevector as sv
 from paper_1912_03243_amd import workloads as W
 
@@ -73,3 +74,72 @@ def test_sums_in_a_workspace_without_room_for_interleaved_states(J):
     for size in (least, most - 1, most):
         work = torch.empty(size, dtype=torch.uint8, device="cuda")
         assert np.array_equal(J.juqcs_branch_amplitudes(n, circ, side, z, work=work), want)
+
+
+def parts_of(nloc, parts, per, rounds, seed):
+    """Equal parts, per random gates each between the crossings."""
+    rng = np.random.default_rng(seed)
+    recs = []
+    for r in range(rounds):
+        for p in range(parts):
+            for _ in range(per):
+                a, b = (int(x) + p * nloc for x in rng.choice(nloc, 2, replace=False))
+                recs.append([W.gate(W.OP_U, a, u=W.haar_u2(rng)), W.gate(W.OP_H, a), W.gate(W.OP_CNOT, a, b),
+                             W.gate(W.OP_CZ, a, b), W.gate(W.OP_CP, a, b, theta=1.1)][int(rng.integers(5))])
+        if r + 1 < rounds:
+            a, b = (int(x) for x in rng.choice(parts, 2, replace=False))
+            recs.append(W.gate(W.OP_CZ, a * nloc + int(rng.integers(nloc)), b * nloc + int(rng.integers(nloc))))
+    return nloc * parts, np.repeat(np.arange(parts), nloc).astype(np.uint8), W.concat(*recs)
+
+
+# Workspaces (64 bitstrings from the host) of these circuits with fused passes,
+# per group size; the register-resident passes' work lists are larger.
+FUSED_BYTES = [((11, 2, 40, 7, 1), {1: 45312, 4: 160512, 0: 2481664}),
+               ((11, 3, 78, 4, 2), {1: 82176, 4: 174080, 0: 288768}),
+               ((12, 3, 30, 4, 3), {1: 115968, 4: 284160, 0: 487424})]
+
+
+@pytest.mark.parametrize("args, sizes", FUSED_BYTES)
+def test_workspaces_of_the_fused_passes(J, args, sizes):
+    # a workspace that one of the two kinds of passes has room in is enough, and
+    # every group size gives the same bits where both kinds have for one branch
+    import torch
+    print("CASE fused workspaces", args, flush=True)
+    n, side, circ = parts_of(*args)
+    z = np.random.default_rng(1).integers(0, 1 << n, 64, dtype=np.uint64)
+    want = odec.branch_amplitudes(n, circ, side, z)
+    ref = J.juqcs_branch_amplitudes(n, circ, side, z)
+    least = J.juqcs_branch_bytes(n, circ, side, 1, 64, 1)[0]
+    assert sizes[1] < least
+    for group, size in sizes.items():
+        work = torch.empty(size, dtype=torch.uint8, device="cuda")
+        got = J.juqcs_branch_amplitudes(n, circ, side, z, group_size=group, work=work)
+        assert np.max(np.abs(got - want)) < 1e-5 * np.abs(want).max()
+        if size >= least:
+            assert np.array_equal(got, ref)
+    with pytest.raises(J.JuqcsError) as e:
+        J.juqcs_branch_amplitudes(n, circ, side, z, group_size=1, work=work[:sizes[1] // 512 * 256])
+    assert e.value.status == J.ERR_SIZE
+
+
+def test_noalloc_bits_do_not_depend_on_the_group_size(J):
+    # bitstrings until the largest group's register-resident passes no longer fit
+    # the static scratch, where the fused ones do
+    import torch
+    n, side, circ = parts_of(11, 3, 78, 4, 2)
+    need = lambda count: J.juqcs_branch_bytes(n, circ, side, 1, count, 0, False)
+    lo, hi = 1 << 10, 1 << 22
+    least, whole = need(lo)  # the largest group takes this much more than one branch
+    full = lambda count: need(count)[0] + whole - least
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if full(mid) <= J.NOALLOC_SCRATCH_BYTES else (lo, mid)
+    count = hi + 64
+    print("CASE noalloc groups", count, flush=True)
+    z = torch.from_numpy(np.random.default_rng(2).integers(0, 1 << n, (count, 1), dtype=np.int64)).cuda()
+    out = []
+    for group in (0, 8, 1):
+        got = torch.empty(2 * count, dtype=torch.float64, device="cuda")
+        J.juqcs_branch_amplitudes_noalloc(n, circ, side, z, got, group_size=group)
+        out.append(got.cpu().numpy())
+    assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
