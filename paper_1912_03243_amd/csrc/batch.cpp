@@ -757,6 +757,7 @@ struct BranchSeg {
   // diagonals, the plan of each setting (bit j: crossing ks[j]), and the most
   // that one of them takes in a work list
   BlkSchedule bsched;
+  std::vector<BlkGate> bgates;  // of setting 0
   std::vector<BlkPlan> bplans;
   BlkSizes bmax;
 };
@@ -805,11 +806,10 @@ std::vector<Gate> seg_gates(const BranchPart& bp, const BranchSeg& sg, long long
   return hg;
 }
 
-// The register-resident plan of a segment for a setting of its diagonals.
-bool seg_plan(const BranchPart& bp, const BranchSeg& sg, long long setting, BlkPlan* out) {
-  std::vector<BlkGate> bg;
-  return block_gates(bp.nloc, seg_gates(bp, sg, setting), block_tol(false), &bg, true) &&
-         block_build(sg.bsched, bg, false, out);
+// A segment's gates for a setting of its diagonals, rewritten for
+// register-resident passes.
+bool seg_block_gates(const BranchPart& bp, const BranchSeg& sg, long long setting, std::vector<BlkGate>* out) {
+  return block_gates(bp.nloc, seg_gates(bp, sg, setting), block_tol(false), out, true);
 }
 
 // Selects the tiles of a part's segments for register-resident passes; pos:
@@ -821,9 +821,8 @@ bool cut_block(BranchPart* bp, std::vector<int>* pos) {
     sg.gates.assign(bp->gates.begin() + sg.g0, bp->gates.begin() + sg.g1);
     for (Gate& g : sg.gates)
       for (int j = 0; j < g.nq; ++j) g.q[j] = (*pos)[g.q[j]];
-    std::vector<BlkGate> bg;
-    if (!block_gates(bp->nloc, seg_gates(*bp, sg, 0), block_tol(false), &bg, true)) return false;
-    block_schedule(bp->nloc, std::min(7, b), b, bg, 0, true, false, &sg.bsched);
+    if (!seg_block_gates(*bp, sg, 0, &sg.bgates)) return false;
+    block_schedule(bp->nloc, std::min(7, b), b, sg.bgates, 0, true, false, &sg.bsched);
     for (int q = 0; q < bp->nloc; ++q) (*pos)[q] = sg.bsched.sched.final_pos[(*pos)[q]];
   }
   return true;
@@ -832,42 +831,57 @@ bool cut_block(BranchPart* bp, std::vector<int>* pos) {
 // Gates that are planned in about the time that it takes to start a thread.
 constexpr size_t kThreadGates = 256;
 
-// The plans of every segment and setting of the register-resident parts; a
-// part that turns out not to allow one falls back to the fused passes.
-void plan_blocks(BranchPart* parts, int P) {
+// The plans of every segment and setting of the register-resident parts, and
+// the most that one of a segment's takes in a work list; a part that turns out
+// not to allow one falls back to the fused passes.  keep = false: for the sizes
+// only.  Settings whose gates have the same shape then count as one: their
+// plans can differ by phases that cancel to 1 on the way for one setting and
+// not for another, and a call that finds its plans larger than its workspace
+// takes smaller groups.
+void plan_blocks(BranchPart* parts, int P, bool keep) {
   struct Todo {
     BranchPart* bp;
     BranchSeg* sg;
-    long long setting;
+    long long from, to;  // settings
+    BlkSizes most;
+    bool ok = true;
   };
   std::vector<Todo> todo;
+  size_t gates = 0;
   for (int p = 0; p < P; ++p)
     for (BranchSeg& sg : parts[p].segs) {
-      BranchPart& bp = parts[p];
-      if (!bp.block) continue;
-      sg.bplans.resize(size_t(1) << sg.ks.size());
-      for (size_t x = 0; x < sg.bplans.size(); ++x) todo.push_back({&bp, &sg, (long long)x});
+      if (!parts[p].block) continue;
+      const long long n = 1ll << sg.ks.size();
+      if (keep) sg.bplans.resize((size_t)n);
+      for (long long x = 0; x < n; x += keep ? 1 : n) todo.push_back({&parts[p], &sg, x, keep ? x + 1 : n, {}});
+      gates += (sg.gates.size() + 4) * (keep ? (size_t)n : 1);
     }
-  std::vector<char> made(todo.size());
-  size_t gates = 0;
-  for (const Todo& t : todo) gates += t.sg->gates.size() + 4;
   parallel_for(
       (int)todo.size(),
       [&](int i) {
-        const Todo& t = todo[i];
-        made[i] = seg_plan(*t.bp, *t.sg, t.setting, &t.sg->bplans[t.setting]) ? 1 : 0;
+        Todo& t = todo[i];
+        std::vector<uint64_t> shapes;
+        for (long long x = t.from; x < t.to && t.ok; ++x) {
+          std::vector<BlkGate> bg;
+          if (x == 0) bg = std::move(t.sg->bgates);
+          else t.ok = seg_block_gates(*t.bp, *t.sg, x, &bg);
+          if (!t.ok) break;
+          if (!keep) {
+            const uint64_t h = block_shape(bg);
+            if (std::find(shapes.begin(), shapes.end(), h) != shapes.end()) continue;
+            shapes.push_back(h);
+          }
+          BlkPlan own;
+          BlkPlan* plan = keep ? &t.sg->bplans[x] : &own;
+          t.ok = block_build(t.sg->bsched, bg, false, plan);
+          t.most.grow(BlkSizes(*plan));
+        }
       },
       1 + gates / kThreadGates);
-  for (size_t i = 0; i < todo.size(); ++i)
-    if (!made[i] && todo[i].bp->block) cut_part(todo[i].bp, false);
-  for (const Todo& t : todo) {
-    if (!t.bp->block) continue;
-    const BlkSizes z(t.sg->bplans[t.setting]);
-    t.sg->bmax.passes = std::max(t.sg->bmax.passes, z.passes);
-    t.sg->bmax.stages = std::max(t.sg->bmax.stages, z.stages);
-    t.sg->bmax.layers = std::max(t.sg->bmax.layers, z.layers);
-    t.sg->bmax.ops = std::max(t.sg->bmax.ops, z.ops);
-  }
+  for (Todo& t : todo)
+    if (!t.ok && t.bp->block) cut_part(t.bp, false);
+  for (Todo& t : todo)
+    if (t.bp->block) t.sg->bmax.grow(t.most);
 }
 
 // Cuts the part before every run of its crossings (consecutive gates of the
@@ -973,7 +987,7 @@ struct BranchJob {
 };
 
 juqcs_status branch_prepare(int n, const juqcs_gate* gates, size_t gate_count, const uint8_t* side,
-                            int words, size_t count, bool host_io, bool block, BranchJob* J) {
+                            int words, size_t count, bool host_io, bool block, bool sizes_only, BranchJob* J) {
   if (n < 2 || n > kBranchMaxQubits) return fail(JUQCS_ERR_ARG, "n must be in [2, 240]");
   if (words < (n + 63) / 64 || words > kBranchMaxWords)
     return fail(JUQCS_ERR_ARG, "words must be in [ceil(n / 64), 4]");
@@ -1048,7 +1062,7 @@ juqcs_status branch_prepare(int n, const juqcs_gate* gates, size_t gate_count, c
     parts[p].sbytes = align256((size_t)8 << J->nloc[p]);
   }
   parallel_for(P, [&](int p) { cut_part(&parts[p], block); }, 1 + gate_count / kThreadGates);
-  plan_blocks(parts, P);
+  plan_blocks(parts, P, !sizes_only);
   return JUQCS_OK;
 }
 
@@ -1199,7 +1213,7 @@ juqcs_status branch_amplitudes(int n, const juqcs_gate* gates, size_t gate_count
                                void* d_work, size_t work_bytes, hipStream_t s, bool dev, bool scratch = false) {
   if (count > 0 && (!z || !out)) return fail(JUQCS_ERR_ARG, "null argument");
   auto J = std::make_unique<BranchJob>();
-  if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, !dev, true, J.get()))
+  if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, !dev, true, false, J.get()))
     return rc;
   // bits at or above n must be clear (only the words that can hold them)
   for (int w = n / 64; !dev && w < words; ++w) {
@@ -1234,7 +1248,7 @@ juqcs_status branch_amplitudes(int n, const juqcs_gate* gates, size_t gate_count
   BranchLayout lay = largest(*J, want);
   if (lay.total > work_bytes || (group_size > 0 && lay.L > want)) {
     auto F = std::make_unique<BranchJob>();
-    if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, !dev, false, F.get()))
+    if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, !dev, false, false, F.get()))
       return rc;
     const BranchLayout fused = group_size > 0 ? branch_layout(*F, want) : largest(*F, 0);
     if (fused.total > work_bytes) {
@@ -1535,7 +1549,7 @@ extern "C" juqcs_status juqcs_branch_bytes(int n, const juqcs_gate* gates, size_
                                            size_t* bytes) {
   if (!min_bytes || !bytes) return fail(JUQCS_ERR_ARG, "null output");
   auto J = std::make_unique<BranchJob>();
-  if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, host_io != 0, true, J.get()))
+  if (juqcs_status rc = branch_prepare(n, gates, gate_count, side, words, count, host_io != 0, true, true, J.get()))
     return rc;
   *min_bytes = branch_layout(*J, J->m).total;
   const BranchLayout lay = branch_layout(*J, group_bits(J->m, group_size));

@@ -34,10 +34,10 @@ bool zero(C a) { return a.re == 0 && a.im == 0; }
 bool equal(C a, R re) { return std::fabs(a.re - re) <= 0x1p-58L && std::fabs(a.im) <= 0x1p-58L; }
 bool one(C a) { return equal(a, 1); }
 bool minus_one(C a) { return equal(a, -1); }
-// Neither a nor 1 / a overflows in FP64 (zero does).
+// Neither a nor 1 / a comes near FP64's range.
 bool ranged(C a) {
-  const R n = norm2(a);
-  return n >= 0x1p-2040L && n <= 0x1p2040L;
+  const R m = std::max(std::fabs(a.re), std::fabs(a.im));
+  return m >= 1e-300 && m <= 1e300;
 }
 
 // Collects the single-qubit gates of each qubit until a gate that does not
@@ -232,6 +232,18 @@ bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<
   }
   for (int q = 0; q < n; ++q) rw.flush(q, true);
   return true;
+}
+
+uint64_t block_shape(const std::vector<BlkGate>& gates) {
+  uint64_t h = 1469598103934665603ull;
+  for (const BlkGate& g : gates) {
+    const uint64_t v = (uint64_t)g.kind | (uint64_t)(uint8_t)g.q[0] << 8 | (uint64_t)(uint8_t)g.q[1] << 16 |
+                       (uint64_t)g.formb << 24 | (uint64_t)one(g.ph) << 25 | (uint64_t)minus_one(g.ph) << 26 |
+                       (uint64_t)one(g.lam) << 27;
+    h = (h ^ v) * 1099511628211ull;
+    h ^= h >> 29;
+  }
+  return h;
 }
 
 namespace {
@@ -978,8 +990,11 @@ void plan_block_pass(const TileGeom& tg, const std::vector<const BlkGate*>& gate
   // at[s][b]: where (in which of the first stage's elements' slots) the tile
   // element 1 << b of stage s lies: the CNOTs done by the exchanges so far,
   // linear over XOR; from[s][b]: the same in the elements of the stage before
-  std::vector<std::vector<int>> at(st.size(), std::vector<int>(tb)), from = at;
-  for (int b = 0; b < tb; ++b) at[0][b] = 1 << b;
+  struct Map {
+    int e[kBlkRegs + kBlkThrBits];
+  };
+  std::vector<Map> at(st.size()), from(st.size());
+  for (int b = 0; b < tb; ++b) at[0].e[b] = 1 << b;
   for (size_t s = 0; s < st.size(); ++s) {
     StagePlan& p = st[s];
     if (s > 0)
@@ -988,9 +1003,9 @@ void plan_block_pass(const TileGeom& tg, const std::vector<const BlkGate*>& gate
         for (size_t i = p.lin.size(); i-- > 0;)
           if ((x >> p.lin[i].first) & 1) x ^= 1 << p.lin[i].second;
         for (int c = 0; c < tb; ++c)
-          if ((x >> c) & 1) y ^= at[s - 1][c];
-        from[s][b] = x;
-        at[s][b] = y;
+          if ((x >> c) & 1) y ^= at[s - 1].e[c];
+        from[s].e[b] = x;
+        at[s].e[b] = y;
       }
     const bool f = s == 0, l = s + 1 == st.size();
     const uint32_t no = p.regs | (f ? low_src : 0u) | (l ? low_dst : 0u);
@@ -1008,7 +1023,7 @@ void plan_block_pass(const TileGeom& tg, const std::vector<const BlkGate*>& gate
     uint32_t used = p.regs;
     for (int b : wv) used |= 1u << b;
     int span = 1;
-    auto dir = [&](int b) { return slot(at[s][b]) & ((1 << phase) - 1); };
+    auto dir = [&](int b) { return slot(at[s].e[b]) & ((1 << phase) - 1); };
     auto put = [&](int b) {
       int g = span;
       for (int u = 0; u < (1 << phase); ++u)
@@ -1053,10 +1068,10 @@ void plan_block_pass(const TileGeom& tg, const std::vector<const BlkGate*>& gate
   }
   // Whether every wave's elements of stage b lie in slots of its own elements of
   // stage a.  in: the element of a in whose slot each element 1 << e of b lies.
-  auto same_slots = [&](const StagePlan& a, const StagePlan& b, const std::vector<int>& in) {
+  auto same_slots = [&](const StagePlan& a, const StagePlan& b, const Map& in) {
     for (int i = lanes; i < nthr; ++i)
       for (int e = 0; e < tb; ++e)
-        if (((in[e] >> a.thr[i]) & 1) != (e == b.thr[i])) return false;
+        if (((in.e[e] >> a.thr[i]) & 1) != (e == b.thr[i])) return false;
     return true;
   };
   // A tile's first exchange writes the first stage's slots, which other waves
@@ -1070,8 +1085,8 @@ void plan_block_pass(const TileGeom& tg, const std::vector<const BlkGate*>& gate
     const StagePlan& p = st[s];
     BlkStage x{};
     x.exchange = s > 0 && !same_slots(st[s - 1], p, from[s]) ? BLK_CROSS : BLK_WAVE;
-    for (int j = 0; j < K; ++j) x.row[j] = slot(at[s][p.reg[j]]) * kSlotBytes;
-    for (int i = 0; i < nthr; ++i) x.thr[i] = slot(at[s][p.thr[i]]) * kSlotBytes;
+    for (int j = 0; j < K; ++j) x.row[j] = slot(at[s].e[p.reg[j]]) * kSlotBytes;
+    for (int i = 0; i < nthr; ++i) x.thr[i] = slot(at[s].e[p.thr[i]]) * kSlotBytes;
     emit_layers(p, nthr, x, plan);
   }
   plan->passes.push_back(out);

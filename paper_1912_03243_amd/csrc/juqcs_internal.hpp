@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <cmath>
 #include <cstdint>
@@ -487,6 +488,9 @@ struct BlkPlan {
 // keep: phases that happen to be 1 stay in the list, so that its shape (kinds
 // and qubits) is the same for circuits that differ in their diagonals' values.
 bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<BlkGate>* out, bool keep = false);
+// A number that tells apart lists whose plans differ in more than coefficients:
+// kinds, qubits, forms, and which phases and scalars are 1 or -1.
+uint64_t block_shape(const std::vector<BlkGate>& gates);
 // Appends one pass: geometry tg, its gates (on the physical bits of where[taken[i]]).
 // low: low bits that the first and the last stage keep on lanes (contiguous
 // accesses of 2^low amplitudes).
@@ -526,6 +530,12 @@ struct BlkSizes {
   BlkSizes() = default;
   explicit BlkSizes(const BlkPlan& p)
       : passes(p.passes.size()), stages(p.stages.size()), layers(p.layers.size()), ops(p.ops.size()) {}
+  void grow(const BlkSizes& z) {  // each the larger of the two
+    passes = std::max(passes, z.passes);
+    stages = std::max(stages, z.stages);
+    layers = std::max(layers, z.layers);
+    ops = std::max(ops, z.ops);
+  }
 };
 // Appends p to all (indices moved).
 void append_plan(const BlkPlan& p, BlkPlan* all);

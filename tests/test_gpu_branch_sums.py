@@ -143,3 +143,22 @@ def test_noalloc_bits_do_not_depend_on_the_group_size(J):
         J.juqcs_branch_amplitudes_noalloc(n, circ, side, z, got, group_size=group)
         out.append(got.cpu().numpy())
     assert np.array_equal(out[0], out[1]) and np.array_equal(out[0], out[2])
+
+
+@pytest.mark.parametrize("group", [0, 1, 4, 16])
+@pytest.mark.parametrize("args", [(11, 2, 12, 7, 11), (12, 3, 30, 5, 12), (13, 2, 8, 9, 13)])
+def test_reported_workspaces_hold_the_group(J, args, group):
+    # the sizes come from the gates' shapes, without a plan for every setting of
+    # the crossings
+    import torch
+    print("CASE reported workspaces", args, group, flush=True)
+    n, side, circ = parts_of(*args)
+    z = np.random.default_rng(3).integers(0, 1 << n, 200, dtype=np.uint64)
+    least, size = J.juqcs_branch_bytes(n, circ, side, 1, len(z), group)
+    for want, work in ((group, size), (1, least)):
+        got = J.juqcs_branch_amplitudes(n, circ, side, z, group_size=want,
+                                        work=torch.empty(work, dtype=torch.uint8, device="cuda"))
+        st = J.juqcs_branch_last_stats()
+        assert st["group_bits"] == (0 if want == 0 else max(0, st["crossings"] - int(np.log2(want))))
+    ref = odec.branch_amplitudes(n, circ, side, z)
+    assert np.max(np.abs(got - ref)) < 1e-5 * np.abs(ref).max()
