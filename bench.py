@@ -29,7 +29,8 @@ sys.path.insert(0, ROOT)
 METRIC = "gate-updates/s and achieved HBM GB/s per gate pass (fraction of peak), 1 GPU"
 HBM_PEAK_GBPS = 8000.0
 FP64_VECTOR_PEAK_TFLOPS = 78.6  # 256 CUs x 4 SIMDs x 16 FP64 FMA lanes x 2 flops x 2.4 GHz
-FP32_MFMA_PEAK_TFLOPS = 157.3   # dense FP32 matrix-core peak (the in-tile 8x8 ops of C64 passes)
+FP32_MFMA_PEAK_TFLOPS = 157.3   # dense FP32 matrix-core peak (the 8x8 ops of fused C64 passes)
+FP32_VECTOR_PEAK_TFLOPS = 78.6  # FP32 vector arithmetic without packed math: the FP64 rate
 FUSE_K_C128 = 5                 # fused block width of the fused comparison step
 
 
@@ -41,6 +42,28 @@ def gate_flops_per_amp(gates, W) -> float:
     per = {W.OP_H: 14.0, W.OP_X: 14.0, W.OP_Y: 14.0, W.OP_U: 14.0, W.OP_Z: 3.0, W.OP_S: 3.0,
            W.OP_T: 3.0, W.OP_CNOT: 0.0, W.OP_CZ: 0.5, W.OP_CP: 1.5}
     return float(sum(per[int(op)] for op in gates["op"]))
+
+
+def alu_roofline(gate_tflops: float, fp64: bool, fuse_k: int = 0, **more) -> dict:
+    """Roofline of tile passes that on-chip arithmetic bounds, from the rate of
+    the gates' algorithmic flops.  Register-resident passes (fuse_k 0) apply a
+    2x2 unitary as a phase and a rotation on vector units, 7 flops per amplitude
+    instead of 14, which is what their rate counts; passes of fused gates have
+    8x8 ops on the FP32 matrix cores."""
+    mfma = bool(fuse_k) and not fp64
+    peak = FP64_VECTOR_PEAK_TFLOPS if fp64 else FP32_MFMA_PEAK_TFLOPS if mfma else FP32_VECTOR_PEAK_TFLOPS
+    tf = gate_tflops * (1.0 if fuse_k else 0.5)
+    return {"bound": "alu", "achieved": tf, "peak": peak, "unit": "TFLOP/s", "frac": tf / peak,
+            "gate_tflops": gate_tflops, **more}
+
+
+def tile_kernel(dtype: str, fuse_k: int, tune) -> str:
+    """The tile kernel of a run (tune: the tuning record's entry or None)."""
+    b = 12 if tune and tune["tile_bits"] == 12 else 13
+    if dtype == "enc2":
+        return "k_tile_enc2_fixed<13>" if fuse_k else "k_block_codes<13,4>"
+    t = "double" if dtype == "c128" else "float"
+    return f"k_tile_fixed<{t},{b},{512 if b == 12 else 1024}>" if fuse_k else f"k_block<{t},{b},4>"
 
 
 def log(*a):
@@ -281,16 +304,14 @@ def main():
     if chosen == "tile":
         # A tile pass absorbs ~64 gates here: far past the FP64 ridge (about
         # 22 gates per pass), so the pass is bound by arithmetic on chip.
-        # achieved = the absorbed gates' algorithmic flops per launch / the
+        # gate_tflops = the absorbed gates' algorithmic flops per launch / the
         # average launch time (HIP events on the launch stream).
         flops_launch = gate_flops_per_amp(gates, W) * float(1 << n) * args.steps / max(passes, 1)
         tflops = flops_launch / (pass_ms / 1e3) / 1e12
-        roofline = {"bound": "alu", "achieved": tflops, "peak": FP64_VECTOR_PEAK_TFLOPS,
-                    "unit": "TFLOP/s", "frac": tflops / FP64_VECTOR_PEAK_TFLOPS,
-                    "traffic": traffic_for(TILE_SOURCES),
-                    "kernel": ("k_block<double,12,4>" if tune and tune["tile_bits"] == 12
-                               else "k_block<double,13,4>"),
-                    "flops_per_launch": flops_launch, "avg_launch_ms": pass_ms, "hbm": hbm}
+        fuse_k = tune["fuse_k"] if tune else args.tile_fuse
+        roofline = alu_roofline(tflops, True, fuse_k, traffic=traffic_for(TILE_SOURCES),
+                                kernel=tile_kernel("c128", fuse_k, tune),
+                                flops_per_launch=flops_launch, avg_launch_ms=pass_ms, hbm=hbm)
     elif chosen == "fused":
         tf = mma_flops / max(passes, 1) / (pass_ms / 1e3) / 1e12
         roofline = {"bound": "mfma", "achieved": tf, "peak": FP64_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
@@ -453,17 +474,15 @@ def batch_sample_errors(amps, count):
 
 
 def tree_roofline(bst, ms):
-    """Roofline of the part-state trees of a decomposition step: the
-    algorithmic flops of the gates they simulated over the step time (the
-    tile kernel is most of the step, so this is a lower bound on its rate),
-    against the FP32 matrix-core peak, with their HBM bytes beside."""
-    tf = bst["gate_flops"] / (ms / 1e3) / 1e12
-    return {"bound": "alu", "achieved": tf, "peak": FP32_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
-            "frac": tf / FP32_MFMA_PEAK_TFLOPS, "kernel": "k_block_round<13,4>", "flops_per_step": bst["gate_flops"],
-            "hbm": {"achieved_GBps": bst["pass_bytes"] / (ms / 1e3) / 1e9,
-                    "bytes_per_step": bst["pass_bytes"],
-                    "note": "24-qubit part states (128 MiB) are cache-resident: effective"},
-            "note": "over the whole step"}
+    """Roofline of the part-state trees of a decomposition step: the gates
+    that they simulated over the step time (the tile kernel is most of the
+    step, so this is a lower bound on its rate), with their HBM bytes beside."""
+    return alu_roofline(bst["gate_flops"] / (ms / 1e3) / 1e12, False, kernel="k_block_round<13,4>",
+                        flops_per_step=bst["gate_flops"],
+                        hbm={"achieved_GBps": bst["pass_bytes"] / (ms / 1e3) / 1e9,
+                             "bytes_per_step": bst["pass_bytes"],
+                             "note": "part states read and written once a pass (effective)"},
+                        note="over the whole step")
 
 
 def tuned_mode(args, juqcs, st, gates):
@@ -570,13 +589,11 @@ def other_workload(args, juqcs, W, dev, stream, emit=True):
             "planning_s": t_plan,
             "cost_model_ms_per_step": cost_model_ms,
             # the graph is one persistent tile kernel per pass round: its
-            # time is the step; in-tile ops run on FP32 matrix cores and VALU
-            "roofline": {"bound": "alu", "achieved": tf, "peak": FP32_MFMA_PEAK_TFLOPS,
-                         "unit": "TFLOP/s", "frac": tf / FP32_MFMA_PEAK_TFLOPS,
-                         "kernel": "k_block_round<13,4>", "flops_per_step": flops,
-                         "hbm": {"achieved_GBps": 16.0 * st["tasks"] * 8192 / (ms / 1e3) / 1e9,
-                                 "note": "tile tasks x 2^13 amplitudes x 16 B; states of n <= 24 "
-                                         "are cache-resident, so effective"}},
+            # time is the step
+            "roofline": alu_roofline(tf, False, 0 if (kin == 1).all() else int(kin.max()),
+                                     kernel="k_block_round<13,4>", flops_per_step=flops,
+                                     hbm={"achieved_GBps": 16.0 * st["tasks"] * 8192 / (ms / 1e3) / 1e9,
+                                          "note": "tile tasks x 2^13 amplitudes x 16 B (effective)"}),
             "check": check,
         })
         b.close()
@@ -826,17 +843,12 @@ def other_workload(args, juqcs, W, dev, stream, emit=True):
                                    "seed 3), tile passes", "n": n, "passes_per_step": passes,
                        "relabel": args.relabel, "autotune": tune},
             # passes absorb far more gates than one HBM pass pays for: bound
-            # by on-chip arithmetic (FP32 matrix cores for the 8x8 ops, VALU
-            # for the rest and for the two-byte codec)
-            "roofline": {"bound": "alu", "achieved": tf, "peak": FP32_MFMA_PEAK_TFLOPS,
-                         "unit": "TFLOP/s", "frac": tf / FP32_MFMA_PEAK_TFLOPS,
-                         "frac_of_fp32_valu": tf / FP64_VECTOR_PEAK_TFLOPS,
-                         "flops_per_launch": fl / passes, "avg_launch_ms": kms / passes,
-                         "kernel": (("k_block<float,12,4>" if tune and tune["tile_bits"] == 12
-                                     else "k_block<float,13,4>") if dtype == "c64"
-                                    else "k_block_codes<13,4>"),
-                         "hbm": {"achieved_GBps": achieved, "peak_GBps": HBM_PEAK_GBPS,
-                                 "frac": achieved / HBM_PEAK_GBPS, "bytes_per_launch": kb / passes}},
+            # by vector arithmetic on chip (and by the two-byte codec's)
+            "roofline": alu_roofline(tf, False, tune["fuse_k"] if tune else args.tile_fuse,
+                                     flops_per_launch=fl / passes, avg_launch_ms=kms / passes,
+                                     kernel=tile_kernel(dtype, tune["fuse_k"] if tune else args.tile_fuse, tune),
+                                     hbm={"achieved_GBps": achieved, "peak_GBps": HBM_PEAK_GBPS,
+                                          "frac": achieved / HBM_PEAK_GBPS, "bytes_per_launch": kb / passes}),
             "amp_updates_per_s": len(circ) * float(1 << n) / (ms / 1e3),
             "check": check,
         })
