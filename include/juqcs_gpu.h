@@ -186,8 +186,10 @@ typedef struct {
                           use the batch's state buffer); 0 = cost model  */
   int32_t pass_gates;  /* TILE: most gates one pass may absorb; -1 = no
                           limit; 0 = the planner's choice (no limit for
-                          C128; for C64 and ENC2 the limit its cost model
-                          prefers, which spreads on-chip work over passes) */
+                          C128 and for gates applied from registers; for
+                          ENC2 and for fused gates in C64 the limit its
+                          cost model prefers, which spreads on-chip work
+                          over passes)                                    */
   int32_t relabel;     /* TILE: 0 or 1 = a pass may hand the
                           low (contiguous) physical bits to other qubits of
                           its tile as it writes the tile back (qubit

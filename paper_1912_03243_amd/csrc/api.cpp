@@ -280,8 +280,12 @@ double tile_plan_ms(const TilePlan& p, juqcs_dtype dt, int n) {
 }
 
 // pass_gates: > 0 caps the gates per pass, -1 lifts the cap, 0 is the
-// planner's choice: no cap for C128 (measured fastest: capped plans carry
-// more, less dense ops), for C64 and ENC2 the cap the cost model prefers.
+// planner's choice: no cap for register-resident passes of C128 and C64 (ms on
+// 31 qubits, 16 brick layers in C64: 157.2 without, 152.4 at 140 gates, 157.7
+// at 100, 171.8 at 60; 28 qubits 17.6, 17.9, 18.4, 20.8; 30 qubits, 20 layers
+// in C128 153.3, 154.5, 160.5, 177.8; random pairs and mixed gates within 3%
+// down to 80; the cost model does not tell these apart: it would take 100) and
+// for C128; for other C64 passes and ENC2 the cap that the cost model prefers.
 // relabel >= 0: plans may move qubits onto the low physical bits between
 // passes (the layout st->phys follows); -1: the data stay where they are
 // (explicit layout moves rely on that).

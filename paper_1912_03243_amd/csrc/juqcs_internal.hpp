@@ -95,7 +95,7 @@ struct TileGeom {
   int32_t maxk;                  // widest op of the pass (1..4)
   int32_t mat_count;             // coefficients of the pass's ops, from ops[0].moff on
   int32_t mma_count;             // 8x8 (TOP_DENSE3) ops of the pass
-  // Relabeling (C128 / C64 only): after its ops the pass writes the tile
+  // Relabeling: after its ops the pass writes the tile
   // back with local bits swap_a[i] and swap_b[i] exchanged (disjoint pairs),
   // i.e. the qubits at those two physical positions trade places.
   int32_t nswap;
@@ -503,6 +503,8 @@ bool plan_block(int n, int L, int b, const std::vector<Gate>& gates, bool fp64, 
 
 // The relative miss of a matrix entry by the rotation form up to which a
 // gate is not kept dense: an FP64 rounding step, or far below an FP32 one.
+// (Haar circuits in FP64: one rotation in 250 stays dense, against one in 20
+// at 2^-53; errors of 20 layers 1.28e-15 against 1.21e-15.)
 inline double block_tol(bool fp64) { return fp64 ? 0x1p-52 : 1e-9; }
 // Tile selection of a rewritten circuit; plans of circuits of the same shape
 // (kinds and qubits) can be built on it with other values.

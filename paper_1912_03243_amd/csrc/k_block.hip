@@ -60,7 +60,7 @@ __device__ __forceinline__ void amp_ptrs_flip(V* base, uint64_t off, Const<int32
 // At most 128 registers per thread, so that 16 waves share a CU: while a
 // workgroup's tile is on its way from or to HBM, the others compute.  (With
 // the next tile prefetched into registers instead, FP64 had room for 8 waves:
-// brick30 175 ms per step against 165.)
+// brick30 175 ms per step where this form took 165; it takes 157 now.)
 // The geometry is read again for every tile, through an opaque pointer: kept
 // over the layers it would hold the scalar registers that their coefficients
 // need.
@@ -234,8 +234,10 @@ __global__ __launch_bounds__(1 << (TB - K), 4) void k_block_codes(int8_t* __rest
 
 // One round of many C64 states: workgroups claim chunks of tiles through the
 // ticket counter until none are left (none ever waits for another).  States
-// are read and written through the caches: part states and small circuits
-// stay there from pass to pass.
+// are read and written through the caches.  A round goes over all of its
+// states, so they stay there from pass to pass only where they take less than
+// the 256 MiB last-level cache together: the levels of small decompositions,
+// not those of 42 qubits in halves with 8 crossings (98 GB at 3.1 TB/s).
 template <int TB, int K>
 __global__ __launch_bounds__(1 << (TB - K), 4) void k_block_round(
     char* __restrict__ states, const BatchGroup* __restrict__ groups, int g0, int g1,
