@@ -70,6 +70,7 @@ struct juqcs_state {
   // the stored amplitudes (phases and scalar weights are absorbed here
   // instead of passes over the data)
   C gf{1.0, 0.0};
+  double size = 1.0;  // product of the factors of juqcs_scale since the last init
   int phys[64];  // logical qubit -> physical bit
   size_t ring;   // next free offset inside the ring
   // per-pass timing of juqcs_run_circuit when profiling (else empty)
@@ -305,7 +306,10 @@ juqcs_status tile_gates(juqcs_state* st, const std::vector<Gate>& gates, int L, 
   if (st->dt == JUQCS_ENC2 && b < L + 2) b = std::min(maxb, L + 2);  // room for two gathered qubits
   if (st->n > b && b - L < 2)
     return fail(JUQCS_ERR_ARG, "a tile needs at least two gathered bits (tile_bits >= low_bits + 2)");
-  const bool block = kin <= 0;  // no fusion width asked for
+  // No fusion width asked for.  Register-resident passes hold up to 2^24 times
+  // an amplitude on the way, so states scaled up to near the end of their range
+  // take the fused ones.
+  const bool block = kin <= 0 && st->size <= (st->dt == JUQCS_C128 ? 0x1p990 : 0x1p100);
   if (kin <= 0) kin = 3;
   if (kin > 4) return fail(JUQCS_ERR_ARG, "in-pass fusion width must be 1..4");
   if (pass_gates < -1) return fail(JUQCS_ERR_ARG, "pass_gates must be >= -1");
@@ -676,6 +680,7 @@ juqcs_status juqcs_state_init(juqcs_state* st, uint64_t basis_index) {
   if (st->n < 64 && (basis_index >> st->n) != 0) return fail(JUQCS_ERR_ARG, "basis index >= 2^n");
   for (int q = 0; q < 64; ++q) st->phys[q] = q;
   st->gf = C{1.0, 0.0};
+  st->size = 1.0;
   hipError_t e = launch_init(st->dt, st->amps, st->scales, st->n, st->B, basis_index, st->stream);
   if (e != hipSuccess) return hip_fail(e, "init launch");
   return JUQCS_OK;
@@ -1156,6 +1161,7 @@ juqcs_status juqcs_scale(juqcs_state* st, double factor) {
   if (st->dt == JUQCS_ENC2 && !(factor > 0)) return fail(JUQCS_ERR_ARG, "ENC2 scale factor must be > 0");
   hipError_t e = launch_scale(st->dt, st->amps, st->scales, st->n, st->B, factor, st->stream);
   if (e != hipSuccess) return hip_fail(e, "scale launch");
+  st->size *= std::fabs(factor);
   return JUQCS_OK;
 }
 

@@ -213,3 +213,25 @@ def test_no_gates_no_pass(J, n, dtype):
             assert s.run(W.empty_circuit(0), **opts).passes == 0
         got = s.state_vector()
     assert got[3] == 1 and np.count_nonzero(got) == 1
+
+
+@pytest.mark.parametrize("dtype, power", [("c128", 1010), ("c64", 115), ("enc2", 115)])
+def test_scaled_states_stay_in_range(J, dtype, power):
+    # a pass of 300 rotations would enlarge amplitudes of 2^power / 91 by up to 2^24
+    # before its scalars come in: such states take the fused passes, and a power
+    # of two changes none of their roundings
+    print("CASE blocks-scaled", dtype, power, flush=True)
+    n = 13
+    first = W.layered_brick(n, 2, seed=37)
+    circ = W.layered_brick(n, 24, seed=38)
+
+    def run(p, fuse_k):
+        with J.State(n, dtype) as s:
+            s.init(0)
+            s.run(first, mode="tile", fuse_k=3)
+            s.scale(2.0 ** (p // 2))
+            s.scale(2.0 ** (p - p // 2))
+            s.run(circ, mode="tile", fuse_k=fuse_k)
+            return s.state_vector() * 2.0 ** -(p // 2) * 2.0 ** -(p - p // 2)
+    got = run(power, 0)
+    assert np.isfinite(got).all() and np.array_equal(got, run(0, 3))
