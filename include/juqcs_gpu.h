@@ -175,7 +175,11 @@ typedef struct {
   int32_t fuse_k;      /* FUSED: block width 2..6 (0 = 5).  TILE: widest
                           fused op inside a pass, 1..4; 0 = gates one at a
                           time from registers where the tile size and the
-                          gates allow it, else 3                          */
+                          gates allow it, else 3.  (Registers hold up to
+                          2^24 times an amplitude on the way: a state that
+                          juqcs_scale made larger than 2^100, 2^990 for
+                          C128, is given 3; amplitudes of that size from
+                          elsewhere need 1..4.)                           */
   int32_t mma;         /* FUSED: juqcs_mma                                */
   int32_t tile_bits;   /* TILE: total tile bits (0 = default for dtype)   */
   int32_t low_bits;    /* TILE: contiguous low bits per chunk (0 = default) */
