@@ -1167,23 +1167,26 @@ double plan_ms(const BlkPlan& p, bool fp64) {
 // amplitudes take the ops one by one).  Matrices far from unitary ones may not
 // be; the fused passes multiply them in FP64 first.
 bool in_range(const BlkPlan& p, bool fp64) {
-  const double most = fp64 ? 0x1p500 : 0x1p60, least = 1.0 / most;
-  const auto ok = [&](double x) { return x >= least && x <= most; };
+  const double most = fp64 ? 0x1p500 : 0x1p60, most2 = most * most;
+  const auto ok = [&](double x, double y) {
+    const double n = x * x + y * y;
+    return n >= 1.0 / most2 && n <= most2;
+  };
   for (const BlkLayer<double>& y : p.layers)
     for (int j = 0; j < kBlkRegs; ++j)
-      if ((y.flags & (BLK_ROT << j)) && !(ok(std::hypot(y.c[3 * j], y.c[3 * j + 1])) && std::isfinite(y.c[3 * j + 2])))
+      if ((y.flags & (BLK_ROT << j)) && !(ok(y.c[3 * j], y.c[3 * j + 1]) && std::isfinite(y.c[3 * j + 2])))
         return false;
   for (size_t o = 0; o < p.ops.size(); ++o) {
     const uint32_t kind = p.ops[o].kind;
     const double* c = &p.ocoef[8 * o];
-    if ((kind == 0 || (kind & (blk_phase() * 127))) && !ok(std::hypot(c[0], c[1]))) return false;
+    if ((kind == 0 || (kind & (blk_phase() * 127))) && !ok(c[0], c[1])) return false;
     if (kind & (blk_dense(0) * 15)) {
       double m = 0.0;
       for (int i = 0; i < 8; ++i) {
         if (!std::isfinite(c[i])) return false;
         m = std::max(m, std::fabs(c[i]));
       }
-      if (!ok(m)) return false;
+      if (!ok(m, 0.0)) return false;
     }
   }
   return true;
