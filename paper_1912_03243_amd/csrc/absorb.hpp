@@ -34,13 +34,18 @@ struct Absorb {
 // Weights that a growing set of bits takes.  What a set takes, a larger one
 // takes too (it leaves fewer gates behind), so a candidate is tried on the gates
 // that the set so far leaves behind only; eight candidates run side by side.
-// Gates after the point where a set is wholly blocked are not looked at.
+// Gates after the point where a set is wholly blocked are not looked at, nor
+// those that come after window gates in a row of which no set takes any.
 class AbsorbSearch {
  public:
-  AbsorbSearch(std::vector<AbsorbMask> gates, uint64_t set) : gates_(std::move(gates)) {
-    left_.reserve(std::min<size_t>(gates_.size(), 256));
+  // Gates head, then count more (which outlive the search).
+  AbsorbSearch(std::vector<AbsorbMask> head, const AbsorbMask* gates, size_t count, uint64_t set, size_t window)
+      : gates_(gates), count_(count), window_(window), left_(std::move(head)) {
+    left_.reserve(std::min<size_t>(left_.size() + count_, 256));
     grow(set);
   }
+  AbsorbSearch(const std::vector<AbsorbMask>& gates, uint64_t set)
+      : AbsorbSearch({}, gates.data(), gates.size(), set, gates.size()) {}
   // The set takes on bits.
   void grow(uint64_t set) {
     Absorb ab(set);
@@ -50,9 +55,11 @@ class AbsorbSearch {
       else left_[k++] = left_[i];
     }
     left_.resize(k);
-    for (; next_ < gates_.size() && !ab.done(); ++next_) {
-      if (ab.take(gates_[next_])) taken_ += gates_[next_].weight;
-      else left_.push_back(gates_[next_]);
+    for (size_t i = next_; i < count_ && i - next_ <= window_ && !ab.done(); ++i) {
+      if (!ab.take(gates_[i])) continue;
+      taken_ += gates_[i].weight;
+      left_.insert(left_.end(), gates_ + next_, gates_ + i);
+      next_ = i + 1;
     }
   }
   uint64_t taken() const { return taken_; }
@@ -60,8 +67,9 @@ class AbsorbSearch {
   void weights(const uint64_t* set, int count, uint64_t* out) const;
 
  private:
-  std::vector<AbsorbMask> gates_;  // from next_ on: not looked at yet, all left behind
-  std::vector<AbsorbMask> left_;   // left behind before that
+  const AbsorbMask* gates_;  // from next_ on: not looked at yet, all left behind
+  size_t count_, window_;
+  std::vector<AbsorbMask> left_;  // left behind before that
   size_t next_ = 0;
   uint64_t taken_ = 0;
 };

@@ -248,11 +248,14 @@ namespace {
 // Eight sets at a time, as two vectors of four words; all ones where a set
 // leaves the gate behind.  Sets that are wholly blocked take nothing more.
 #define JUQCS_ABSORB_EIGHT(NAME, ATTR)                                                              \
-  ATTR void NAME(const AbsorbMask* const* list, const size_t* size, const uint64_t* set, uint64_t* out) { \
+  ATTR void NAME(const AbsorbMask* const* list, const size_t* size, size_t window, const uint64_t* set, \
+                 uint64_t* out) {                                                                   \
     typedef uint64_t v4 __attribute__((vector_size(32)));                                           \
     v4 t[2], f[2] = {}, d[2] = {}, c[2] = {};                                                       \
     for (int h = 0; h < 2; ++h) t[h] = v4{set[4 * h], set[4 * h + 1], set[4 * h + 2], set[4 * h + 3]}; \
     bool open = true;                                                                               \
+    uint64_t sum = 0;                                                                               \
+    size_t last = 0;                                                                                \
     for (int part = 0; part < 2; ++part) {                                                          \
       const AbsorbMask* m = list[part];                                                             \
       for (size_t i = 0; i < size[part] && open; ++i) {                                             \
@@ -267,6 +270,13 @@ namespace {
         if ((i & 7) == 7) {                                                                         \
           const v4 o = (t[0] & ~f[0]) | (t[1] & ~f[1]);                                             \
           open = (o[0] | o[1] | o[2] | o[3]) != 0;                                                  \
+        }                                                                                           \
+        if (part == 1 && (i & 63) == 63) {                                                          \
+          const v4 a = c[0] + c[1];                                                                 \
+          const uint64_t now = a[0] + a[1] + a[2] + a[3];                                           \
+          if (now != sum || i < 64) last = i;                                                       \
+          sum = now;                                                                                \
+          open = open && i - last <= window;                                                        \
         }                                                                                           \
       }                                                                                             \
     }                                                                                               \
@@ -286,16 +296,16 @@ void AbsorbSearch::weights(const uint64_t* set, int count, uint64_t* out) const 
 #ifdef JUQCS_ABSORB_AVX2
   static const bool avx2 = __builtin_cpu_supports("avx2");
 #endif
-  const AbsorbMask* const list[2] = {left_.data(), gates_.data() + next_};
-  const size_t size[2] = {left_.size(), gates_.size() - next_};
+  const AbsorbMask* const list[2] = {left_.data(), gates_ + next_};
+  const size_t size[2] = {left_.size(), count_ - next_};
   for (int i = 0; i < count; i += 8) {
     uint64_t s[8] = {}, w[8];
     for (int k = 0; k < 8 && i + k < count; ++k) s[k] = set[i + k];
 #ifdef JUQCS_ABSORB_AVX2
-    if (avx2) absorb_eight_avx2(list, size, s, w);
+    if (avx2) absorb_eight_avx2(list, size, window_, s, w);
     else
 #endif
-      absorb_eight(list, size, s, w);
+      absorb_eight(list, size, window_, s, w);
     for (int k = 0; k < 8 && i + k < count; ++k) out[i + k] = taken_ + w[k];
   }
 }
@@ -434,7 +444,8 @@ void select_tiles(int n, int L, int b, int block_bits, const std::vector<Gate>& 
         if ((int)cand.size() >= kCandidates) break;
       }
       // greedy: add the candidate that lets the most gates through
-      AbsorbSearch search(rem_masks(gates, rem), tile_mask(in_tile));
+      const std::vector<AbsorbMask> rm = rem_masks(gates, rem);
+      AbsorbSearch search(rm, tile_mask(in_tile));
       for (int step = 0; step < H; ++step) {
         int best = best_candidate(search, tile_mask(in_tile), cand, [](int) { return true; });
         if (best < 0) {
@@ -501,7 +512,8 @@ std::vector<char> pick_tile(int n, int b, const std::vector<Gate>& gates, const 
     }
     if ((int)cand.size() >= kCandidates) break;
   }
-  AbsorbSearch search(rem_masks(gates, rem), tile_mask(in_tile));
+  const std::vector<AbsorbMask> rm = rem_masks(gates, rem);
+  AbsorbSearch search(rm, tile_mask(in_tile));
   while (count < b) {
     int best = best_candidate(search, tile_mask(in_tile), cand,
                               [&](int c) { return near[c] || far < far_cap; });

@@ -31,7 +31,8 @@ class Programs:
         subprocess.run(["g++", "-shared", "-pthread", *objs, "-o", lib], check=True)
         self.lib = ct.CDLL(lib)
 
-    def run(self, n, circ, dtype="c128", low=None, tile=None, pass_gates=0, relabel=0, block=0, psi=None):
+    def run(self, n, circ, dtype="c128", low=None, tile=None, pass_gates=0, relabel=0, block=0, psi=None,
+            plan_only=False):
         """(state, report) of the circuit run from psi (default |0...0>); the
         state is None where the planner leaves the circuit to the fused passes."""
         tile = min(n, 13) if tile is None else tile
@@ -46,7 +47,7 @@ class Programs:
         rc = self.lib.run_program(ct.c_int(n), ct.c_void_p(g.ctypes.data), ct.c_int64(g.size),
                                   ct.c_int(dtype == "c128"), ct.c_int(low), ct.c_int(tile),
                                   ct.c_int(pass_gates), ct.c_int(relabel), ct.c_int(block),
-                                  ct.c_void_p(v.ctypes.data), ct.byref(rep))
+                                  ct.c_void_p(None if plan_only else v.ctypes.data), ct.byref(rep))
         assert rc in (0, 1), rc
         return (v if rc == 0 else None), rep
 

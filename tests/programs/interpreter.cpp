@@ -271,8 +271,8 @@ void sizes(const BlkPlan& p, bool fp64, Report* rep) {
 
 // Plans a circuit with the given tile geometry and runs the plan on psi (2^n
 // complex numbers; qubit q on bit q before and after).  block_bits > 0: the
-// passes of a two-byte state, without its codes.  Returns 0, or 1 where the
-// plan is left to the fused passes.
+// passes of a two-byte state, without its codes; psi null: the plan alone.
+// Returns 0, or 1 where the plan is left to the fused passes.
 extern "C" int run_program(int n, const juqcs_gate* gates, int64_t count, int fp64, int low, int tile, int pass_gates,
                            int relabel, int block_bits, double* psi, Report* rep) {
   *rep = Report();
@@ -291,6 +291,7 @@ extern "C" int run_program(int n, const juqcs_gate* gates, int64_t count, int fp
     return 1;
   }
   sizes(plan, fp64 != 0, rep);
+  if (!psi) return 0;
   std::vector<cplx<double>> v(size_t(1) << n);
   std::memcpy(v.data(), psi, v.size() * sizeof v[0]);
   if (fp64) run_plan<double>(plan, block_bits, &v, rep);

@@ -1,5 +1,7 @@
 """Register-resident tile programs on the host: the planner's output run by an
 interpreter of the kernels (threads, LDS slots, layers), without a GPU."""
+import time
+
 import numpy as np
 import pytest
 
@@ -152,3 +154,23 @@ def test_rounded_phases_keep_the_norm(P, n, layers):
         drift.append(float(np.sum(np.abs(got.astype(np.clongdouble)) ** 2) / exact - 1))
         left = max(left, 2 * n + rep.misc)
     assert np.sqrt(np.mean(np.square(drift))) <= ROUNDING["c64"] * np.sqrt(left)
+
+
+@pytest.mark.parametrize("idle", [0, 8])
+def test_planning_time_is_in_proportion_to_the_gates(P, idle):
+    # one tile, all gates in one pass of many stages; idle: qubits that only the
+    # last gate acts on.  Eight times the gates: eight times the time, 64 times if
+    # every stage went through all of them
+    n = 13
+
+    def plan(count):
+        circ = W.concat(W.random_mixed(n - idle, count, 5), W.gate(W.OP_CNOT, 0, n - 1))
+        best = 1e9
+        for _ in range(3):
+            t = time.perf_counter()
+            _, rep = P.run(n, circ, "c64", plan_only=True)
+            best = min(best, time.perf_counter() - t)
+        assert rep.passes == 1
+        return best
+    few, many = plan(5000), plan(40000)
+    assert many < 24 * few, (few, many)
