@@ -182,15 +182,18 @@ struct Rewriter {
 
 }  // namespace
 
-bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<BlkGate>* out, bool keep) {
+bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<BlkGate>* out, bool keep,
+                 const std::vector<int>* order) {
+  const size_t count = order ? order->size() : gates.size();
   out->clear();
-  out->reserve(gates.size() + n);
+  out->reserve(count + n);
   Rewriter rw;
   rw.tol = tol;
   rw.keep = keep;
   rw.out = out;
   rw.open.resize(n);
-  for (const Gate& g : gates) {
+  for (size_t k = 0; k < count; ++k) {
+    const Gate& g = gates[order ? (*order)[k] : k];
     if (g.nq == 1) {
       rw.single(g.q[0], g.m);
       continue;
@@ -901,8 +904,8 @@ constexpr int kSlotBytes = 8;
 
 }  // namespace
 
-void plan_block_pass(const TileGeom& tg, const std::vector<const BlkGate*>& gates, const std::vector<int>& taken,
-                     const std::vector<Gate>& where, bool fp64, int low, BlkPlan* plan, int codes) {
+void plan_block_pass(const TileGeom& tg, const std::vector<const BlkGate*>& gates,
+                     const std::vector<std::array<int, 2>>& at_bits, bool fp64, int low, BlkPlan* plan, int codes) {
   const int tb = tg.b, K = kBlkRegs, nthr = tb - K, lanes = std::min(6, nthr), waves = nthr - lanes;
   // tile-local bit of a physical bit, or 64 + its bit in the tile number
   int local_of[64];
@@ -915,10 +918,11 @@ void plan_block_pass(const TileGeom& tg, const std::vector<const BlkGate*>& gate
     if (local_of[p] < 0) local_of[p] = 64 + tau++;
   }
   std::vector<Local> gs;
-  for (size_t i = 0; i < taken.size(); ++i) {
+  gs.reserve(gates.size());
+  for (size_t i = 0; i < gates.size(); ++i) {
     Local l;
     l.g = gates[i];
-    for (int j = 0; j < 2; ++j) l.q[j] = j < where[taken[i]].nq ? local_of[where[taken[i]].q[j]] : -1;
+    for (int j = 0; j < 2; ++j) l.q[j] = at_bits[i][j] < 0 ? -1 : local_of[at_bits[i][j]];
     gs.push_back(l);
   }
   // destination bit of each local bit (relabel swaps); the low bits of the
@@ -1292,9 +1296,14 @@ bool block_build(const BlkSchedule& bs, const std::vector<BlkGate>& bg, bool fp6
   const std::vector<Gate>& src = sched.tgates.empty() ? bs.shape : sched.tgates;
   for (size_t i = 0; i < sched.passes.size(); ++i) {
     std::vector<const BlkGate*> mine;
+    std::vector<std::array<int, 2>> at;
     mine.reserve(sched.taken[i].size());
-    for (int t : sched.taken[i]) mine.push_back(&bg[sched.tsrc.empty() ? t : sched.tsrc[t]]);
-    plan_block_pass(sched.passes[i].g, mine, sched.taken[i], src, fp64, std::min(bs.low, fp64 ? 5 : 6), plan);
+    at.reserve(sched.taken[i].size());
+    for (int t : sched.taken[i]) {
+      mine.push_back(&bg[sched.tsrc.empty() ? t : sched.tsrc[t]]);
+      at.push_back({src[t].q[0], src[t].nq > 1 ? src[t].q[1] : -1});
+    }
+    plan_block_pass(sched.passes[i].g, mine, at, fp64, std::min(bs.low, fp64 ? 5 : 6), plan);
   }
   return in_range(*plan, fp64);
 }
@@ -1302,21 +1311,18 @@ bool block_build(const BlkSchedule& bs, const std::vector<BlkGate>& bg, bool fp6
 bool block_tile_plan(const TilePlan& tp, int block_bits, BlkPlan* plan) {
   for (const TilePass& ps : tp.passes) {
     // a pass's gates in the order that its ops apply them
-    std::vector<Gate> gates;
+    std::vector<int> order;
     for (int o = ps.op_begin; o < ps.op_begin + ps.op_count; ++o)
-      for (int gi : tp.op_gates[o]) gates.push_back(tp.src[gi]);
+      order.insert(order.end(), tp.op_gates[o].begin(), tp.op_gates[o].end());
     std::vector<BlkGate> bg;
-    if (!block_gates(ps.g.n, gates, block_tol(false), &bg)) return false;
-    std::vector<Gate> where(bg.size());
-    std::vector<int> taken(bg.size());
-    std::vector<const BlkGate*> mine(bg.size());
-    for (size_t i = 0; i < bg.size(); ++i) {
-      mine[i] = &bg[i];
-      taken[i] = (int)i;
-      where[i].nq = bg[i].kind == BlkGate::CPHASE || bg[i].kind == BlkGate::CNOT ? 2 : 1;
-      for (int j = 0; j < 2; ++j) where[i].q[j] = bg[i].q[j];
+    if (!block_gates(ps.g.n, tp.src, block_tol(false), &bg, false, &order)) return false;
+    std::vector<const BlkGate*> mine;
+    std::vector<std::array<int, 2>> at;
+    for (const BlkGate& g : bg) {
+      mine.push_back(&g);
+      at.push_back({g.q[0], g.kind == BlkGate::CPHASE || g.kind == BlkGate::CNOT ? g.q[1] : -1});
     }
-    plan_block_pass(ps.g, mine, taken, where, false, 0, plan, block_bits);
+    plan_block_pass(ps.g, mine, at, false, 0, plan, block_bits);
   }
   return in_range(*plan, false);
 }

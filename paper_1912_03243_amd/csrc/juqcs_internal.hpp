@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cstddef>
 #include <cmath>
 #include <cstdint>
@@ -487,15 +488,17 @@ struct BlkPlan {
 // two-qubit gate is neither a controlled phase nor a CNOT.
 // keep: phases that happen to be 1 stay in the list, so that its shape (kinds
 // and qubits) is the same for circuits that differ in their diagonals' values.
-bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<BlkGate>* out, bool keep = false);
+// order: which of the gates, in which order (null: all as they come).
+bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<BlkGate>* out, bool keep = false,
+                 const std::vector<int>* order = nullptr);
 // A number that tells apart lists whose plans differ in more than coefficients:
 // kinds, qubits, forms, and which phases and scalars are 1 or -1.
 uint64_t block_shape(const std::vector<BlkGate>& gates);
-// Appends one pass: geometry tg, its gates (on the physical bits of where[taken[i]]).
+// Appends one pass: geometry tg, its gates and the physical bits of their qubits.
 // low: low bits that the first and the last stage keep on lanes (contiguous
 // accesses of 2^low amplitudes).
-void plan_block_pass(const TileGeom& tg, const std::vector<const BlkGate*>& gates, const std::vector<int>& taken,
-                     const std::vector<Gate>& where, bool fp64, int low, BlkPlan* plan, int codes = 0);
+void plan_block_pass(const TileGeom& tg, const std::vector<const BlkGate*>& gates,
+                     const std::vector<std::array<int, 2>>& at, bool fp64, int low, BlkPlan* plan, int codes = 0);
 // Plans a circuit as register-resident passes (arguments as plan_tiles);
 // false when it holds gates they do not take.
 bool plan_block(int n, int L, int b, const std::vector<Gate>& gates, bool fp64, int max_take, bool relabel,

@@ -21,6 +21,7 @@ inline C cx(double re, double im) { return C{re, im}; }
 inline C cadd(C a, C b) { return C{a.re + b.re, a.im + b.im}; }
 
 bool finite(C z) { return std::isfinite(z.re) && std::isfinite(z.im); }
+bool zero(C z) { return z.re == 0.0 && z.im == 0.0; }
 
 // One nonzero entry per row, in distinct columns: row r reads column
 // sigma(r), packed 3 bits per row (dim <= 8).
@@ -75,7 +76,9 @@ int union_size(const Cluster& c, const Gate& g) {
 // Fold gate g into cluster c (g applied after c), re-expressed on the union
 // of their qubits (the cluster's order, then the gate's new qubits): the
 // cluster matrix is widened by identities on the new qubits, and g's rows
-// are combined over the index bits of its qubits, column by column.
+// are combined over the index bits of its qubits, column by column.  Products
+// with zeros, most of them where gates are sparse, are left out: a fused
+// multiply-add is a call on the host.
 void merge_into(Cluster& c, const Gate& g) {
   int u[8];
   const int kold = (int)c.q.size();
@@ -109,7 +112,8 @@ void merge_into(Cluster& c, const Gate& g) {
       for (int t = 0; t < gd; ++t) v[t] = a[(size_t)(r0 | off[t]) * dim + cc];
       for (int t = 0; t < gd; ++t) {
         C acc = cx(0, 0);
-        for (int t2 = 0; t2 < gd; ++t2) acc = cmad(g.m[t * gd + t2], v[t2], acc);
+        for (int t2 = 0; t2 < gd; ++t2)
+          if (!zero(g.m[t * gd + t2]) && !zero(v[t2])) acc = cmad(g.m[t * gd + t2], v[t2], acc);
         out[(size_t)(r0 | off[t]) * dim + cc] = acc;
       }
     }
@@ -720,7 +724,6 @@ void emit_schedule(const TileSchedule& sched, const std::vector<Gate>& gates, in
   kin = std::max(1, std::min(kin, 4));  // on-chip fusion width
   const std::vector<Gate>& src = sched.tgates.empty() ? gates : sched.tgates;
   plan->src.clear();
-  if (!sched.passes.empty() && sched.passes[0].g.block_bits > 0) plan->src = src;  // (they are large)
   for (size_t i = 0; i < sched.passes.size(); ++i) {
     std::vector<Cluster> cl;
     fuse(src, sched.taken[i], kin, &cl);
@@ -740,7 +743,7 @@ void emit_schedule(const TileSchedule& sched, const std::vector<Gate>& gates, in
         mma += x;
         ++c1;
       }
-      const std::vector<Cluster> part(cl.begin() + c0, cl.begin() + c1);
+      const std::vector<Cluster> part(std::make_move_iterator(cl.begin() + c0), std::make_move_iterator(cl.begin() + c1));
       TilePass pass = sched.passes[i];
       if (c1 < cl.size()) pass.g.nswap = 0;  // swaps after the pass's last ops
       pass.op_begin = (int32_t)plan->ops.size();
@@ -769,6 +772,10 @@ void plan_tiles(int n, int L, int b, int block_bits, const std::vector<Gate>& ga
     for (int q = 0; q < n; ++q) sched.final_pos[q] = q;
   }
   emit_schedule(sched, gates, kin, plan, max_mats, max_mma);
+  if (block_bits > 0) {  // (they are large)
+    if (sched.tgates.empty()) plan->src = gates;
+    else plan->src = std::move(sched.tgates);
+  }
   if (final_pos) *final_pos = sched.final_pos;
 }
 
