@@ -71,6 +71,8 @@ struct juqcs_state {
   // instead of passes over the data)
   C gf{1.0, 0.0};
   double size = 1.0;  // product of the factors of juqcs_scale since the last init
+  bool fresh = false;  // no gate since juqcs_state_init put it into a basis state
+  uint64_t basis = 0;  // that basis state
   int phys[64];  // logical qubit -> physical bit
   size_t ring;   // next free offset inside the ring
   // per-pass timing of juqcs_run_circuit when profiling (else empty)
@@ -318,6 +320,8 @@ juqcs_status tile_gates(juqcs_state* st, const std::vector<Gate>& gates, int L, 
     if (passes) *passes = 0;
     return JUQCS_OK;
   }
+  const bool fresh = st->fresh;
+  st->fresh = false;
   const int cap = tile_mat_cap(st->dt, std::min(b, st->n));
   const int mcap = tile_mma_cap(st->dt, std::min(b, st->n));
   const int l = std::min(L, st->n);
@@ -325,7 +329,8 @@ juqcs_status tile_gates(juqcs_state* st, const std::vector<Gate>& gates, int L, 
   std::vector<int> moved;  // moved[p]: physical bit that the qubit at bit p ends on
   if (block && block_sized(st->dt, std::min(b, st->n))) {
     BlkPlan bp;
-    if (plan_block(st->n, l, b, gates, st->dt == JUQCS_C128, std::max(pass_gates, 0), rl, &bp, &moved) &&
+    if (plan_block(st->n, l, b, gates, st->dt == JUQCS_C128, std::max(pass_gates, 0), rl, &bp, &moved,
+                   fresh ? &st->basis : nullptr) &&
         fits_ring(st, bp)) {
       if (passes) *passes = (int64_t)bp.passes.size();
       if (juqcs_status rc = run_block_plan(st, bp)) return rc;
@@ -388,6 +393,7 @@ double touched(const juqcs_state* st, uint64_t mask) {
 
 juqcs_status apply_gate_plain(juqcs_state* st, const Gate& g0) {
   hipError_t e = hipSuccess;
+  st->fresh = false;
   Gate g = g0;
   if (g.nq == 1 && g.diag && !is_one(g.m[0]) && (g.m[0].re != 0.0 || g.m[0].im != 0.0)) {
     // diag(a, b) = a diag(1, b / a): the factor a goes into the state's FP64
@@ -475,6 +481,7 @@ std::vector<T> embed_real(const C* m, int K) {
 
 juqcs_status apply_fused_phys(juqcs_state* st, int k, const int* targets, const C* m,
                               juqcs_mma mode) {
+  st->fresh = false;
   if (mode == JUQCS_MMA_AUTO) mode = st->dt == JUQCS_C128 ? JUQCS_MMA_FP64 : JUQCS_MMA_FP32;
   if (st->dt == JUQCS_C128 && mode != JUQCS_MMA_FP64)
     return fail(JUQCS_ERR_DTYPE, "C128 states use FP64 matrix cores");
@@ -681,6 +688,8 @@ juqcs_status juqcs_state_init(juqcs_state* st, uint64_t basis_index) {
   for (int q = 0; q < 64; ++q) st->phys[q] = q;
   st->gf = C{1.0, 0.0};
   st->size = 1.0;
+  st->fresh = true;
+  st->basis = basis_index;
   hipError_t e = launch_init(st->dt, st->amps, st->scales, st->n, st->B, basis_index, st->stream);
   if (e != hipSuccess) return hip_fail(e, "init launch");
   return JUQCS_OK;

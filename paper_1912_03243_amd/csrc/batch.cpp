@@ -494,7 +494,8 @@ juqcs_status juqcs_batch_create(juqcs_batch** out, int count, const int* n,
     if (fuse == 0 && block_batch(n[c])) {
       std::vector<int> final_pos;
       const int b = block_bits_for(n[c]);
-      if (plan_block(n[c], std::min(7, b), b, B->dec[c], false, 0, B->relabel, &B->own[c], &final_pos)) {
+      const uint64_t zero = 0;
+      if (plan_block(n[c], std::min(7, b), b, B->dec[c], false, 0, B->relabel, &B->own[c], &final_pos, &zero)) {
         B->bplan[c] = &B->own[c];
         B->kin[c] = 1;  // gates one at a time
         set_layout(B, c, final_pos);
@@ -809,7 +810,9 @@ std::vector<Gate> seg_gates(const BranchPart& bp, const BranchSeg& sg, long long
 // A segment's gates for a setting of its diagonals, rewritten for
 // register-resident passes.
 bool seg_block_gates(const BranchPart& bp, const BranchSeg& sg, long long setting, std::vector<BlkGate>* out) {
-  return block_gates(bp.nloc, seg_gates(bp, sg, setting), block_tol(false), out, true);
+  const uint64_t zero = 0;  // the part starts there
+  return block_gates(bp.nloc, seg_gates(bp, sg, setting), block_tol(false), out, true, nullptr,
+                     sg.g0 == 0 ? &zero : nullptr);
 }
 
 // Selects the tiles of a part's segments for register-resident passes; pos:

@@ -48,6 +48,7 @@ struct Rewriter {
   std::vector<BlkGate>* out;
   struct Open {
     bool any = false;
+    double share = 0.5;  // of the set half, until a gate other than a diagonal acts
     C m[4];
   };
   std::vector<Open> open;
@@ -155,6 +156,8 @@ struct Rewriter {
         rest = times(m[2], m[0], h);
       }
       if (ranged(g.lam) && ranged(g.ph) && ranged(rest)) {
+        g.share = w.share;
+        w.share = 0.5;
         out->push_back(g);
         w.m[0] = C{1, 0};
         w.m[1] = w.m[2] = C{0, 0};
@@ -172,6 +175,7 @@ struct Rewriter {
   }
 
   void dense(int q, const C* m) {
+    open[q].share = 0.5;
     BlkGate g;
     g.kind = BlkGate::DENSE;
     g.q[0] = q;
@@ -183,7 +187,7 @@ struct Rewriter {
 }  // namespace
 
 bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<BlkGate>* out, bool keep,
-                 const std::vector<int>* order) {
+                 const std::vector<int>* order, const uint64_t* basis) {
   const size_t count = order ? order->size() : gates.size();
   out->clear();
   out->reserve(count + n);
@@ -192,6 +196,8 @@ bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<
   rw.keep = keep;
   rw.out = out;
   rw.open.resize(n);
+  if (basis)
+    for (int q = 0; q < n; ++q) rw.open[q].share = (double)((*basis >> q) & 1);
   for (size_t k = 0; k < count; ++k) {
     const Gate& g = gates[order ? (*order)[k] : k];
     if (g.nq == 1) {
@@ -218,6 +224,7 @@ bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<
       b.kind = BlkGate::CNOT;
       rw.flush(b.q[0], false);
       rw.flush(b.q[1], true);
+      rw.open[b.q[1]].share = 0.5;
     } else {
       bool swap = one(m[0]) && one(m[6]) && one(m[9]) && one(m[15]);
       for (int i = 0; i < 16; ++i)
@@ -225,6 +232,7 @@ bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<
       if (!swap) return false;
       rw.flush(b.q[0], true);
       rw.flush(b.q[1], true);
+      std::swap(rw.open[b.q[0]].share, rw.open[b.q[1]].share);
       b.kind = BlkGate::CNOT;
       out->push_back(b);
       std::swap(b.q[0], b.q[1]);
@@ -392,6 +400,7 @@ struct EOp {  // an op of a stage before it is put into layers
   R t = 0;
   std::vector<C> m;     // DENSE: the matrix
   C lam{1, 0};
+  double share = 0.5;   // ROT: of the norm, in the set half
   struct Col {          // phase where an outer bit is set
     C ph;
     int q;
@@ -538,6 +547,7 @@ struct Emitter {
         e.kind = E_ROT;
         e.lam = g.lam;
         e.ph = f0 ? inv(g.ph) : g.ph;
+        e.share = f0 ? 1.0 - g.share : g.share;
         e.t = f0 ? -g.t : g.t;
         if (f0) e.lam = mul(e.lam, g.ph);
         if (g.formb) {
@@ -659,7 +669,8 @@ R rounded(R x, bool fp64) { return fp64 ? (R)(double)x : (R)(float)(double)x; }
 // Rounds the phases and tangents of the ops to the state's precision.  What the
 // rounding multiplies a half (or quarter) of the state by is divided out of the
 // whole on average, with the scalars of the pass: left to itself, each rounding
-// changes the norm and turns that part of the state.
+// changes the norm and turns that part of the state.  (A qubit's first rotation
+// after a basis state finds all or nothing of the state in that half.)
 void round_phases(std::vector<StagePlan>& st, bool fp64) {
   for (StagePlan& s : st)
     for (EOp& e : s.ops) {
@@ -672,7 +683,7 @@ void round_phases(std::vector<StagePlan>& st, bool fp64) {
         *p = r;
       };
       if (e.kind != E_ROT && e.kind != E_PHASE) continue;
-      const double share = e.kind == E_ROT ? 0.5 : 1.0 / (1 << __builtin_popcount(e.cm));
+      const double share = e.kind == E_ROT ? e.share : 1.0 / (1 << __builtin_popcount(e.cm));
       phase(&e.ph, share);
       for (EOp::Col& c : e.col) phase(&c.ph, share / 2);
       if (e.kind == E_ROT) {
@@ -1357,10 +1368,10 @@ void append_plan(const BlkPlan& p, BlkPlan* all) {
 }
 
 bool plan_block(int n, int L, int b, const std::vector<Gate>& gates, bool fp64, int max_take, bool relabel,
-                BlkPlan* plan, std::vector<int>* final_pos) {
+                BlkPlan* plan, std::vector<int>* final_pos, const uint64_t* basis) {
   *plan = BlkPlan();
   std::vector<BlkGate> bg;
-  if (!block_gates(n, gates, block_tol(fp64), &bg)) return false;
+  if (!block_gates(n, gates, block_tol(fp64), &bg, false, nullptr, basis)) return false;
   // Both selections where a run takes far longer than planning (2^24
   // amplitudes or more), side by side, and the better by plan_ms; else the
   // second alone.

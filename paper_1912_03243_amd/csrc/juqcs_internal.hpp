@@ -471,6 +471,7 @@ struct BlkGate {
   BlkReal t = 0;
   cplx<BlkReal> ph{1, 0};   // phase of the set half (ROT, PHASE1) or quarter (CPHASE)
   cplx<BlkReal> lam{1, 0};  // scalar factor (ROT, PHASE1)
+  double share = 0.5;       // ROT: how much of the state's norm its set half holds, as far as is known
   cplx<BlkReal> m[4];       // DENSE
 };
 struct BlkPlan {
@@ -489,8 +490,9 @@ struct BlkPlan {
 // keep: phases that happen to be 1 stay in the list, so that its shape (kinds
 // and qubits) is the same for circuits that differ in their diagonals' values.
 // order: which of the gates, in which order (null: all as they come).
+// basis: the basis state that the circuit starts from (null: any state).
 bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<BlkGate>* out, bool keep = false,
-                 const std::vector<int>* order = nullptr);
+                 const std::vector<int>* order = nullptr, const uint64_t* basis = nullptr);
 // A number that tells apart lists whose plans differ in more than coefficients:
 // kinds, qubits, forms, and which phases and scalars are 1 or -1.
 uint64_t block_shape(const std::vector<BlkGate>& gates);
@@ -502,7 +504,7 @@ void plan_block_pass(const TileGeom& tg, const std::vector<const BlkGate*>& gate
 // Plans a circuit as register-resident passes (arguments as plan_tiles);
 // false when it holds gates they do not take.
 bool plan_block(int n, int L, int b, const std::vector<Gate>& gates, bool fp64, int max_take, bool relabel,
-                BlkPlan* plan, std::vector<int>* final_pos);
+                BlkPlan* plan, std::vector<int>* final_pos, const uint64_t* basis = nullptr);
 
 // The relative miss of a matrix entry by the rotation form up to which a
 // gate is not kept dense: an FP64 rounding step, or far below an FP32 one.

@@ -47,6 +47,7 @@ class Programs:
         rc = self.lib.run_program(ct.c_int(n), ct.c_void_p(g.ctypes.data), ct.c_int64(g.size),
                                   ct.c_int(dtype == "c128"), ct.c_int(low), ct.c_int(tile),
                                   ct.c_int(pass_gates), ct.c_int(relabel), ct.c_int(block),
+                                  ct.byref(ct.c_uint64(0)) if psi is None else None,
                                   ct.c_void_p(None if plan_only else v.ctypes.data), ct.byref(rep))
         assert rc in (0, 1), rc
         return (v if rc == 0 else None), rep

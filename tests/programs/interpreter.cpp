@@ -271,10 +271,11 @@ void sizes(const BlkPlan& p, bool fp64, Report* rep) {
 
 // Plans a circuit with the given tile geometry and runs the plan on psi (2^n
 // complex numbers; qubit q on bit q before and after).  block_bits > 0: the
-// passes of a two-byte state, without its codes; psi null: the plan alone.
+// passes of a two-byte state, without its codes; basis: the basis state that psi
+// is (null: unknown); psi null: the plan alone.
 // Returns 0, or 1 where the plan is left to the fused passes.
 extern "C" int run_program(int n, const juqcs_gate* gates, int64_t count, int fp64, int low, int tile, int pass_gates,
-                           int relabel, int block_bits, double* psi, Report* rep) {
+                           int relabel, int block_bits, const uint64_t* basis, double* psi, Report* rep) {
   *rep = Report();
   std::vector<Gate> gs(count);
   std::string err;
@@ -287,7 +288,7 @@ extern "C" int run_program(int n, const juqcs_gate* gates, int64_t count, int fp
     TilePlan tp;
     plan_tiles(n, L, tile, block_bits, gs, &tp, 3, 0, pass_gates, 0, relabel >= 0, &moved);
     if (!block_tile_plan(tp, block_bits, &plan)) return 1;
-  } else if (!plan_block(n, L, tile, gs, fp64 != 0, pass_gates, relabel >= 0, &plan, &moved)) {
+  } else if (!plan_block(n, L, tile, gs, fp64 != 0, pass_gates, relabel >= 0, &plan, &moved, basis)) {
     return 1;
   }
   sizes(plan, fp64 != 0, rep);

@@ -174,3 +174,19 @@ def test_planning_time_is_in_proportion_to_the_gates(P, idle):
         return best
     few, many = plan(5000), plan(40000)
     assert many < 24 * few, (few, many)
+
+
+def test_first_rotations_find_a_basis_state(P):
+    # the set half of a qubit in |0> is empty: a rounded phase there changes
+    # nothing, and nothing has to be made up for
+    n, known, unknown = 13, [], []
+    start = np.zeros(1 << n)
+    start[0] = 1
+    for seed in range(12):
+        circ = W.layered_brick(n, 1, seed=seed)
+        exact = np.sum(np.abs(exact_state(n, circ)) ** 2)
+        for psi, drift in ((None, known), (start, unknown)):
+            got, _ = P.run(n, circ, "c64", psi=psi)
+            drift.append(float(np.sum(np.abs(got.astype(np.clongdouble)) ** 2) / exact - 1))
+    rms = lambda x: np.sqrt(np.mean(np.square(x)))
+    assert rms(known) < rms(unknown)
