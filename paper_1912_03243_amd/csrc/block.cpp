@@ -48,7 +48,7 @@ struct Rewriter {
   std::vector<BlkGate>* out;
   struct Open {
     bool any = false;
-    double share = 0.5;  // of the set half, until a gate other than a diagonal acts
+    double share = 0.5;  // of the norm, in the set half, as far as is known
     C m[4];
   };
   std::vector<Open> open;
@@ -157,7 +157,7 @@ struct Rewriter {
       }
       if (ranged(g.lam) && ranged(g.ph) && ranged(rest)) {
         g.share = w.share;
-        w.share = 0.5;
+        w.share = moved(w.share, n2);
         out->push_back(g);
         w.m[0] = C{1, 0};
         w.m[1] = w.m[2] = C{0, 0};
@@ -171,11 +171,20 @@ struct Rewriter {
       }
     }
     w.any = false;
+    w.share = moved(w.share, n2);
     dense(q, w.m);
   }
 
+  // The share after a matrix with entries of sizes squared n2: a column's where
+  // the qubit was in |0> or |1>.  (Gates that are diagonal on the qubit keep it,
+  // so the second rotation finds this share whatever has entangled the qubit.)
+  static double moved(double share, const R* n2) {
+    if (share != 0.0 && share != 1.0) return 0.5;
+    const R a = n2[share == 0.0 ? 0 : 1], b = n2[share == 0.0 ? 2 : 3];
+    return a + b > 0 ? (double)(b / (a + b)) : 0.5;
+  }
+
   void dense(int q, const C* m) {
-    open[q].share = 0.5;
     BlkGate g;
     g.kind = BlkGate::DENSE;
     g.q[0] = q;
@@ -224,7 +233,9 @@ bool block_gates(int n, const std::vector<Gate>& gates, double tol, std::vector<
       b.kind = BlkGate::CNOT;
       rw.flush(b.q[0], false);
       rw.flush(b.q[1], true);
-      rw.open[b.q[1]].share = 0.5;
+      const double c = rw.open[b.q[0]].share;
+      double& t = rw.open[b.q[1]].share;
+      t = c == 0.0 ? t : c == 1.0 ? 1.0 - t : 0.5;
     } else {
       bool swap = one(m[0]) && one(m[6]) && one(m[9]) && one(m[15]);
       for (int i = 0; i < 16; ++i)
@@ -669,8 +680,8 @@ R rounded(R x, bool fp64) { return fp64 ? (R)(double)x : (R)(float)(double)x; }
 // Rounds the phases and tangents of the ops to the state's precision.  What the
 // rounding multiplies a half (or quarter) of the state by is divided out of the
 // whole on average, with the scalars of the pass: left to itself, each rounding
-// changes the norm and turns that part of the state.  (A qubit's first rotation
-// after a basis state finds all or nothing of the state in that half.)
+// changes the norm and turns that part of the state.  (The first rotations after
+// a basis state find other shares of it in that half, which the gates tell.)
 void round_phases(std::vector<StagePlan>& st, bool fp64) {
   for (StagePlan& s : st)
     for (EOp& e : s.ops) {
